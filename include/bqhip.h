@@ -166,6 +166,9 @@ typedef void (*bq_dealloc_fn)(void* ptr, void* alloc_ctx);
  * has BQCD hand a gauge field and a source to a GPU library and receive the solution).
  *   hbm_budget_bytes  bound on the device memory the context may hold (0 = 90% of the
  *                     device's free memory); an allocation above it fails with BQ_ERR_OOM.
+ *                     Without a caller's allocator, blocks that buffers give back are kept for
+ *                     the next buffers of their size (at most 8 GiB and an eighth of the budget,
+ *                     within the budget) until the context is freed or an allocation needs room.
  *   alloc, dealloc    route every device allocation of the context (fields, links, clover,
  *                     workspaces) through the caller's allocator; both NULL = hipMalloc/hipFree.
  *                     Before a block goes back to dealloc the library waits for the device

@@ -138,10 +138,88 @@ static Geom with_order(Geom g, int order)
     return g;
 }
 
+// Device blocks that a context's buffers gave back, kept for its next ones (contexts on hipMalloc
+// only; a caller's allocator sees every block come and go).  hipMalloc, the clearing of the new
+// block and hipFree, which waits for the device, cost more than the work of many calls: a 24^3x48
+// FP64 Mhat^dag Mhat took 1.1 ms, 0.56 ms of it in its stencils, and a 32^3x64 12-column FP32 one
+// between 7.5 and 113 ms.  The pool holds at most kPoolMost bytes, an eighth of the budget and
+// what the budget leaves; it is given back when an allocation fails anywhere in the process, when
+// the budget needs it, and with the context.
+struct BlockPool {
+    static const size_t kPoolMost = (size_t)8 << 30;
+    std::mutex mu;
+    std::multimap<size_t, void*> idle;  // by size
+    size_t bytes = 0;
+    bool dirty = false;  // a block may still be in use by work queued before it came back
+    int device = 0;
+    BlockPool();
+    ~BlockPool();
+    // a block of n bytes that no queued work can touch any more; nullptr if there is none or the
+    // device cannot be waited for
+    void* take(size_t n)
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        auto it = idle.find(n);
+        if (it == idle.end()) return nullptr;
+        if (dirty) {
+            if (hipDeviceSynchronize() != hipSuccess) return nullptr;
+            dirty = false;
+        }
+        void* p = it->second;
+        bytes -= n;
+        idle.erase(it);
+        return p;
+    }
+    // keep a block (done: no queued work uses it any more); false if there is no room for it
+    bool put(void* p, size_t n, size_t most, bool done)
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        if (bytes + n > std::min(most, kPoolMost)) return false;
+        idle.emplace(n, p);
+        bytes += n;
+        dirty = dirty || !done;
+        return true;
+    }
+    void trim()
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        int cur = device;
+        (void)hipGetDevice(&cur);
+        if (cur != device) (void)hipSetDevice(device);
+        for (auto& b : idle) (void)hipFree(b.second);  // waits for the device
+        if (cur != device) (void)hipSetDevice(cur);
+        idle.clear();
+        bytes = 0;
+        dirty = false;
+    }
+};
+// every context's pool, so that an allocation that fails can have all of them given back
+static std::mutex pools_mu;
+static std::set<BlockPool*> pools;
+BlockPool::BlockPool()
+{
+    std::lock_guard<std::mutex> lk(pools_mu);
+    pools.insert(this);
+}
+BlockPool::~BlockPool()
+{
+    {
+        std::lock_guard<std::mutex> lk(pools_mu);
+        pools.erase(this);
+    }
+    trim();
+}
+static void trim_pools()
+{
+    std::lock_guard<std::mutex> lk(pools_mu);
+    for (BlockPool* p : pools) p->trim();
+}
+
 struct bq_context_s {
     int device = 0;
     uint64_t budget = 0;
     uint64_t used = 0;
+    BlockPool pool;
     hipStream_t stream = nullptr;
     std::map<std::pair<int, int>, Tune> tune;  // (prec, ncol) -> config
     unsigned nalloc = 0;                       // allocation counter (skews)
@@ -167,6 +245,11 @@ static void ctx_release_handle(bq_context ctx)
 // unskewed the same tile of all of them would fall into the same L2 sets.
 static const size_t kSkew = 17 * 128;
 
+// What of a new buffer or work field is zeroed: all of it; of a field only the sites that pad its
+// last tile, which the vector kernels read along with the others and nothing writes; nothing (the
+// stencils read and write real sites only)
+enum Clear { CLEAR_ALL, CLEAR_PAD, CLEAR_NONE };
+
 struct DevBuf {
     bq_context ctx = nullptr;
     void* raw = nullptr;
@@ -176,7 +259,8 @@ struct DevBuf {
     DevBuf(const DevBuf&) = delete;
     DevBuf& operator=(const DevBuf&) = delete;
     ~DevBuf() { release(); }
-    void release()
+    // done: the caller has waited for all work that uses the block
+    void release(bool done = false)
     {
         if (raw) {
             if (ctx->dealloc) {
@@ -184,7 +268,7 @@ struct DevBuf {
                 // queued on it first (hipFree synchronizes the same way)
                 (void)hipDeviceSynchronize();
                 ctx->dealloc(raw, ctx->alloc_ctx);
-            } else {
+            } else if (!ctx->pool.put(raw, bytes, ctx->budget / 8, done)) {
                 (void)hipFree(raw);
             }
             ctx->used -= bytes;
@@ -192,7 +276,8 @@ struct DevBuf {
         raw = p = nullptr;
         bytes = 0;
     }
-    int alloc(bq_context c, size_t n)
+    // n bytes; those not cleared are written before they are read, and need no waiting
+    int alloc(bq_context c, size_t n, Clear clear = CLEAR_ALL)
     {
         release();
         ctx = c;
@@ -211,20 +296,28 @@ struct DevBuf {
                 raw = nullptr;
                 return fail(BQ_ERR_INVALID, "the caller's allocator returned a block not aligned to 256 bytes");
             }
-        } else {
+        } else if ((raw = c->pool.take(total)) == nullptr) {
+            if (c->used + total + c->pool.bytes > c->budget) c->pool.trim();
             e = hipMalloc(&raw, total);
+            if (e == hipErrorOutOfMemory) {
+                (void)hipGetLastError();
+                trim_pools();
+                e = hipMalloc(&raw, total);
+            }
             if (e != hipSuccess) {
                 raw = nullptr;
                 return fail(BQ_ERR_OOM, "hipMalloc(%zu) failed: %s", total, hipGetErrorString(e));
             }
         }
-        // zero on the context stream and wait, so that work on any stream sees zeros
-        e = hipMemsetAsync(raw, 0, total, c->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-        if (e != hipSuccess) return fail(BQ_ERR_DEVICE, "zeroing new device memory failed: %s", hipGetErrorString(e));
         p = (char*)raw + skew;
         bytes = total;
         c->used += total;
+        if (clear == CLEAR_ALL) {
+            // zero on the context stream and wait, so that work on any stream sees zeros
+            e = hipMemsetAsync(raw, 0, total, c->stream);
+            if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+            if (e != hipSuccess) return fail(BQ_ERR_DEVICE, "zeroing new device memory failed: %s", hipGetErrorString(e));
+        }
         return BQ_OK;
     }
     template <typename T> T* as() const { return (T*)p; }
@@ -398,15 +491,27 @@ static void vec_layout(const Geom& g, int prec, int nh, int ncol, Vec& v, size_t
     scale_bytes = prec == PREC_F16 ? v.sstride * ncol * sizeof(float) : 0;
 }
 
-static int alloc_vec(bq_context ctx, const Geom& g, int prec, int nh, int ncol, DevBuf& data, DevBuf& scale, Vec& v)
+static int alloc_vec(bq_context ctx, const Geom& g, int prec, int nh, int ncol, DevBuf& data, DevBuf& scale, Vec& v,
+                     Clear clear = CLEAR_ALL)
 {
     size_t db = 0, sb = 0;
     vec_layout(g, prec, nh, ncol, v, db, sb);
-    CHK(data.alloc(ctx, db));
+    CHK(data.alloc(ctx, db, clear));
     v.d = data.p;
     if (sb) {
-        CHK(scale.alloc(ctx, sb));
+        CHK(scale.alloc(ctx, sb, clear));
         v.s = scale.as<float>();
+    }
+    if (clear == CLEAR_PAD && g.Vh % kTile) {
+        const size_t ub = unit_bytes(prec), tile = (size_t)kTile * spinor_nu(prec);
+        for (int h = 0; h < nh; h++) {
+            HIPCHK(hipMemset2DAsync((char*)v.d + ((h + 1) * v.half_units - tile) * ub, v.cstride * ub, 0, tile * ub, ncol,
+                                    ctx->stream));
+            if (sb)
+                HIPCHK(hipMemset2DAsync(v.s + (h + 1) * v.half_sites - kTile, v.sstride * sizeof(float), 0,
+                                        kTile * sizeof(float), ncol, ctx->stream));
+        }
+        HIPCHK(hipStreamSynchronize(ctx->stream));
     }
     return BQ_OK;
 }
@@ -986,7 +1091,7 @@ static int block_engine(bq_op op, const Vec& B, int ncol, int nshift, const doub
     Vec R, P, W, Q, T;
     int nb_ = 0;
     for (Vec* v : {&R, &P, &W, &Q, &T}) {
-        CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, d[nb_], sc[nb_], *v));
+        CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, d[nb_], sc[nb_], *v, CLEAR_PAD));
         nb_++;
     }
     BlockFields f{};
@@ -997,7 +1102,7 @@ static int block_engine(bq_op op, const Vec& B, int ncol, int nshift, const doub
             continue;
         }
         Vec v;
-        CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, d[nb_], sc[nb_], v));
+        CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, d[nb_], sc[nb_], v, CLEAR_PAD));
         nb_++;
         f.p[s] = v.all();
     }
@@ -1336,17 +1441,17 @@ static int bicg_views(bq_op op, const Vec& b_even, const Vec& b_odd, const Vec& 
     DevBuf d[16], sc[16];
     Vec bh, x64, r64, q64, t64, r, rh, p, v, s_, t, te, xi;
     int k = 0;
-    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, d[k], sc[k], bh)); k++;
-    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, d[k], sc[k], x64)); k++;
-    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, d[k], sc[k], r64)); k++;
-    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, d[k], sc[k], q64)); k++;
-    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, d[k], sc[k], t64)); k++;
+    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, d[k], sc[k], bh, CLEAR_PAD)); k++;
+    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, d[k], sc[k], x64, CLEAR_PAD)); k++;
+    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, d[k], sc[k], r64, CLEAR_PAD)); k++;
+    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, d[k], sc[k], q64, CLEAR_PAD)); k++;
+    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, d[k], sc[k], t64, CLEAR_PAD)); k++;
     for (Vec* vv : {&r, &rh, &p, &v, &s_, &t, &te}) {
-        CHK(alloc_vec(ctx, g, prec, 1, ncol, d[k], sc[k], *vv));
+        CHK(alloc_vec(ctx, g, prec, 1, ncol, d[k], sc[k], *vv, CLEAR_PAD));
         k++;
     }
     if (prec == PREC_F64) xi = x64;
-    else CHK(alloc_vec(ctx, g, prec, 1, ncol, d[k], sc[k], xi));
+    else CHK(alloc_vec(ctx, g, prec, 1, ncol, d[k], sc[k], xi, CLEAR_PAD));
     const int n = (int)bh.half_sites;
     DevBuf part, scal, ints;
     CHK(part.alloc(ctx, sizeof(double) * (size_t)hw * ncol * 4));
@@ -1562,7 +1667,7 @@ int bq_context_create(int device, uint64_t hbm_budget_bytes, bq_alloc_fn alloc, 
     HIPCHK(hipSetDevice(device));
     CHK(scratch_resolve(device));
     auto c = std::make_unique<bq_context_s>();
-    c->device = device;
+    c->device = c->pool.device = device;
     size_t fr = 0, tot = 0;
     HIPCHK(hipMemGetInfo(&fr, &tot));
     c->budget = hbm_budget_bytes ? hbm_budget_bytes : (uint64_t)(0.9 * (double)fr);
@@ -1613,7 +1718,7 @@ int bq_gauge_upload(bq_context ctx, const int dims[4], const double* links, int 
     DevBuf stage;
     const double2* canon = (const double2*)links;
     if (!links_on_device) {
-        CHK(stage.alloc(ctx, nbytes));
+        CHK(stage.alloc(ctx, nbytes, CLEAR_NONE));
         HIPCHK(hipMemcpyAsync(stage.p, links, nbytes, hipMemcpyHostToDevice, ctx->stream));
         canon = stage.as<double2>();
     }
@@ -1625,7 +1730,7 @@ int bq_gauge_upload(bq_context ctx, const int dims[4], const double* links, int 
         const size_t nl = 4 * V;
         const int np = link_su3_parts(nl);
         DevBuf part;
-        CHK(part.alloc(ctx, sizeof(double) * np));
+        CHK(part.alloc(ctx, sizeof(double) * np, CLEAR_NONE));
         HIPCHK(launch_link_su3_dev(canon, nl, part.as<double>(), ctx->stream));
         std::vector<double> h(np);
         HIPCHK(hipMemcpyAsync(h.data(), part.p, sizeof(double) * np, hipMemcpyDeviceToHost, ctx->stream));
@@ -1643,7 +1748,7 @@ int bq_gauge_upload(bq_context ctx, const int dims[4], const double* links, int 
         ls.prec = forms[f][0];
         ls.recon = forms[f][1];
         const size_t per = Vp * link_nu(ls.prec, ls.recon) * unit_bytes(ls.prec) + kSkew;
-        CHK(ls.buf.alloc(ctx, per * 8));
+        CHK(ls.buf.alloc(ctx, per * 8, CLEAR_NONE));
         for (int k = 0; k < 8; k++) ls.U[k] = (char*)ls.buf.p + per * k;
         for (int p = 0; p < 2; p++) {
             void* dst[4] = {(void*)ls.U[p * 4 + 0], (void*)ls.U[p * 4 + 1], (void*)ls.U[p * 4 + 2], (void*)ls.U[p * 4 + 3]};
@@ -1670,7 +1775,7 @@ int bq_gauge_plaquette(bq_gauge g, double* plaq)
     HIPCHK(hipSetDevice(ctx->device));
     const int nw = pad_sites(g->g.Vh) / kTile;
     DevBuf part;
-    CHK(part.alloc(ctx, sizeof(double) * 2 * nw));
+    CHK(part.alloc(ctx, sizeof(double) * 2 * nw, CLEAR_NONE));
     const LinkSet* ls = g->get(PREC_F64, 18);
     const double2* U[8];
     for (int k = 0; k < 8; k++) U[k] = (const double2*)ls->U[k];
@@ -1749,7 +1854,7 @@ static int op_build(bq_gauge g, double kappa, double csw, double mu, int lean_pr
     HIPCHK(hipSetDevice(ctx->device));
     const size_t Vp = pad_sites(g->g.Vh);
     if (!g->B[0].p) {
-        for (int p = 0; p < 2; p++) CHK(g->B[p].alloc(ctx, Vp * 36 * 16));
+        for (int p = 0; p < 2; p++) CHK(g->B[p].alloc(ctx, Vp * 36 * 16, CLEAR_NONE));
         CloverBuild cb;
         cb.g = g->g;
         const LinkSet* ls = g->get(PREC_F64, 18);
@@ -1762,15 +1867,15 @@ static int op_build(bq_gauge g, double kappa, double csw, double mu, int lean_pr
     op->gauge = g;
     op->mu = mu;
     for (int p = 0; p < 2; p++) {
-        CHK(op->T[PREC_F64][p].alloc(ctx, Vp * 36 * 16));
-        if (lean_prec < 0 || p == 0) CHK(op->Tinv[PREC_F64][p].alloc(ctx, Vp * 36 * 16));
+        CHK(op->T[PREC_F64][p].alloc(ctx, Vp * 36 * 16, CLEAR_NONE));
+        if (lean_prec < 0 || p == 0) CHK(op->Tinv[PREC_F64][p].alloc(ctx, Vp * 36 * 16, CLEAR_NONE));
     }
     for (int prec : {PREC_F32, PREC_F16}) {
         if (lean_prec >= 0 && prec != lean_prec) continue;
         const size_t bytes = Vp * clover_nu(prec) * unit_bytes(prec);
         for (int p = 0; p < 2; p++) {
-            if (lean_prec < 0 || p == 1) CHK(op->T[prec][p].alloc(ctx, bytes));
-            if (lean_prec < 0 || p == 0) CHK(op->Tinv[prec][p].alloc(ctx, bytes));
+            if (lean_prec < 0 || p == 1) CHK(op->T[prec][p].alloc(ctx, bytes, CLEAR_NONE));
+            if (lean_prec < 0 || p == 0) CHK(op->Tinv[prec][p].alloc(ctx, bytes, CLEAR_NONE));
         }
     }
     DevBuf own;
@@ -1859,7 +1964,7 @@ int bq_field_put(bq_field f, const double* src, int src_on_device, void* stream)
     DevBuf stage;
     const double2* canon = (const double2*)src;
     if (!src_on_device) {
-        CHK(stage.alloc(ctx, bytes));
+        CHK(stage.alloc(ctx, bytes, CLEAR_NONE));
         HIPCHK(hipMemcpyAsync(stage.p, src, bytes, hipMemcpyHostToDevice, ctx->stream));
         canon = stage.as<double2>();
     }
@@ -1883,7 +1988,7 @@ int bq_field_get(bq_field f, double* dst, int dst_on_device, void* stream)
     DevBuf stage;
     double2* canon = (double2*)dst;
     if (!dst_on_device) {
-        CHK(stage.alloc(ctx, bytes));
+        CHK(stage.alloc(ctx, bytes, CLEAR_NONE));
         // keep the sites outside the field's subset as the caller had them
         if (f->subset != BQ_FULL) HIPCHK(hipMemcpyAsync(stage.p, dst, bytes, hipMemcpyHostToDevice, ctx->stream));
         canon = stage.as<double2>();
@@ -1939,7 +2044,7 @@ static int apply_impl(bq_op op, int kind, bq_field in, bq_field out, hipStream_t
         return tv(c, dag, 1, ie.all(), io.all(), oo.all(), -k, nullptr, 0, 0);
     }
     case BQ_OP_MDAGM: {
-        if (!scr.a.d) CHK(alloc_vec(ctx, g, prec, 2, ncol, scr.d1, scr.s1, scr.a));
+        if (!scr.a.d) CHK(alloc_vec(ctx, g, prec, 2, ncol, scr.d1, scr.s1, scr.a, CLEAR_NONE));
         Vec ie = parity_vec(in, 0), io = parity_vec(in, 1), oe = parity_vec(out, 0), oo = parity_vec(out, 1);
         CHK(tv(c, 0, 0, io.all(), ie.all(), scr.a.half(0), -k, nullptr, 0, 0));
         CHK(tv(c, 0, 1, ie.all(), io.all(), scr.a.half(1), -k, nullptr, 0, 0));
@@ -1949,14 +2054,14 @@ static int apply_impl(bq_op op, int kind, bq_field in, bq_field out, hipStream_t
     case BQ_OP_MHAT:
     case BQ_OP_MHATDAG: {
         const int dag = kind == BQ_OP_MHATDAG;
-        if (!scr.a.d) CHK(alloc_vec(ctx, g, prec, 1, ncol, scr.d1, scr.s1, scr.a));
+        if (!scr.a.d) CHK(alloc_vec(ctx, g, prec, 1, ncol, scr.d1, scr.s1, scr.a, CLEAR_NONE));
         Vec io = parity_vec(in, 1), oo = parity_vec(out, 1);
         CHK(k1(c, dag, io.all(), scr.a.all()));
         return tv(c, dag, 1, scr.a.all(), io.all(), oo.all(), -k * k, nullptr, 0, 0);
     }
     case BQ_OP_MHATDAG_MHAT: {
-        if (!scr.a.d) CHK(alloc_vec(ctx, g, prec, 1, ncol, scr.d1, scr.s1, scr.a));
-        if (!scr.b.d) CHK(alloc_vec(ctx, g, prec, 1, ncol, scr.d2, scr.s2, scr.b));
+        if (!scr.a.d) CHK(alloc_vec(ctx, g, prec, 1, ncol, scr.d1, scr.s1, scr.a, CLEAR_NONE));
+        if (!scr.b.d) CHK(alloc_vec(ctx, g, prec, 1, ncol, scr.d2, scr.s2, scr.b, CLEAR_NONE));
         Vec io = parity_vec(in, 1), oo = parity_vec(out, 1);
         CHK(k1(c, 0, io.all(), scr.a.all()));
         CHK(tv(c, 0, 1, scr.a.all(), io.all(), scr.b.all(), -k * k, nullptr, 0, 0));
@@ -2007,7 +2112,10 @@ int bq_apply(bq_op op, int kind, bq_field in, bq_field out, void* stream)
     hipStream_t st = stream ? (hipStream_t)stream : ctx->stream;
     Scratch scr;
     int rc = apply_impl(op, kind, in, out, st, scr);
-    if (scr.a.d || scr.b.d) HIPCHK(hipStreamSynchronize(st));  // scratch is freed on return
+    if (scr.a.d || scr.b.d) {  // scratch goes back on return
+        HIPCHK(hipStreamSynchronize(st));
+        for (DevBuf* b : {&scr.d1, &scr.s1, &scr.d2, &scr.s2}) b->release(true);
+    }
     return rc;
 }
 
@@ -2234,9 +2342,9 @@ static int ms_block(bq_op op, bq_field b, int nshift, const double* shifts, int 
     // FP64 residuals per shift
     DevBuf dq, sq, dt, stt, dw, sw, part, sum;
     Vec q, t, w;
-    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, dq, sq, q));
-    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, dt, stt, t));
-    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, dw, sw, w));
+    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, dq, sq, q, CLEAR_PAD));
+    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, dt, stt, t, CLEAR_PAD));
+    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, dw, sw, w, CLEAR_PAD));
     const int hw = pad_sites(g.Vh) / kTile;
     const int n = (int)bv.half_sites;
     CHK(part.alloc(ctx, sizeof(double) * (size_t)hw * ncol));
@@ -2335,11 +2443,11 @@ int bq_solve_multishift(bq_op op, bq_field b, int nshift, const double* shifts, 
     // workspace: r, p, w, q (odd), t (even), a direction per shift other than the base
     DevBuf dr, sr, dp, spp, dw, sw, dq, sq, dt, stt;
     Vec r, p, w, q, t;
-    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, dr, sr, r));
-    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, dp, spp, p));
-    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, dw, sw, w));
-    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, dq, sq, q));
-    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, dt, stt, t));
+    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, dr, sr, r, CLEAR_PAD));
+    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, dp, spp, p, CLEAR_PAD));
+    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, dw, sw, w, CLEAR_PAD));
+    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, dq, sq, q, CLEAR_PAD));
+    CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, dt, stt, t, CLEAR_PAD));
     std::vector<std::unique_ptr<DevBuf>> pkbuf;
     MsFields f{};
     f.r = r.all();
@@ -2354,7 +2462,7 @@ int bq_solve_multishift(bq_op op, bq_field b, int nshift, const double* shifts, 
         pkbuf.emplace_back(new DevBuf);
         DevBuf dummy;
         Vec v;
-        CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, *pkbuf.back(), dummy, v));
+        CHK(alloc_vec(ctx, g, PREC_F64, 1, ncol, *pkbuf.back(), dummy, v, CLEAR_PAD));
         f.pk[k] = v.all();
     }
     const int hw = pad_sites(g.Vh) / kTile;
@@ -2994,7 +3102,7 @@ static int admit(bq_server S, Request* q, Session* s)
     }
     const size_t V = 2 * (size_t)g.Vh;
     const size_t bytes = (size_t)q->nrhs * V * 12 * 16;
-    if (s->stage.bytes < bytes) CHK(s->stage.alloc(ctx, bytes));
+    if (s->stage.bytes < bytes) CHK(s->stage.alloc(ctx, bytes, CLEAR_NONE));
     HIPCHK(hipMemcpyAsync(s->stage.p, q->b, bytes, hipMemcpyDefault, s->st));  // b in host or device memory
     q->slots.clear();
     for (int c = 0, k = 0; c < s->cap && k < q->nrhs; c++)
@@ -3096,7 +3204,7 @@ static int retire(bq_server S, Session* s, std::vector<Request*>& done)
     const size_t V = 2 * (size_t)g.Vh;
     for (Request* q : done) {
         const size_t bytes = (size_t)q->nrhs * V * 12 * 16;
-        if (s->stage.bytes < bytes) CHK(s->stage.alloc(S->ctx, bytes));
+        if (s->stage.bytes < bytes) CHK(s->stage.alloc(S->ctx, bytes, CLEAR_NONE));
         for (size_t k = 0; k < q->slots.size(); k++)
             for (int p = 0; p < 2; p++)
                 HIPCHK(launch_spinor_export(col_arg(s->xfull, p, q->slots[k]), 1, g, p, PREC_F64,
