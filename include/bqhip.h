@@ -377,7 +377,10 @@ int bq_time_copy(bq_context ctx, uint64_t bytes, int reps, void* stream, double*
  * the t-marching stencil and on other lattices); 2 is order 1 where it applies and, on any lattice
  * with a multiple of 8 tile blocks, has each XCD walk its tile blocks once per column-group chunk
  * (fewer columns in flight per XCD; links and clover are read once per chunk).  Errors: BQ_ERR_INVALID for a configuration
- * that is not compiled or out of range.  Results do not depend on the configuration. */
+ * that is not compiled or out of range.  Results do not depend on the configuration.
+ * A configuration of the default's shape (R, bs, march, lds and order as bq_tune_get gives them when
+ * nothing was set; either link form) names the default: the size of each launch picks its kernel, on
+ * small lattices one with a workgroup of eight waves, one per half hop, for each tile and column. */
 int bq_tune_get(bq_context ctx, int prec, int nrhs, int* recon, int* R, int* bs, int* march, int* lds, int* order);
 int bq_tune_set(bq_context ctx, int prec, int nrhs, int recon, int R, int bs, int march, int lds, int order);
 /* Time the candidate configurations for (op's lattice, prec, nrhs) on op and keep the fastest. */

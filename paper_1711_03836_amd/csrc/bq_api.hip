@@ -112,6 +112,7 @@ struct Tune {
     int order = 0;  // tile traversal of the plain and tile-shared stencils: 0 blocks of 4x4 (z,t) planes,
                     // 1 one z slab per XCD walked plane by plane in t, 2 as 1 with the column-group
                     // chunks walked one after another on each XCD
+    bool chosen = false;  // set by the user or the autotuner; otherwise the launch's size picks the kernel
 };
 
 // The geometry a stencil launch walks for traversal order `order` (tile_at, item_of).  Order 1 cuts the
@@ -522,10 +523,8 @@ static int alloc_vec(bq_context ctx, const Geom& g, int prec, int nh, int ncol, 
 
 static int max_R(int prec) { return prec == PREC_F64 ? 2 : 4; }
 
-static Tune get_tune(bq_context ctx, int prec, int ncol)
+static Tune default_tune(int prec, int ncol)
 {
-    auto it = ctx->tune.find({prec, ncol});
-    if (it != ctx->tune.end()) return it->second;
     Tune t;
     t.recon = prec == PREC_F16 ? 12 : 18;
     t.bs = ncol > 1 ? 128 : 256;
@@ -538,8 +537,64 @@ static Tune get_tune(bq_context ctx, int prec, int ncol)
     return t;
 }
 
+// The configuration as tune_set, a tuning file or the autotuner gives it.  One of the default's shape
+// names the default, in the link form it gives: the launch's size picks the kernel (pick_kernel).
+static Tune make_tune(int prec, int ncol, int recon, int R, int bs, int march, int lds, int order)
+{
+    const Tune d = default_tune(prec, ncol);
+    return Tune{recon, R, bs, march, lds, order, R != d.R || bs != d.bs || march != 0 || lds != 0 || order != 0};
+}
+
+static Tune get_tune(bq_context ctx, int prec, int ncol)
+{
+    auto it = ctx->tune.find({prec, ncol});
+    return it != ctx->tune.end() ? it->second : default_tune(prec, ncol);
+}
+
+// The kernel of a launch whose configuration nobody chose, by tiles and columns (nact: the columns
+// that are worked on).  Times are of Mhat (K1 + K2, 18-real links; FP16 12) in us on one MI355X.
+static void pick_kernel(HopLaunch& L, const Geom& g, int nact, int& order)
+{
+    const int n = L.ncol;
+    const long items = (long)g.ntiles * nact;
+    const bool f64 = L.prec == PREC_F64, f16 = L.prec == PREC_F16;
+    L.march = L.lds = 0;
+    // One round of the hop-split kernel's workgroups on 256 CUs (two FP64 or four FP32/FP16 per CU
+    // by their registers and LDS).  Within it a launch is one chain of memory latencies and the
+    // split shortens it (8^4: FP64 20.7 -> 10.6, FP32 x 8 43 -> 10.3; 12^3x24 FP32 x 3 20.7 -> 19.2);
+    // beyond it the kernels that use fewer waves per site win (12^3x24 FP64 x 2 31.1 against 28.7,
+    // FP32 x 4 25.3 against 24.8)
+    if (items <= (f64 ? 512 : 1024)) {
+        L.split = 1;
+        L.R = 1;
+        return;
+    }
+    // The z-slab traversal keeps the +-t planes in the last-level cache; lattices that fit there
+    // whole lose a little L2 locality to it (FP32 x 1: 16^3x32 28.1 in order 0, 29.0 in order 1;
+    // 32^3x64 415 and 386)
+    order = g.ntiles >= 4096 ? 1 : 0;
+    // From these column counts on, links and clover read once per tile into LDS beat reading them
+    // per wave (32^3x64: FP64 x 3 1442 against 1572, x 2 1307 against 1176; FP32 x 6 1176 against
+    // 1211, x 5 1100 against 1077; FP16 x 8 967 against 1015, x 6 852 against 770).  Over 12
+    // columns in two chunks, one after the other per XCD (24^3x48 FP32 x 16: 978 against 1046)
+    if (n >= (f64 ? 3 : f16 ? 8 : 6)) {
+        L.lds = 1;
+        L.R = 1;
+        L.bs = 768;
+        if (n > 12) order = 2;
+        return;
+    }
+    // Two columns per wave halve the link reads but also the waves: worth it beyond 4096 one-column
+    // waves, four per SIMD (FP32 x 2: 16^3x32 43 against 33.3, 32^3x64 535 against 661), not for
+    // FP64, which then runs two waves per SIMD (32^3x64 x 2: 1335 against 1176), nor for FP16, whose
+    // links are half as large, below five columns (24^3x48 x 4: 169 against 165; x 6: 254 against 269)
+    const bool many = items > 4096;
+    L.R = std::min(n, f64 ? (many ? 1 : 2) : f16 ? (n > 4 ? 2 : 1) : (many ? 2 : 1));
+    L.bs = f64 && n > 1 ? 128 : 64;
+}
+
 // hop launch skeleton for op, precision and tune
-static HopLaunch hop_base(bq_op op, int prec, const Tune& t, int dagger, int out_parity, int ncol)
+static HopLaunch hop_base(bq_op op, int prec, const Tune& t, int dagger, int out_parity, int ncol, int nact = 0)
 {
     HopLaunch L;
     const bq_gauge G = op->gauge;
@@ -551,10 +606,12 @@ static HopLaunch hop_base(bq_op op, int prec, const Tune& t, int dagger, int out
     L.bs = t.bs;
     L.march = (t.march > 0 && G->g.blocked && G->g.L[3] % t.march == 0) ? t.march : 0;
     L.lds = t.lds;
-    L.dagger = dagger;
-    L.g = with_order(G->g, t.order);
-    L.parity = out_parity;
     L.ncol = ncol;
+    int order = t.order;
+    if (!t.chosen) pick_kernel(L, G->g, nact > 0 ? nact : ncol, order);
+    L.dagger = dagger;
+    L.g = with_order(G->g, order);
+    L.parity = out_parity;
     const LinkSet* ls = G->get(prec, L.recon);
     for (int k = 0; k < 8; k++) L.U[k] = ls ? ls->U[k] : nullptr;
     const double ep = std::exp(op->mu), em = std::exp(-op->mu);
@@ -602,6 +659,7 @@ struct OpCall {
     int statmask = 1;
     hipStream_t st;
     const ColTable* ct = nullptr;
+    int nact = 0;  // columns in use, where they are fewer than ncol (0: all)
 };
 
 // switch a launch to per-column operators: clover per column (parity `par`, inverse or not), f by mode
@@ -626,7 +684,7 @@ static void apply_cols(const OpCall& c, HopLaunch& L, int par, bool inverse, int
 static int k1(const OpCall& c, int dag, FieldArg in_o, FieldArg out_e, FieldArg v_e = FieldArg(), double a = 0,
               double f = 1, int fk = FK_CONST)
 {
-    HopLaunch L = hop_base(c.op, c.prec, c.t, dag, 0, c.ncol);
+    HopLaunch L = hop_base(c.op, c.prec, c.t, dag, 0, c.ncol, c.nact);
     L.epi = EPI_TINV;
     L.in = in_o;
     L.out = out_e;
@@ -644,7 +702,7 @@ static int k1(const OpCall& c, int dag, FieldArg in_o, FieldArg out_e, FieldArg 
 static int tv(const OpCall& c, int dag, int parity, FieldArg in, FieldArg v, FieldArg out, double f, double* partial,
               int nwaves, int pstride, int fk = FK_CONST)
 {
-    HopLaunch L = hop_base(c.op, c.prec, c.t, dag, parity, c.ncol);
+    HopLaunch L = hop_base(c.op, c.prec, c.t, dag, parity, c.ncol, c.nact);
     L.epi = EPI_TV;
     L.in = in;
     L.v = v;
@@ -664,7 +722,7 @@ static int tv(const OpCall& c, int dag, int parity, FieldArg in, FieldArg v, Fie
 static int tvr(const OpCall& c, int dag, int parity, FieldArg in, FieldArg v, FieldArg rin, FieldArg rout, double f,
                const double* alpha, double* partial, int nwaves, int pstride, int fk = FK_CONST)
 {
-    HopLaunch L = hop_base(c.op, c.prec, c.t, dag, parity, c.ncol);
+    HopLaunch L = hop_base(c.op, c.prec, c.t, dag, parity, c.ncol, c.nact);
     L.epi = EPI_TVR;
     L.in = in;
     L.v = v;
@@ -686,7 +744,7 @@ static int tvr(const OpCall& c, int dag, int parity, FieldArg in, FieldArg v, Fi
 static int hopv(const OpCall& c, int dag, int parity, FieldArg in, FieldArg out, FieldArg v, double a, double f,
                 int fk = FK_CONST)
 {
-    HopLaunch L = hop_base(c.op, c.prec, c.t, dag, parity, c.ncol);
+    HopLaunch L = hop_base(c.op, c.prec, c.t, dag, parity, c.ncol, c.nact);
     L.epi = EPI_HOP;
     L.in = in;
     L.out = out;
@@ -704,7 +762,7 @@ static int hopv(const OpCall& c, int dag, int parity, FieldArg in, FieldArg out,
 static int hop_coef(const OpCall& c, int parity, FieldArg in, FieldArg out, FieldArg v, double a, double f, double ef,
                     double eb)
 {
-    HopLaunch L = hop_base(c.op, c.prec, c.t, 0, parity, c.ncol);
+    HopLaunch L = hop_base(c.op, c.prec, c.t, 0, parity, c.ncol, c.nact);
     L.epi = EPI_HOP;
     L.in = in;
     L.out = out;
@@ -770,6 +828,7 @@ struct Workspace {
     int graph_chunk = 0;
     double graph_delta2 = -1;
     const ColTable* ct = nullptr;  // per-column operators (server sessions)
+    int nact = 0;                  // columns in use (server sessions; 0: all)
     ~Workspace()
     {
         if (graph) (void)hipGraphExecDestroy(graph);
@@ -903,6 +962,7 @@ static int cg_iteration(bq_op op, Workspace* w, int prec, hipStream_t st)
     const int n = w->xs.sites();
     OpCall c{op, prec, get_tune(ctx, prec, w->ncol), w->ncol, w->cs.status, kIterMask, st};
     c.ct = w->ct;
+    c.nact = w->nact;
     CHK(op_fwd(c, w->full, w->ps, w->qs, w->ts, w->partial, w->hw));
     HIPCHK(launch_fin_alpha(w->cs, w->partial, w->pstride, w->ncol, st));
     CHK(op_dag_r(c, w->full, w->qs, w->ts, w->rs, w->rs, w->cs.alpha, w->partial, w->hw));
@@ -919,6 +979,7 @@ static int true_residual(bq_op op, Workspace* w, const int* status, int statmask
     bq_context ctx = op->gauge->ctx;
     OpCall c{op, PREC_F64, get_tune(ctx, PREC_F64, w->ncol), w->ncol, status, statmask, st};
     c.ct = w->ct;
+    c.nact = w->nact;
     CHK(op_fwd(c, w->full, w->x, w->q64, w->t64, nullptr, w->hw));
     return op_dag_r(c, w->full, w->q64, w->t64, w->bp, w->r, nullptr, w->partial, w->hw);
 }
@@ -2825,7 +2886,7 @@ int bq_tune_set(bq_context ctx, int prec, int nrhs, int recon, int R, int bs, in
     if (lds < 0 || lds > 2) return fail(BQ_ERR_INVALID, "lds must be 0, 1 or 2");
     if (lds == 2 && R != 1) return fail(BQ_ERR_INVALID, "lds 2 (lane exchange) takes one column per thread");
     if (order < 0 || order > 2) return fail(BQ_ERR_INVALID, "order must be 0, 1 or 2");
-    ctx->tune[{prec, nrhs}] = Tune{recon, R, bs, march, lds, order};
+    ctx->tune[{prec, nrhs}] = make_tune(prec, nrhs, recon, R, bs, march, lds, order);
     return BQ_OK;
 }
 
@@ -2863,7 +2924,7 @@ int bq_autotune(bq_op op, int prec, int nrhs)
                 for (int bs : {64, 128, 256, 512}) {
                     if (!hop_variant_exists(prec, rprec, recon, R, EPI_TINV)) continue;
                     if (recon == 12 && !op->gauge->get(prec, 12)) continue;  // not an SU(3) field
-                    const Tune t{recon, R, bs, march, 0};
+                    const Tune t = make_tune(prec, nrhs, recon, R, bs, march, 0, 0);
                     const double ms = time_of(t, 5);
                     if (ms < 1e300) cand.push_back({ms, t});
                 }
@@ -2880,7 +2941,7 @@ int bq_autotune(bq_op op, int prec, int nrhs)
                     if (waves > G && waves != 4) continue;  // bs / 64 is only a bound on the waves
                     if (mode == 2 && (R != 1 || waves < std::min(G, 16))) continue;
                     if (prec == PREC_F64 && R > 1) continue;  // spills under the 768-thread bound of FP64
-                    const Tune t{recon, R, 64 * waves, 0, mode};
+                    const Tune t = make_tune(prec, nrhs, recon, R, 64 * waves, 0, mode, 0);
                     const double ms = time_of(t, 5);
                     if (ms < 1e300) cand.push_back({ms, t});
                 }
@@ -2906,7 +2967,7 @@ int bq_autotune(bq_op op, int prec, int nrhs)
         }
     // pass 3: the winner in the other traversals (z slabs per XCD; and those with the column-group
     // chunks one after another per XCD), kept if 2% faster
-    if (bt.march == 0) {
+    if (bt.chosen && bt.march == 0) {
         double tb = time_of(bt, 20);
         const Tune base = bt;
         for (int order : {1, 2}) {
@@ -3123,6 +3184,7 @@ static int admit(bq_server S, Request* q, Session* s)
             k++;
         }
     s->used += q->nrhs;
+    s->w.nact = s->used;
     q->sess = s;
     q->state = REQ_RUNNING;
     return BQ_OK;
@@ -3134,11 +3196,13 @@ static int prepare_new(Session* s)
     const int cap = s->cap;
     Workspace* w = &s->w;
     hipStream_t st = s->st;
+    w->nact = s->used;
     HIPCHK(hipMemcpyAsync(s->dflags.p, s->hflags, sizeof(int) * cap + sizeof(double) * cap, hipMemcpyHostToDevice, st));
     HIPCHK(launch_set_status(w->cs.status, dsel(s), cap, COL_NEW, st));
     const int m = 1 << COL_NEW;
     OpCall c64{&s->stub, PREC_F64, get_tune(s->g->ctx, PREC_F64, cap), cap, w->cs.status, m, st};
     c64.ct = &s->ct;
+    c64.nact = w->nact;
     const void* tinv[kMaxCols];
     for (int c = 0; c < cap; c++) tinv[c] = s->ct.Tinv[PREC_F64][0][c];
     HIPCHK(launch_clover_apply(PREC_F64, s->g->g, nullptr, s->bfull.half(0), w->t64.all(), cap, st, tinv, w->cs.status, m));
@@ -3186,6 +3250,7 @@ static int retire(bq_server S, Session* s, std::vector<Request*>& done)
     HIPCHK(launch_convert(PREC_F64, w->x.all(), PREC_F64, s->xfull.half(1), n, cap, w->cs.status, m, st));
     OpCall c64{&s->stub, PREC_F64, get_tune(s->g->ctx, PREC_F64, cap), cap, w->cs.status, m, st};
     c64.ct = &s->ct;
+    c64.nact = w->nact;
     CHK(k1(c64, 0, s->xfull.half(1), s->xfull.half(0), s->bfull.half(0), 1.0, 0.0, FK_KAPPA));
     // |b - M x|^2 on the full lattice (t64 and q64 as even / odd scratch) and |b|^2
     const int hw = w->hw;
@@ -3450,6 +3515,7 @@ static int launch_idle(bq_server S)
         Session* s = sp.get();
         if (s->busy || s->used == 0) continue;
         Workspace* w = &s->w;
+        w->nact = s->used;
         w->cs.delta2 = s->prec == PREC_F64 ? 0.0 : 0.01;  // reliable-update threshold delta = 0.1
         CHK(chunk(&s->stub, w, s->prec, S->chunk, s->st));
         HIPCHK(hipMemcpyAsync(w->h_status, w->cs.status, sizeof(int) * 4 * s->cap, hipMemcpyDeviceToHost, s->st));

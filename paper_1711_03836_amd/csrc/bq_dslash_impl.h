@@ -1152,6 +1152,247 @@ __global__ __launch_bounds__(lds_max_threads<P>()) __attribute__((amdgpu_waves_p
     epilogue<P, PR, R, EPI, PC, LA, CL>(A, j, act, any, c0, acc, CL ? sc : nullptr);
 }
 
+// ---------------------------------------------------------------------------
+// Hop-split variant for launches with few tiles and columns.
+//
+// A workgroup owns one 64-site tile and one column and has one wave per half hop: the 8 links and
+// neighbour spinors of a site are in flight together, where the kernels above load and multiply
+// them one (or two) at a time in one wave.  The colour-rotated half spinors meet in LDS; wave b
+// (0, 1) sums those of clover block b in the order of the half hops and runs that block's
+// epilogue.  Per site and column the arithmetic is the plain kernel's, in the same order, so the
+// results (norm partials included) are bitwise equal.
+// ---------------------------------------------------------------------------
+
+// acc += the spins of block BLK (0: 0 and 1, 1: 2 and 3) of k (1 + S gamma_mu) psi, given the half
+// spinor h: the lines of reconstruct_add (FP16 storage: of reconstruct_add_k) for that block
+template <typename T, int MU, int S, int BLK, bool SCALED>
+__device__ __forceinline__ void reconstruct_block(cx<T> (&acc)[6], const cx<T> (&h)[6], T k)
+{
+    cx<T> full[12];
+#pragma unroll
+    for (int q = 0; q < 12; q++) full[q] = q / 6 == BLK ? acc[q - 6 * BLK] : cx<T>{T(0), T(0)};
+    if constexpr (SCALED) reconstruct_add_k<T, MU, S>(full, h, k);
+    else reconstruct_add<T, MU, S>(full, h);
+#pragma unroll
+    for (int q = 0; q < 6; q++) acc[q] = full[6 * BLK + q];
+}
+
+constexpr int kSplitWaves = 8;
+
+// LDS of a workgroup: half spinors [half hop][6][64], FP16 factors [half hop][64], norms [64]
+template <class P>
+constexpr int split_lds_bytes()
+{
+    return kSplitWaves * 6 * kTile * (int)sizeof(typename LinkLds<P>::C) + kSplitWaves * kTile * 4 + kTile * 8;
+}
+
+// y = U (1 + S gamma_mu) psi of half hop H at every site of the tile, into LDS
+template <class P, class PR, int DAG, int RECON, int H, int LA>
+__device__ __forceinline__ void split_hop(const Args<P, PR>& A, const Site& s, bool act, int c, int lane,
+                                          typename LinkLds<P>::C* yb, float* kb)
+{
+    using T = typename P::real;
+    constexpr int MU = H >> 1;
+    constexpr bool BW = H & 1;
+    constexpr int S = (DAG ? +1 : -1) * (BW ? -1 : +1);
+    cx<T> y[6];
+    float k = 0.0f;
+    if (act) {
+        HalfHop<P, 1, RECON> d;
+        hh_load_link<P, PR, 1, RECON, H, LA>(A, s, d);
+        hh_load_spinor(A, c, 0, d);
+        PLink<P, RECON, BW> L;
+        prep_link<P, RECON, BW>(d.link, L);
+        T coef = T(1);
+        if constexpr (MU == 3) {
+            if constexpr (BW) coef = (s.t == 0) ? A.eb_bc : A.eb;
+            else coef = (s.t == A.g.L[3] - 1) ? A.ef_bc : A.ef;
+        }
+        if constexpr (P::id == PREC_F16) {
+            hop_product<P, RECON, MU, S, BW, false>(L, d.sp[0], T(1), y);
+            k = (MU == 3) ? coef * d.sc[0] : d.sc[0];
+        } else {
+            hop_product<P, RECON, MU, S, BW, MU == 3>(L, d.sp[0], coef, y);
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < 6; q++) y[q] = {T(0), T(0)};
+    }
+#pragma unroll
+    for (int q = 0; q < 6; q++) yb[(H * 6 + q) * kTile + lane] = {y[q].re, y[q].im};
+    if constexpr (P::id == PREC_F16) kb[H * kTile + lane] = k;
+}
+
+template <class P, int DAG, int BLK, int H>
+__device__ __forceinline__ void split_sum(const typename LinkLds<P>::C* yb, const float* kb, int lane,
+                                          cx<typename P::real> (&acc)[6])
+{
+    using T = typename P::real;
+    if constexpr (H < 8) {
+        constexpr int S = (DAG ? +1 : -1) * ((H & 1) ? -1 : +1);
+        cx<T> y[6];
+#pragma unroll
+        for (int q = 0; q < 6; q++) {
+            const auto t = yb[(H * 6 + q) * kTile + lane];
+            y[q] = {(T)t.x, (T)t.y};
+        }
+        T k = T(1);
+        if constexpr (P::id == PREC_F16) k = kb[H * kTile + lane];
+        reconstruct_block<T, (H >> 1), S, BLK, P::id == PREC_F16>(acc, y, k);
+        split_sum<P, DAG, BLK, H + 1>(yb, kb, lane, acc);
+    }
+}
+
+// What wave BLK reads of its clover block, v and r while the half hops are on their way
+template <class P, class PR, int EPI>
+struct SplitIn {
+    cx<typename P::real> cb[EPI == EPI_HOP ? 1 : 18];
+    cx<typename P::real> v[6];
+    cx<typename PR::real> r[EPI == EPI_TVR ? 6 : 1];
+};
+
+template <class P, class PR, int EPI, bool PC, int LA, int BLK>
+__device__ __forceinline__ void split_load(const Args<P, PR>& A, int j, int c, SplitIn<P, PR, EPI>& in)
+{
+    if constexpr (EPI != EPI_HOP) load_clover_block<P, LA>(PC ? A.cclov[c] : A.clov, j, BLK, in.cb);
+    if constexpr (EPI == EPI_TV || EPI == EPI_TVR) load_spinor_part(A.v, c, j, BLK, in.v);
+    if constexpr (EPI == EPI_TVR) load_spinor_part(A.rin, c, j, BLK, in.r);
+}
+
+template <class P, class PR, int DAG, int EPI, int RECON, bool PC, int LA>
+__global__ __launch_bounds__(kSplitWaves * kTile) void k_hop_split(const Args<P, PR> A)
+{
+    using T = typename P::real;
+    using TR = typename PR::real;
+    using LC = typename LinkLds<P>::C;
+    __shared__ __align__(16) unsigned char smem[split_lds_bytes<P>()];
+    LC* yb = (LC*)smem;
+    float* kb = (float*)(smem + kSplitWaves * 6 * kTile * sizeof(LC));
+    double* nb = (double*)(kb + kSplitWaves * kTile);
+    const int lb = xcd_remap(blockIdx.x, gridDim.x);
+    int lt, c;
+    item_of(A.g, lb, A.nblk, A.nch, lt, c);
+    c = __builtin_amdgcn_readfirstlane(c);
+    if (!col_selected(A.status, A.statmask, c)) return;  // uniform over the workgroup
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> kTileLog);
+    const int lane = threadIdx.x & (kTile - 1);
+    const int j = tile_at(A.g, lt) * kTile + lane;  // lt < ntiles
+    const bool act = j < A.g.Vh;
+    const Site s = site_of(A.g, A.parity, act ? j : 0);
+    SplitIn<P, PR, EPI> in;
+    switch (w) {
+    case 0: split_hop<P, PR, DAG, RECON, 0, LA>(A, s, act, c, lane, yb, kb); break;
+    case 1: split_hop<P, PR, DAG, RECON, 1, LA>(A, s, act, c, lane, yb, kb); break;
+    case 2: split_hop<P, PR, DAG, RECON, 2, LA>(A, s, act, c, lane, yb, kb); break;
+    case 3: split_hop<P, PR, DAG, RECON, 3, LA>(A, s, act, c, lane, yb, kb); break;
+    case 4: split_hop<P, PR, DAG, RECON, 4, LA>(A, s, act, c, lane, yb, kb); break;
+    case 5: split_hop<P, PR, DAG, RECON, 5, LA>(A, s, act, c, lane, yb, kb); break;
+    case 6: split_hop<P, PR, DAG, RECON, 6, LA>(A, s, act, c, lane, yb, kb); break;
+    default: split_hop<P, PR, DAG, RECON, 7, LA>(A, s, act, c, lane, yb, kb); break;
+    }
+    if (act && w == 0) split_load<P, PR, EPI, PC, LA, 0>(A, j, c, in);
+    if (act && w == 1) split_load<P, PR, EPI, PC, LA, 1>(A, j, c, in);
+    __syncthreads();
+    cx<T> o[6];
+    double term[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, sum = 0.0;  // |out|^2 of this block, term by term and summed
+    if (w < 2 && act) {
+        cx<T> acc[6];
+#pragma unroll
+        for (int k = 0; k < 6; k++) acc[k] = {T(0), T(0)};
+        if (w == 0) split_sum<P, DAG, 0, 0>(yb, kb, lane, acc);
+        else split_sum<P, DAG, 1, 0>(yb, kb, lane, acc);
+        const T f = colf<PC>(A, c);
+        if constexpr (EPI == EPI_HOP || EPI == EPI_TINV) {
+            if (A.v.d != nullptr) {
+                cx<T> v[6];
+                load_spinor_part(A.v, c, j, w, v);
+#pragma unroll
+                for (int k = 0; k < 6; k++) acc[k] = caxpy(f, acc[k], cscale(A.a, v[k]));
+            } else {
+#pragma unroll
+                for (int k = 0; k < 6; k++) acc[k] = cscale(f, acc[k]);
+            }
+            if constexpr (EPI == EPI_TINV) clover_mul(in.cb, acc, o);
+            else {
+#pragma unroll
+                for (int k = 0; k < 6; k++) o[k] = acc[k];
+            }
+        } else if constexpr (EPI == EPI_TV) {
+            clover_mul(in.cb, in.v, o);
+#pragma unroll
+            for (int k = 0; k < 6; k++) {
+                o[k] = caxpy(f, acc[k], o[k]);
+                term[k] = (double)o[k].re * o[k].re + (double)o[k].im * o[k].im;
+            }
+        } else {
+            const TR al = A.alpha ? (TR)A.alpha[c] : TR(1);
+            clover_mul(in.cb, in.v, o);
+            typename PR::unit* rb = A.rout.d + c * A.rout.cstride;
+#pragma unroll
+            for (int k = 0; k < 6; k++) {
+                const cx<T> x = caxpy(f, acc[k], o[k]);
+                in.r[k].re = fmadd(-al, (TR)x.re, in.r[k].re);
+                in.r[k].im = fmadd(-al, (TR)x.im, in.r[k].im);
+                st_stream(&at(rb, j, w * 6 + k, 12), {in.r[k].re, in.r[k].im});
+                sum += (double)in.r[k].re * in.r[k].re + (double)in.r[k].im * in.r[k].im;
+            }
+        }
+        if constexpr (EPI != EPI_TVR && P::id != PREC_F16) {
+            typename P::unit* ob = A.out.d + c * A.out.cstride;
+#pragma unroll
+            for (int k = 0; k < 6; k++) {
+                if constexpr (EPI == EPI_TV) at(ob, j, w * 6 + k, 12) = {o[k].re, o[k].im};
+                else st_stream(&at(ob, j, w * 6 + k, 12), {o[k].re, o[k].im});
+            }
+        }
+    }
+    if constexpr (EPI != EPI_TVR && P::id == PREC_F16) {
+        // the site's scale spans both blocks: their maxima meet in LDS (the half spinors are read)
+        float m = 0.0f;
+        if (w < 2 && act)
+#pragma unroll
+            for (int k = 0; k < 6; k++) m = fmaxf(m, fmaxf(fabsf(o[k].re), fabsf(o[k].im)));
+        __syncthreads();
+        if (w < 2) kb[w * kTile + lane] = m;
+        __syncthreads();
+        if (w < 2 && act) {
+            m = fmaxf(kb[lane], kb[kTile + lane]);
+            const float inv = m > 0.0f ? 1.0f / m : 0.0f;
+            uint2* ob = A.out.d + c * A.out.cstride;
+#pragma unroll
+            for (int u = 0; u < 3; u++) {
+                const uint2 t = CxIO<P16, 2>::pack(cscale(inv, o[2 * u]), cscale(inv, o[2 * u + 1]));
+                if constexpr (EPI == EPI_TV) at(ob, j, w * 3 + u, 6) = t;
+                else st_stream(&at(ob, j, w * 3 + u, 6), t);
+            }
+            if (w == 0) A.out.s[c * A.out.sstride + j] = m;
+        }
+    }
+    if constexpr (EPI == EPI_TV || EPI == EPI_TVR) {
+        if (A.partial != nullptr) {  // uniform: block 1's wave carries on from block 0's sum
+            if (w == 0) {
+                if constexpr (EPI == EPI_TV)
+#pragma unroll
+                    for (int k = 0; k < 6; k++) sum += term[k];
+                nb[lane] = sum;
+            }
+            __syncthreads();
+            if (w == 1) {
+                double t = nb[lane];
+                if constexpr (EPI == EPI_TV) {
+#pragma unroll
+                    for (int k = 0; k < 6; k++) t += term[k];
+                } else {
+                    t += sum;
+                }
+                t = wave_sum(t);
+                const int wave = j >> kTileLog;
+                if (lane == 0 && wave < A.nwaves) A.partial[(size_t)c * A.pstride + wave] = t;
+            }
+        }
+    }
+}
+
 template <class P>
 SpinorPtr<P> sp(const FieldArg& f)
 {
@@ -1196,6 +1437,17 @@ hipError_t launch_t(const HopLaunch& L, hipStream_t st)
     // (and, without per-column clover, the same clover) soon after: load those through the
     // caches.  With one group they are read once and streamed (non-temporal).
     const bool shared = G > 1;
+    if constexpr (R == 1) {
+        if (L.split) {
+            if (EPI != EPI_HOP && !PC && L.clov == nullptr) return hipErrorInvalidValue;
+            A.tpb = A.gw = 1;
+            A.nch = G;
+            A.nblk = L.g.ntiles;
+            hipLaunchKernelGGL((k_hop_split<P, PR, DAG, EPI, RECON, PC, 0>), dim3(A.nblk * A.nch), dim3(kSplitWaves * kTile),
+                               0, st, A);
+            return hipGetLastError();
+        }
+    }
     if (L.march > 0) {
         // t-marching: one tile position x column-group chunk x time segment per workgroup,
         // at most bs / 64 column groups per workgroup

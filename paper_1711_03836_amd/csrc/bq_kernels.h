@@ -41,6 +41,7 @@ struct HopLaunch {
     int lds = 0;             // 1: tile-shared kernel (links and clover staged in LDS) when a tile has
                              //    several column groups; 2: the same with one column per wave and the
                              //    x and y neighbour spinors exchanged between lanes
+    int split = 0;           // 1: hop-split kernel, one workgroup per tile and column (R = 1; march and lds ignored)
     Geom g{};
     int parity = 0;          // output parity
     int ncol = 1;
