@@ -1069,16 +1069,32 @@ static int cg_solve(bq_op op, Workspace* w, const bq_solve_params& prm, hipStrea
     const double rcol = rel_col_bytes(op, prec, w->full), rshr = iter_shared_bytes(op, PREC_F64);
     const double scol = restart_col_bytes(op, prec, w->full);
     const int rel_launches = (prec != PREC_F64) + 4 + 2;
-    while (true) {
-        if (graph)
-            HIPCHK(hipGraphLaunch(w->graph, st));
-        else
-            CHK(chunk(op, w, prec, k, st));
-        done_iters += k;
-        acct.launches += (long long)k * kIterLaunches + rel_launches;
-        acct.chunks++;
+    const auto read_states = [&]() -> int {
         HIPCHK(hipMemcpyAsync(w->h_status, w->cs.status, sizeof(int) * 4 * ncol, hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
+        return BQ_OK;
+    };
+    while (true) {
+        bool pass = true;  // the chunk's reliable pass ran
+        if (graph) {
+            HIPCHK(hipGraphLaunch(w->graph, st));
+            CHK(read_states());
+        } else {
+            // The reliable pass is launched only after a chunk in which some column stopped for one
+            // (one chunk in five on 16^3x32): its seven launches find nothing to do otherwise, but
+            // cost 3-5 us each on a small lattice and 22 us for each FP64 stencil on 12 columns of 24^3x48.
+            for (int i = 0; i < k; i++) CHK(cg_iteration(op, w, prec, st));
+            CHK(read_states());
+            pass = false;
+            for (int c = 0; c < ncol; c++) pass |= (kRelMask >> w->h_status[c]) & 1;
+            if (pass) {
+                CHK(reliable_pass(op, w, prec, st));
+                CHK(read_states());
+            }
+        }
+        done_iters += k;
+        acct.launches += (long long)k * kIterLaunches + (pass ? rel_launches : 0);
+        acct.chunks++;
         // Within a chunk a column is active for a prefix of the iterations (it can only stop
         // there, and restarts in the chunk's reliable pass), so the counters give exact counts.
         const int* hs = w->h_status;
@@ -1090,7 +1106,7 @@ static int cg_solve(bq_op op, Workspace* w, const bq_solve_params& prm, hipStrea
             dmax = std::max(dmax, di);
             colit += di;
             nrel_cols += dr;
-            nrestart += hs[2 * ncol + c];
+            nrestart += pass ? hs[2 * ncol + c] : 0;
         }
         acct.bytes += dmax * ishr + colit * icol;
         if (nrel_cols > 0) acct.bytes += rshr + nrel_cols * rcol + nrestart * scol;
@@ -1592,17 +1608,24 @@ static int bicg_views(bq_op op, const Vec& b_even, const Vec& b_odd, const Vec& 
             HIPCHK(launch_bicg_xr(prec, xi.all(), p.all(), s_.all(), t.all(), r.all(), rh.all(), S, n, ncol, pt, hw, st));
             HIPCHK(launch_fin_bicg(2, S, pt, hw, ncol, st));
         }
-        // reliable pass for the columns whose inner run stopped: x64 += x, r64 = bhat - Mhat x64
-        if (prec != PREC_F64) HIPCHK(launch_accum(prec, xi.all(), x64.all(), n, ncol, S.status, mStopped, st));
-        CHK(k1(cr, 0, x64.all(), t64.all()));
-        CHK(tvr(cr, 0, 1, t64.all(), x64.all(), bh.all(), r64.all(), -kap * kap, nullptr, pt, hw, hw));
-        CHK(restart());
         done += kchunk;
         acct.chunks++;
         acct.iterations += kchunk;
-        acct.launches += 12L * kchunk + 9 + (prec != PREC_F64);
+        acct.launches += 12L * kchunk;
         HIPCHK(hipMemcpyAsync(hs.data(), S.status, sizeof(int) * 3 * ncol, hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
+        // reliable pass for the columns whose inner run stopped: x64 += x, r64 = bhat - Mhat x64
+        bool pass = false;
+        for (int c = 0; c < ncol; c++) pass |= hs[c] == COL_STOPPED;
+        if (pass) {
+            if (prec != PREC_F64) HIPCHK(launch_accum(prec, xi.all(), x64.all(), n, ncol, S.status, mStopped, st));
+            CHK(k1(cr, 0, x64.all(), t64.all()));
+            CHK(tvr(cr, 0, 1, t64.all(), x64.all(), bh.all(), r64.all(), -kap * kap, nullptr, pt, hw, hw));
+            CHK(restart());
+            acct.launches += 9 + (prec != PREC_F64);
+            HIPCHK(hipMemcpyAsync(hs.data(), S.status, sizeof(int) * 3 * ncol, hipMemcpyDeviceToHost, st));
+            HIPCHK(hipStreamSynchronize(st));
+        }
         int dmax = 0, nrel = 0;
         double colit = 0;
         for (int c = 0; c < ncol; c++) {
