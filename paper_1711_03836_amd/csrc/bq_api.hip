@@ -2054,10 +2054,8 @@ int bq_field_put(bq_field f, const double* src, int src_on_device, void* stream)
     }
     int p0, p1;
     field_parities(f, &p0, &p1);
-    for (int p = p0; p <= p1; p++) {
-        Vec v = parity_vec(f, p);
-        HIPCHK(launch_spinor_import(canon, f->nrhs, f->g, p, f->prec, v.all(), ctx->stream));
-    }
+    HIPCHK(launch_spinor_import(canon, f->nrhs, f->g, p0, p1 - p0 + 1, f->prec, parity_vec(f, p0).all(), f->half_units,
+                                f->half_sites, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
     return BQ_OK;
 }
@@ -2079,10 +2077,8 @@ int bq_field_get(bq_field f, double* dst, int dst_on_device, void* stream)
     }
     int p0, p1;
     field_parities(f, &p0, &p1);
-    for (int p = p0; p <= p1; p++) {
-        Vec v = parity_vec(f, p);
-        HIPCHK(launch_spinor_export(v.all(), f->nrhs, f->g, p, f->prec, canon, ctx->stream));
-    }
+    HIPCHK(launch_spinor_export(parity_vec(f, p0).all(), f->nrhs, f->g, p0, p1 - p0 + 1, f->prec, f->half_units,
+                                f->half_sites, canon, ctx->stream));
     if (!dst_on_device) HIPCHK(hipMemcpyAsync(dst, stage.p, bytes, hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
     return BQ_OK;
@@ -3194,8 +3190,8 @@ static int admit(bq_server S, Request* q, Session* s)
             s->slot[c] = q;
             q->slots.push_back(c);
             const double2* canon = s->stage.as<double2>() + (size_t)k * V * 12;
-            for (int p = 0; p < 2; p++)
-                HIPCHK(launch_spinor_import(canon, 1, g, p, PREC_F64, col_arg(s->bfull, p, c), s->st));
+            HIPCHK(launch_spinor_import(canon, 1, g, 0, 2, PREC_F64, col_arg(s->bfull, 0, c), s->bfull.half_units,
+                                        s->bfull.half_sites, s->st));
             for (int pr = 0; pr < 3; pr++) {
                 s->ct.T[pr][1][c] = q->op->T[pr][1].p;
                 s->ct.T[pr][0][c] = q->op->T[pr][0].p;
@@ -3294,9 +3290,8 @@ static int retire(bq_server S, Session* s, std::vector<Request*>& done)
         const size_t bytes = (size_t)q->nrhs * V * 12 * 16;
         if (s->stage.bytes < bytes) CHK(s->stage.alloc(S->ctx, bytes, CLEAR_NONE));
         for (size_t k = 0; k < q->slots.size(); k++)
-            for (int p = 0; p < 2; p++)
-                HIPCHK(launch_spinor_export(col_arg(s->xfull, p, q->slots[k]), 1, g, p, PREC_F64,
-                                            s->stage.as<double2>() + k * V * 12, st));
+            HIPCHK(launch_spinor_export(col_arg(s->xfull, 0, q->slots[k]), 1, g, 0, 2, PREC_F64, s->xfull.half_units,
+                                        s->xfull.half_sites, s->stage.as<double2>() + k * V * 12, st));
         HIPCHK(hipMemcpyAsync(q->x_host, s->stage.p, bytes, hipMemcpyDefault, st));  // x in host or device memory
         HIPCHK(hipStreamSynchronize(st));
     }

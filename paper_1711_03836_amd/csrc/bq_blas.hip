@@ -7,6 +7,8 @@
 // partials depend only on which 64 sites a wave covers, so a column's result
 // is the same bit for bit whatever the block size, column tile or batch it
 // was computed in.
+#include <type_traits>
+
 #include "bq_kernels.h"
 
 namespace bq {
@@ -51,37 +53,87 @@ __global__ void k_links_import(const double2* __restrict__ canon, const Geom g, 
     }
 }
 
-template <class P>
-__global__ void k_spinor_import(const double2* __restrict__ canon, const Geom g, int parity, SpinorPtr<P> f)
+// Spinors between the canonical array and the tiles: one wavefront per tile, parity and column.
+// The 64 sites j of a tile are the canonical sites 2j + (0 or 1), of 12 consecutive 16-byte values
+// each.  A lane that read or wrote its own site would touch 64 lines with every access, one per
+// lane; so the canonical side is walked in its own order, value u = 12 site + component by lane u mod
+// 64 (192-byte runs), and the wavefront turns the tile around in LDS, in rows of 13 values to keep
+// the lanes' rows in different banks.  Both parities of a tile run in one workgroup and share the
+// lines that their sites halve.  Both sides stream (non-temporal), except that FP32 and FP16 leave
+// the lines of both parities to meet in the L2 on the way out (32^3x64 x 12 FP16: 1346 -> 1190 us).
+// Bound by HBM: 24^3x48 x 12 columns in FP64, 3.06 GB, import 713 -> 583 us, export 793 -> 554 us
+// (5.5 TB/s; a plain copy reaches 6.6); 32^3x64 x 12 in FP32, odd sites only, export 1180 -> 750 us.
+constexpr int kTurnRow = 13;  // values per site in LDS
+
+// canonical value index (site * 12 + component) of value u of the wavefront's tile; odd: bit l set
+// if lane l's site is the odd one of its pair
+__device__ __forceinline__ size_t canon_of(size_t site0, int u, unsigned long long odd)
 {
-    using T = typename P::real;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    const int c = blockIdx.y;
-    if (j >= g.Vh) return;
-    const size_t V = 2 * (size_t)g.Vh;
-    const int lex = lex_of(g, parity, j);
-    cx<T> v[12];
-#pragma unroll
-    for (int k = 0; k < 12; k++) {
-        const double2 t = canon[((size_t)c * V + lex) * 12 + k];
-        v[k] = {(T)t.x, (T)t.y};
-    }
-    store_spinor(f, c, j, v);
+    const int l = u / 12;
+    return (site0 + 2 * l + ((odd >> l) & 1)) * 12 + (u - 12 * l);
 }
 
-template <class P>
-__global__ void k_spinor_export(SpinorPtr<P> f, const Geom g, int parity, double2* __restrict__ canon)
+typedef double bq_d2 __attribute__((ext_vector_type(2)));
+
+// NP parities per workgroup (p0 .. p0 + NP - 1), f: the first one's field, hs / hss: units / scales between them
+template <class P, int NP, bool IMPORT>
+__global__ __launch_bounds__(kTile * 4) void k_spinor_turn(double2* __restrict__ canon, const Geom g, int p0, SpinorPtr<P> f,
+                                                           size_t hs, size_t hss)
 {
     using T = typename P::real;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    using C = typename std::conditional<sizeof(T) == 8, double2, float2>::type;
+    __shared__ C turn[4][kTile * kTurnRow];
+    const int w = threadIdx.x >> kTileLog, lane = threadIdx.x & (kTile - 1);
+    const int tile = blockIdx.x * (4 / NP) + w / NP;
     const int c = blockIdx.y;
-    if (j >= g.Vh) return;
-    const size_t V = 2 * (size_t)g.Vh;
-    const int lex = lex_of(g, parity, j);
+    const int par = p0 + w % NP;
+    C* t = turn[w];
+    const int j = tile * kTile + lane;
+    const bool in = j < g.Vh;
+    const Site s = site_of(g, par, in ? j : 0);
+    const unsigned long long odd = __ballot(s.x & 1);
+    const int nu = 12 * min(kTile, g.Vh - tile * kTile);  // values of the tile (its last sites may be padding)
+    double2* can = canon + (size_t)c * 2 * g.Vh * 12;
+    const size_t site0 = 2 * (size_t)tile * kTile;
+    f.d += (w % NP) * hs;
+    if constexpr (P::id == PREC_F16) f.s += (w % NP) * hss;
     cx<T> v[12];
-    load_spinor(f, c, j, v);
+    if constexpr (IMPORT) {
 #pragma unroll
-    for (int k = 0; k < 12; k++) canon[((size_t)c * V + lex) * 12 + k] = make_double2((double)v[k].re, (double)v[k].im);
+        for (int i = 0; i < 12; i++) {
+            const int u = i * kTile + lane;
+            if (u < nu) {
+                const bq_d2 x = __builtin_nontemporal_load((const bq_d2*)can + canon_of(site0, u, odd));
+                t[u + u / 12 * (kTurnRow - 12)] = C{(T)x.x, (T)x.y};
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 12; k++) {
+            const C x = t[lane * kTurnRow + k];
+            v[k] = {x.x, x.y};
+        }
+        if (in) store_spinor<P, true>(f, c, j, v);
+    } else {
+        if (in) {
+            if constexpr (P::id == PREC_F64) CxIO<P, 12>::load_stream(f.d + c * f.cstride, j, v);
+            else load_spinor(f, c, j, v);
+#pragma unroll
+            for (int k = 0; k < 12; k++) t[lane * kTurnRow + k] = C{v[k].re, v[k].im};
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 12; i++) {
+            const int u = i * kTile + lane;
+            if (u < nu) {
+                const C x = t[u + u / 12 * (kTurnRow - 12)];
+                const bq_d2 y = {(double)x.x, (double)x.y};
+                bq_d2* to = (bq_d2*)can + canon_of(site0, u, odd);
+                if constexpr (NP == 1 || P::id == PREC_F64) __builtin_nontemporal_store(y, to);
+                else *to = y;
+            }
+        }
+    }
 }
 
 // --------------------------------------------------------------------------
@@ -439,30 +491,39 @@ hipError_t launch_links_import(const double2* canon, const Geom& g, int parity, 
     return hipGetLastError();
 }
 
-hipError_t launch_spinor_import(const double2* canon, int ncol, const Geom& g, int parity, int prec, FieldArg dst,
-                                hipStream_t st)
+// canonical array <-> np parities (from p0) of a field whose parities lie half_units / half_sites apart
+template <bool IMPORT>
+static hipError_t spinor_turn(double2* canon, int ncol, const Geom& g, int p0, int np, int prec, const FieldArg& f,
+                              size_t half_units, size_t half_sites, hipStream_t st)
 {
-    const dim3 grid = grid2(g.Vh, ncol);
+    if (np < 1 || np > 2 || p0 < 0 || p0 + np > 2) return hipErrorInvalidValue;
+    const int tpb = 4 / np;  // tiles per workgroup
+    const dim3 grid((g.ntiles + tpb - 1) / tpb, ncol), block(4 * kTile);
+#define TURN(P)                                                                                                       \
+    if (np == 2)                                                                                                      \
+        hipLaunchKernelGGL((k_spinor_turn<P, 2, IMPORT>), grid, block, 0, st, canon, g, p0, sp<P>(f), half_units, half_sites); \
+    else                                                                                                              \
+        hipLaunchKernelGGL((k_spinor_turn<P, 1, IMPORT>), grid, block, 0, st, canon, g, p0, sp<P>(f), half_units, half_sites)
     switch (prec) {
-    case PREC_F64: hipLaunchKernelGGL(k_spinor_import<P64>, grid, dim3(kBS), 0, st, canon, g, parity, sp<P64>(dst)); break;
-    case PREC_F32: hipLaunchKernelGGL(k_spinor_import<P32>, grid, dim3(kBS), 0, st, canon, g, parity, sp<P32>(dst)); break;
-    case PREC_F16: hipLaunchKernelGGL(k_spinor_import<P16>, grid, dim3(kBS), 0, st, canon, g, parity, sp<P16>(dst)); break;
+    case PREC_F64: TURN(P64); break;
+    case PREC_F32: TURN(P32); break;
+    case PREC_F16: TURN(P16); break;
     default: return hipErrorInvalidValue;
     }
+#undef TURN
     return hipGetLastError();
 }
 
-hipError_t launch_spinor_export(FieldArg src, int ncol, const Geom& g, int parity, int prec, double2* canon,
-                                hipStream_t st)
+hipError_t launch_spinor_import(const double2* canon, int ncol, const Geom& g, int p0, int np, int prec, FieldArg dst,
+                                size_t half_units, size_t half_sites, hipStream_t st)
 {
-    const dim3 grid = grid2(g.Vh, ncol);
-    switch (prec) {
-    case PREC_F64: hipLaunchKernelGGL(k_spinor_export<P64>, grid, dim3(kBS), 0, st, sp<P64>(src), g, parity, canon); break;
-    case PREC_F32: hipLaunchKernelGGL(k_spinor_export<P32>, grid, dim3(kBS), 0, st, sp<P32>(src), g, parity, canon); break;
-    case PREC_F16: hipLaunchKernelGGL(k_spinor_export<P16>, grid, dim3(kBS), 0, st, sp<P16>(src), g, parity, canon); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    return spinor_turn<true>(const_cast<double2*>(canon), ncol, g, p0, np, prec, dst, half_units, half_sites, st);
+}
+
+hipError_t launch_spinor_export(FieldArg src, int ncol, const Geom& g, int p0, int np, int prec, size_t half_units,
+                                size_t half_sites, double2* canon, hipStream_t st)
+{
+    return spinor_turn<false>(canon, ncol, g, p0, np, prec, src, half_units, half_sites, st);
 }
 
 hipError_t launch_convert(int sprec, FieldArg src, int dprec, FieldArg dst, int n, int ncol, const int* status,

@@ -87,10 +87,11 @@ hipError_t launch_clover_convert(int prec, const double2* src, void* dst, int Vh
 // layout conversion
 hipError_t launch_links_import(const double2* canon, const Geom& g, int parity, int prec, int recon, void* const dst[4],
                                hipStream_t st);
-hipError_t launch_spinor_import(const double2* canon, int ncol, const Geom& g, int parity, int prec, FieldArg dst,
-                                hipStream_t st);
-hipError_t launch_spinor_export(FieldArg src, int ncol, const Geom& g, int parity, int prec, double2* canon,
-                                hipStream_t st);
+// np parities from p0 on at once; dst / src: the field of parity p0, half_units (half_sites: scales) to the next
+hipError_t launch_spinor_import(const double2* canon, int ncol, const Geom& g, int p0, int np, int prec, FieldArg dst,
+                                size_t half_units, size_t half_sites, hipStream_t st);
+hipError_t launch_spinor_export(FieldArg src, int ncol, const Geom& g, int p0, int np, int prec, size_t half_units,
+                                size_t half_sites, double2* canon, hipStream_t st);
 // distance of the canonical FP64 links from SU(3): one partial maximum per part (see link_su3_parts)
 int link_su3_parts(size_t nlinks);
 hipError_t launch_link_su3_dev(const double2* canon, size_t nlinks, double* partial, hipStream_t st);
