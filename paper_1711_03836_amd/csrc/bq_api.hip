@@ -402,7 +402,7 @@ struct bq_gauge_s {
     Geom g{};
     int t_bc = -1;
     int nops = 0;
-    LinkSet links[5];  // F64/18, F64/12, F32/18, F32/12, F16/12 (two-row forms only where the links are SU(3))
+    LinkSet links[5];  // F64/18, F32/18, F64/12, F32/12, F16/12 (two-row forms only where the links are SU(3))
     DevBuf B[2];       // kappa-independent clover field sum sigma (x) F per parity (built on first use)
     double su3_dev = 0;  // max over links of max(|U U^dag - 1|, |det U - 1|), measured at upload
     int nsess = 0;       // server sessions that hold this gauge field
@@ -1797,8 +1797,7 @@ int bq_gauge_upload(bq_context ctx, const int dims[4], const double* links, int 
     std::memcpy(G->dims, dims, sizeof(G->dims));
     G->g = make_geom(dims);
     G->t_bc = t_bc;
-    const size_t V = 2 * (size_t)G->g.Vh;
-    const size_t nbytes = 4 * V * 9 * 16;
+    const size_t nbytes = 4 * 2 * (size_t)G->g.Vh * 9 * 16;
     DevBuf stage;
     const double2* canon = (const double2*)links;
     if (!links_on_device) {
@@ -1806,39 +1805,42 @@ int bq_gauge_upload(bq_context ctx, const int dims[4], const double* links, int 
         HIPCHK(hipMemcpyAsync(stage.p, links, nbytes, hipMemcpyHostToDevice, ctx->stream));
         canon = stage.as<double2>();
     }
-    // The two-row link form rebuilds row 2 as conj(row0 x row1), which holds for SU(3) only: it is
-    // kept for a storage precision only if every link is SU(3) to well within that precision's
-    // rounding.  Without it FP64 and FP32 stencils read all 18 reals, and FP16 storage and the
-    // server (both two-row only) report BQ_ERR_UNSUPPORTED.
-    {
-        const size_t nl = 4 * V;
-        const int np = link_su3_parts(nl);
-        DevBuf part;
-        CHK(part.alloc(ctx, sizeof(double) * np, CLEAR_NONE));
-        HIPCHK(launch_link_su3_dev(canon, nl, part.as<double>(), ctx->stream));
-        std::vector<double> h(np);
-        HIPCHK(hipMemcpyAsync(h.data(), part.p, sizeof(double) * np, hipMemcpyDeviceToHost, ctx->stream));
-        HIPCHK(hipStreamSynchronize(ctx->stream));
-        double d = 0;
-        for (double v : h) d = std::isnan(v) ? INFINITY : std::max(d, v);
-        G->su3_dev = d;
-        if (!std::isfinite(d)) return fail(BQ_ERR_NONFINITE, "non-finite gauge link");
-    }
-    const int forms[5][2] = {{PREC_F64, 18}, {PREC_F64, 12}, {PREC_F32, 18}, {PREC_F32, 12}, {PREC_F16, 12}};
+    const int forms[5][2] = {{PREC_F64, 18}, {PREC_F32, 18}, {PREC_F64, 12}, {PREC_F32, 12}, {PREC_F16, 12}};
     const size_t Vp = pad_sites(G->g.Vh);
-    for (int f = 0; f < 5; f++) {
+    const auto form = [&](int f) -> int {
         LinkSet& ls = G->links[f];
-        if (forms[f][1] == 12 && G->su3_dev > su3_tolerance(forms[f][0])) continue;
         ls.prec = forms[f][0];
         ls.recon = forms[f][1];
         const size_t per = Vp * link_nu(ls.prec, ls.recon) * unit_bytes(ls.prec) + kSkew;
         CHK(ls.buf.alloc(ctx, per * 8, CLEAR_NONE));
         for (int k = 0; k < 8; k++) ls.U[k] = (char*)ls.buf.p + per * k;
-        for (int p = 0; p < 2; p++) {
-            void* dst[4] = {(void*)ls.U[p * 4 + 0], (void*)ls.U[p * 4 + 1], (void*)ls.U[p * 4 + 2], (void*)ls.U[p * 4 + 3]};
-            HIPCHK(launch_links_import(canon, G->g, p, ls.prec, ls.recon, dst, ctx->stream));
-        }
+        return BQ_OK;
+    };
+    for (int f = 0; f < 2; f++) CHK(form(f));
+    {
+        const int np = links_take_parts(G->g);
+        DevBuf part;
+        CHK(part.alloc(ctx, sizeof(double) * (np + 1), CLEAR_NONE));
+        HIPCHK(launch_links_take(canon, G->g, G->links[0].U, G->links[1].U, part.as<double>(), ctx->stream));
+        HIPCHK(launch_fin_max(part.as<double>(), np, part.as<double>() + np, ctx->stream));
+        double d = 0;
+        HIPCHK(hipMemcpyAsync(&d, part.as<double>() + np, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+        HIPCHK(hipStreamSynchronize(ctx->stream));
+        G->su3_dev = d;
+        if (!std::isfinite(d)) return fail(BQ_ERR_NONFINITE, "non-finite gauge link");
     }
+    // The two-row link form rebuilds row 2 as conj(row0 x row1), which holds for SU(3) only: it is
+    // kept for a storage precision only if every link is SU(3) to well within that precision's
+    // rounding.  Without it FP64 and FP32 stencils read all 18 reals, and FP16 storage and the
+    // server (both two-row only) report BQ_ERR_UNSUPPORTED.
+    bool rows = false;
+    for (int f = 2; f < 5; f++)
+        if (G->su3_dev <= su3_tolerance(forms[f][0])) {
+            CHK(form(f));
+            rows = true;
+        }
+    if (rows)
+        HIPCHK(launch_links_rows(G->links[0].U, G->g.Vh, G->links[2].U, G->links[3].U, G->links[4].U, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
     *out = G.release();
     ctx->nhandles++;
@@ -1859,16 +1861,15 @@ int bq_gauge_plaquette(bq_gauge g, double* plaq)
     HIPCHK(hipSetDevice(ctx->device));
     const int nw = pad_sites(g->g.Vh) / kTile;
     DevBuf part;
-    CHK(part.alloc(ctx, sizeof(double) * 2 * nw, CLEAR_NONE));
+    CHK(part.alloc(ctx, sizeof(double) * (2 * nw + 1), CLEAR_NONE));
     const LinkSet* ls = g->get(PREC_F64, 18);
     const double2* U[8];
     for (int k = 0; k < 8; k++) U[k] = (const double2*)ls->U[k];
     HIPCHK(launch_plaquette(g->g, U, part.as<double>(), 2 * nw, ctx->stream));
-    std::vector<double> h(2 * nw);
-    HIPCHK(hipMemcpyAsync(h.data(), part.p, sizeof(double) * 2 * nw, hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(hipStreamSynchronize(ctx->stream));
+    HIPCHK(launch_fin_sum(part.as<double>(), 2 * nw, 1, part.as<double>() + 2 * nw, ctx->stream));
     double s = 0;
-    for (double v : h) s += v;
+    HIPCHK(hipMemcpyAsync(&s, part.as<double>() + 2 * nw, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(hipStreamSynchronize(ctx->stream));
     *plaq = s / (6.0 * 2.0 * g->g.Vh);
     return BQ_OK;
 }
@@ -1894,32 +1895,24 @@ int bq_gauge_free(bq_gauge g)
 // lean_prec >= 0 builds only what a solve in that inner precision needs: FP64 T on both
 // parities and T_ee^-1, plus T_oo and T_ee^-1 in lean_prec.
 // The clover arrays of an operator for kappa and c_SW from the gauge field's kappa-independent B
-// (Eq. 2), into arrays op_build allocated for the same lean precision, on stream st; then waits
+// (Eq. 2), into the arrays op_build allocated, on stream st; then waits
 // for st.  flag: one device int for the positive-definiteness check.
-static int clover_fill(bq_op op, double kappa, double csw, int lean_prec, int* flag, hipStream_t st)
+static int clover_fill(bq_op op, double kappa, double csw, int* flag, hipStream_t st)
 {
     bq_gauge g = op->gauge;
     HIPCHK(hipMemsetAsync(flag, 0, sizeof(int), st));
     for (int p = 0; p < 2; p++) {
-        const bool inv = lean_prec < 0 || p == 0;
-        HIPCHK(launch_clover_from_B(g->g, p, g->B[p].as<double2>(), kappa * csw, op->T[PREC_F64][p].as<double2>(),
-                                    inv ? op->Tinv[PREC_F64][p].as<double2>() : nullptr, flag, st));
+        void *T[3], *Ti[3];
+        for (int prec : {PREC_F64, PREC_F32, PREC_F16}) {  // null where op_build allocated nothing
+            T[prec] = op->T[prec][p].p;
+            Ti[prec] = op->Tinv[prec][p].p;
+        }
+        HIPCHK(launch_clover_from_B(g->g, g->B[p].as<double2>(), kappa * csw, T, Ti, flag, st));
     }
     int hbad = 0;
     HIPCHK(hipMemcpyAsync(&hbad, flag, sizeof(int), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     if (hbad) return fail(BQ_ERR_CLOVER_NOT_HPD, "clover block not positive definite (kappa*c_SW = %g)", kappa * csw);
-    for (int prec : {PREC_F32, PREC_F16}) {
-        if (lean_prec >= 0 && prec != lean_prec) continue;
-        for (int p = 0; p < 2; p++) {
-            if (lean_prec < 0 || p == 1)
-                HIPCHK(launch_clover_convert(prec, op->T[PREC_F64][p].as<double2>(), op->T[prec][p].p, g->g.Vh, st));
-            if (lean_prec < 0 || p == 0)
-                HIPCHK(launch_clover_convert(prec, op->Tinv[PREC_F64][p].as<double2>(), op->Tinv[prec][p].p, g->g.Vh,
-                                             st));
-        }
-    }
-    HIPCHK(hipStreamSynchronize(st));
     op->kappa = kappa;
     op->csw = csw;
     return BQ_OK;
@@ -1939,12 +1932,11 @@ static int op_build(bq_gauge g, double kappa, double csw, double mu, int lean_pr
     const size_t Vp = pad_sites(g->g.Vh);
     if (!g->B[0].p) {
         for (int p = 0; p < 2; p++) CHK(g->B[p].alloc(ctx, Vp * 36 * 16, CLEAR_NONE));
-        CloverBuild cb;
-        cb.g = g->g;
         const LinkSet* ls = g->get(PREC_F64, 18);
-        for (int k = 0; k < 8; k++) cb.U64[k] = (const double2*)ls->U[k];
-        for (int p = 0; p < 2; p++) cb.B[p] = g->B[p].as<double2>();
-        HIPCHK(launch_clover_build(cb, ctx->stream));
+        const double2* U[8];
+        for (int k = 0; k < 8; k++) U[k] = (const double2*)ls->U[k];
+        double2* const B[2] = {g->B[0].as<double2>(), g->B[1].as<double2>()};
+        HIPCHK(launch_clover_build(g->g, U, B, ctx->stream));
         HIPCHK(hipStreamSynchronize(ctx->stream));  // B is read on the build stream below
     }
     auto op = std::make_unique<bq_op_s>();
@@ -1969,7 +1961,7 @@ static int op_build(bq_gauge g, double kappa, double csw, double mu, int lean_pr
     }
     g->nops++;  // from here the operator is whole: freeing it releases this count
     bq_op o = op.release();
-    const int rc = clover_fill(o, kappa, csw, lean_prec, flag, st ? st : ctx->stream);
+    const int rc = clover_fill(o, kappa, csw, flag, st ? st : ctx->stream);
     if (rc != BQ_OK) {
         bq_op_free(o);
         return rc;
@@ -3170,7 +3162,7 @@ static int admit(bq_server S, Request* q, Session* s)
     if (!s->spare.empty()) {
         bq_op o = s->spare.back();
         s->spare.pop_back();
-        const int rc = clover_fill(o, q->kappa, q->csw, s->prec, s->flag.as<int>(), s->st);
+        const int rc = clover_fill(o, q->kappa, q->csw, s->flag.as<int>(), s->st);
         if (rc != BQ_OK) {
             s->spare.push_back(o);
             return rc;

@@ -31,26 +31,120 @@ __device__ __forceinline__ int lex_of(const Geom& g, int parity, int j)
 // the site-tiled checkerboard storage
 // --------------------------------------------------------------------------
 
-template <class P, int NC>
-__global__ void k_links_import(const double2* __restrict__ canon, const Geom g, int parity, typename P::unit* d0,
-                               typename P::unit* d1, typename P::unit* d2, typename P::unit* d3)
+// The link arrays [parity * 4 + mu] of one storage form.
+template <class U>
+struct LinkOut {
+    U* p[8];
+};
+
+// units 2m and 2m + 1 of a site lie side by side in 8-byte units: N of them, a last odd one alone
+template <int N>
+__device__ __forceinline__ void store_pairs(float2* b, int j, const float2 (&v)[N])
 {
-    using T = typename P::real;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= g.Vh) return;
-    const size_t V = 2 * (size_t)g.Vh;
-    const int lex = lex_of(g, parity, j);
-    typename P::unit* dst[4] = {d0, d1, d2, d3};
 #pragma unroll
-    for (int mu = 0; mu < 4; mu++) {
-        cx<T> u[NC];
+    for (int c = 0; c + 1 < N; c += 2) *(float4*)&at(b, j, c, N) = make_float4(v[c].x, v[c].y, v[c + 1].x, v[c + 1].y);
+    if constexpr (N & 1) at(b, j, N - 1, N) = v[N - 1];
+}
+
+// Canonical links into the 18-real forms, with the largest distance from SU(3): per link max over
+// max_ab |(U U^dag - 1)_ab| and |det U - 1|, one partial maximum per workgroup (the host takes the
+// maximum of the partials).  One wavefront per tile, parity and direction, turned around in LDS as
+// k_spinor_turn does (a link's 9 values are an odd number of 16-byte words already).  Bound by HBM:
+// reading the canonical links once for the check and once for each of five forms and two parities took
+// 1122 us at 24^3x48, now 161 (955 MB, 5.9 TB/s) and 122 in k_links_rows.
+__global__ __launch_bounds__(4 * kTile) void k_links_take(const double2* __restrict__ canon, const Geom g, LinkOut<double2> d,
+                                                          LinkOut<float2> f, double* partial)
+{
+    __shared__ double2 turn[4][kTile * 9];
+    __shared__ double wm[4];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> kTileLog), lane = threadIdx.x & (kTile - 1);
+    const int tile = blockIdx.x * 2 + (w >> 1), par = w & 1, mu = blockIdx.y;
+    double2* t = turn[w];
+    const int j = tile * kTile + lane;
+    const bool in = j < g.Vh;
+    const Site s = site_of(g, par, in ? j : 0);
+    const unsigned long long odd = __ballot(s.x & 1);
+    const int nu = 9 * min(kTile, g.Vh - tile * kTile);
+    const double2* can = canon + (size_t)mu * 2 * g.Vh * 9;
+    const size_t site0 = 2 * (size_t)tile * kTile;
 #pragma unroll
-        for (int k = 0; k < NC; k++) {
-            const double2 t = canon[((size_t)mu * V + lex) * 9 + k];
-            u[k] = {(T)t.x, (T)t.y};
+    for (int i = 0; i < 9; i++) {
+        const int u = i * kTile + lane;
+        if (u < nu) {
+            const int l = u / 9;
+            t[u] = ld_stream(can + (site0 + 2 * l + ((odd >> l) & 1)) * 9 + (u - 9 * l));
         }
-        CxIO<P, NC>::store(dst[mu], j, u);
     }
+    __syncthreads();
+    double dev = 0.0;
+    if (in) {
+        cx<double> u[9];
+#pragma unroll
+        for (int e = 0; e < 9; e++) {
+            const double2 x = t[lane * 9 + e];
+            u[e] = {x.x, x.y};
+        }
+        double2* db = d.p[par * 4 + mu];  // uniform over the wavefront
+        float2* fb = f.p[par * 4 + mu];
+        float2 v[9];
+#pragma unroll
+        for (int e = 0; e < 9; e++) {
+            at(db, j, e, 9) = make_double2(u[e].re, u[e].im);
+            v[e] = make_float2((float)u[e].re, (float)u[e].im);
+        }
+        store_pairs<9>(fb, j, v);
+#pragma unroll
+        for (int a = 0; a < 3; a++)
+#pragma unroll
+            for (int b = 0; b < 3; b++) {
+                cx<double> q = {0.0, 0.0};
+#pragma unroll
+                for (int c = 0; c < 3; c++) q = cmacc(q, u[b * 3 + c], u[a * 3 + c]);  // sum_c U_ac conj(U_bc)
+                if (a == b) q.re -= 1.0;
+                dev = fmax(dev, fmax(fabs(q.re), fabs(q.im)));
+            }
+        const cx<double> m0 = csub(cmul(u[4], u[8]), cmul(u[5], u[7]));
+        const cx<double> m1 = csub(cmul(u[5], u[6]), cmul(u[3], u[8]));
+        const cx<double> m2 = csub(cmul(u[3], u[7]), cmul(u[4], u[6]));
+        cx<double> det = cmul(u[0], m0);
+        det = cmac(det, u[1], m1);
+        det = cmac(det, u[2], m2);
+        det.re -= 1.0;
+        dev = fmax(dev, sqrt(cnorm2(det)));
+        if (!isfinite(dev)) dev = INFINITY;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) dev = fmax(dev, __shfl_xor(dev, off, 64));
+    if (lane == 0) wm[w] = dev;
+    __syncthreads();
+    if (threadIdx.x == 0) partial[blockIdx.y * gridDim.x + blockIdx.x] = fmax(fmax(wm[0], wm[1]), fmax(wm[2], wm[3]));
+}
+
+// The two-row forms of the precisions that keep one, from the FP64 18-real form in one pass.
+__global__ __launch_bounds__(256) void k_links_rows(LinkOut<double2> src, int Vh, LinkOut<double2> d, LinkOut<float2> f,
+                                                    LinkOut<uint2> h)
+{
+    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= Vh) return;
+    const double2* sb = src.p[blockIdx.y];
+    double2* db = d.p[blockIdx.y];
+    float2* fb = f.p[blockIdx.y];
+    uint2* hb = h.p[blockIdx.y];
+    double2 u[6];
+    float2 v[6];
+#pragma unroll
+    for (int e = 0; e < 6; e++) {
+        u[e] = ld_stream(&at(sb, j, e, 9));
+        v[e] = make_float2((float)u[e].x, (float)u[e].y);
+    }
+    if (db)
+#pragma unroll
+        for (int e = 0; e < 6; e++) at(db, j, e, 6) = u[e];
+    if (fb) store_pairs<6>(fb, j, v);
+    if (hb)
+#pragma unroll
+        for (int e = 0; e < 3; e++)
+            at(hb, j, e, 3) = CxIO<P16, 2>::pack(cx<float>{v[2 * e].x, v[2 * e].y}, cx<float>{v[2 * e + 1].x, v[2 * e + 1].y});
 }
 
 // Spinors between the canonical array and the tiles: one wavefront per tile, parity and column.
@@ -299,47 +393,6 @@ __global__ void k_restart(SpinorPtr<P64> r64, SpinorPtr<PRS> rs, SpinorPtr<PP> p
     store_spinor(p, c, j, pv);
 }
 
-// Distance of every link from SU(3): max over links of max(max_ab |(U U^dag - 1)_ab|, |det U - 1|),
-// one partial maximum per workgroup (the host takes the maximum of the partials).
-__global__ void k_link_su3_dev(const double2* __restrict__ canon, size_t nlinks, double* partial)
-{
-    __shared__ double w[4];
-    const size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    double dev = 0.0;
-    if (k < nlinks) {
-        cx<double> u[9];
-#pragma unroll
-        for (int e = 0; e < 9; e++) {
-            const double2 t = canon[k * 9 + e];
-            u[e] = {t.x, t.y};
-        }
-#pragma unroll
-        for (int a = 0; a < 3; a++)
-#pragma unroll
-            for (int b = 0; b < 3; b++) {
-                cx<double> s = {0.0, 0.0};
-#pragma unroll
-                for (int c = 0; c < 3; c++) s = cmacc(s, u[b * 3 + c], u[a * 3 + c]);  // sum_c U_ac conj(U_bc)
-                if (a == b) s.re -= 1.0;
-                dev = fmax(dev, fmax(fabs(s.re), fabs(s.im)));
-            }
-        const cx<double> m0 = csub(cmul(u[4], u[8]), cmul(u[5], u[7]));
-        const cx<double> m1 = csub(cmul(u[5], u[6]), cmul(u[3], u[8]));
-        const cx<double> m2 = csub(cmul(u[3], u[7]), cmul(u[4], u[6]));
-        cx<double> det = cmul(u[0], m0);
-        det = cmac(det, u[1], m1);
-        det = cmac(det, u[2], m2);
-        det.re -= 1.0;
-        dev = fmax(dev, sqrt(cnorm2(det)));
-        if (!isfinite(dev)) dev = INFINITY;
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) dev = fmax(dev, __shfl_xor(dev, off, 64));
-    if ((threadIdx.x & 63) == 0) w[threadIdx.x >> 6] = dev;
-    __syncthreads();
-    if (threadIdx.x == 0) partial[blockIdx.x] = fmax(fmax(w[0], w[1]), fmax(w[2], w[3]));
-}
-
 // complex Z2 noise from SplitMix64 used as a counter-based generator:
 // output k of stream `seed` is mix(seed + (k+1) * 0x9E3779B97F4A7C15);
 // component (noise n, lexicographic site i, spin s, colour c) uses k = (n*V + i)*12 + 3s + c,
@@ -398,6 +451,22 @@ __global__ void k_fin_sum(const double* partial, int nwaves, double* out)
     const int c = blockIdx.x;
     const double s = block_sum(partial + (size_t)c * nwaves, nwaves);
     if (threadIdx.x == 0) out[c] = s;
+}
+
+// out[0] = the largest of n partial maxima (infinite if one is not a number)
+__global__ __launch_bounds__(256) void k_fin_max(const double* partial, int n, double* out)
+{
+    __shared__ double w[4];
+    double m = 0.0;
+    for (int i = threadIdx.x; i < n; i += 256) {
+        const double v = partial[i];
+        m = fmax(m, isnan(v) ? (double)INFINITY : v);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+    if ((threadIdx.x & 63) == 0) w[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) out[0] = fmax(fmax(w[0], w[1]), fmax(w[2], w[3]));
 }
 
 __global__ void k_fin_alpha(const CgScalars s, const double* partial, int nwaves)
@@ -474,20 +543,34 @@ inline bool prec_ok(int prec) { return prec == PREC_F64 || prec == PREC_F32 || p
 
 }  // namespace
 
-hipError_t launch_links_import(const double2* canon, const Geom& g, int parity, int prec, int recon, void* const dst[4],
-                               hipStream_t st)
+int links_take_parts(const Geom& g) { return (g.ntiles + 1) / 2 * 4; }
+
+hipError_t launch_links_take(const double2* canon, const Geom& g, const void* const d18[8], const void* const f18[8],
+                             double* partial, hipStream_t st)
 {
-    const dim3 grid((g.Vh + kBS - 1) / kBS);
-#define LI(P, NC)                                                                                                 \
-    hipLaunchKernelGGL((k_links_import<P, NC>), grid, dim3(kBS), 0, st, canon, g, parity, (P::unit*)dst[0],       \
-                       (P::unit*)dst[1], (P::unit*)dst[2], (P::unit*)dst[3])
-    if (prec == PREC_F64 && recon == 18) LI(P64, 9);
-    else if (prec == PREC_F64 && recon == 12) LI(P64, 6);
-    else if (prec == PREC_F32 && recon == 18) LI(P32, 9);
-    else if (prec == PREC_F32 && recon == 12) LI(P32, 6);
-    else if (prec == PREC_F16 && recon == 12) LI(P16, 6);
-    else return hipErrorInvalidValue;
-#undef LI
+    LinkOut<double2> d;
+    LinkOut<float2> f;
+    for (int k = 0; k < 8; k++) {
+        d.p[k] = (double2*)d18[k];
+        f.p[k] = (float2*)f18[k];
+    }
+    hipLaunchKernelGGL(k_links_take, dim3((g.ntiles + 1) / 2, 4), dim3(4 * kTile), 0, st, canon, g, d, f, partial);
+    return hipGetLastError();
+}
+
+hipError_t launch_links_rows(const void* const d18[8], int Vh, const void* const d12[8], const void* const f12[8],
+                             const void* const h12[8], hipStream_t st)
+{
+    LinkOut<double2> src, d;
+    LinkOut<float2> f;
+    LinkOut<uint2> h;
+    for (int k = 0; k < 8; k++) {
+        src.p[k] = (double2*)d18[k];
+        d.p[k] = (double2*)d12[k];
+        f.p[k] = (float2*)f12[k];
+        h.p[k] = (uint2*)h12[k];
+    }
+    hipLaunchKernelGGL(k_links_rows, dim3((Vh + kBS - 1) / kBS, 8), dim3(kBS), 0, st, src, Vh, d, f, h);
     return hipGetLastError();
 }
 
@@ -642,15 +725,6 @@ hipError_t launch_restart(FieldArg r64, int rsprec, FieldArg rs, int pprec, Fiel
     return hipGetLastError();
 }
 
-int link_su3_parts(size_t nlinks) { return (int)((nlinks + kBS - 1) / kBS); }
-
-hipError_t launch_link_su3_dev(const double2* canon, size_t nlinks, double* partial, hipStream_t st)
-{
-    if (nlinks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_link_su3_dev, dim3(link_su3_parts(nlinks)), dim3(kBS), 0, st, canon, nlinks, partial);
-    return hipGetLastError();
-}
-
 hipError_t launch_z2_noise(uint64_t seed, long n0, const Geom& g, int parity, FieldArg dst, int ncol, hipStream_t st)
 {
     hipLaunchKernelGGL(k_z2_noise, grid2(g.Vh, ncol), dim3(kBS), 0, st, seed, n0, g, parity, sp<P64>(dst));
@@ -678,6 +752,12 @@ hipError_t launch_fin_reliable(const CgScalars& s, const double* partial, int nw
 hipError_t launch_fin_sum(const double* partial, int nwaves, int ncol, double* out, hipStream_t st)
 {
     hipLaunchKernelGGL(k_fin_sum, dim3(ncol), dim3(256), 0, st, partial, nwaves, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_fin_max(const double* partial, int n, double* out, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_fin_max, dim3(1), dim3(256), 0, st, partial, n, out);
     return hipGetLastError();
 }
 

@@ -20,142 +20,202 @@ struct M3 {
     c64 m[9];
 };
 
-__device__ __forceinline__ M3 m3_mul(const M3& a, const M3& b)
-{
-    M3 c;
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int k = 0; k < 3; k++) {
-            c64 s = cmul(a.m[i * 3 + 0], b.m[0 * 3 + k]);
-            s = cmac(s, a.m[i * 3 + 1], b.m[1 * 3 + k]);
-            s = cmac(s, a.m[i * 3 + 2], b.m[2 * 3 + k]);
-            c.m[i * 3 + k] = s;
-        }
-    return c;
-}
-
-// a * b^dag
-__device__ __forceinline__ M3 m3_mul_nd(const M3& a, const M3& b)
-{
-    M3 c;
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int k = 0; k < 3; k++) {
-            c64 s = {0, 0};
-            s = cmac(s, a.m[i * 3 + 0], c64{b.m[k * 3 + 0].re, -b.m[k * 3 + 0].im});
-            s = cmac(s, a.m[i * 3 + 1], c64{b.m[k * 3 + 1].re, -b.m[k * 3 + 1].im});
-            s = cmac(s, a.m[i * 3 + 2], c64{b.m[k * 3 + 2].re, -b.m[k * 3 + 2].im});
-            c.m[i * 3 + k] = s;
-        }
-    return c;
-}
-
-// a^dag * b
-__device__ __forceinline__ M3 m3_mul_dn(const M3& a, const M3& b)
-{
-    M3 c;
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int k = 0; k < 3; k++) {
-            c64 s = {0, 0};
-            s = cmacc(s, a.m[0 * 3 + i], b.m[0 * 3 + k]);
-            s = cmacc(s, a.m[1 * 3 + i], b.m[1 * 3 + k]);
-            s = cmacc(s, a.m[2 * 3 + i], b.m[2 * 3 + k]);
-            c.m[i * 3 + k] = s;
-        }
-    return c;
-}
-
-struct Coord {
-    int x[4];
+struct LinkTable {
+    const double2* U[8];
 };
 
-__device__ __forceinline__ Coord shift(const Geom& g, Coord c, int mu, int d)
+// The points of a plane (mu, nu) around site s, mu and nu uniform over the wavefront: a link m steps in
+// mu and n in nu (-1, 0, 1; periodic) away is at lexicographic index l0 + xm sm + xn sn, and on parity
+// p + m + n (the extents are even), so its array is uniform as well.
+struct Plane {
+    int parity, Lm, Ln, sm, sn;  // uniform
+    int l0, xm, xn;
+    __device__ __forceinline__ Plane(const Geom& g, const Site& s, int par, int mu, int nu)
+    {
+        parity = par;
+        Lm = g.L[mu];
+        Ln = g.L[nu];
+        sm = sn = 1;
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            sm *= k < mu ? g.L[k] : 1;
+            sn *= k < nu ? g.L[k] : 1;
+        }
+        const int c[4] = {s.x, s.y, s.z, s.t};
+        xm = xn = 0;
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            xm += k == mu ? c[k] : 0;
+            xn += k == nu ? c[k] : 0;
+        }
+        l0 = s.x + g.L[0] * (s.y + g.L[1] * (s.z + g.L[2] * s.t)) - xm * sm - xn * sn;
+    }
+    __device__ __forceinline__ int index(int m, int n) const  // in its parity
+    {
+        int a = xm + m, b = xn + n;
+        a = a < 0 ? a + Lm : (a >= Lm ? a - Lm : a);
+        b = b < 0 ? b + Ln : (b >= Ln ? b - Ln : b);
+        return (l0 + a * sm + b * sn) >> 1;
+    }
+    __device__ __forceinline__ M3 link(const LinkTable& t, int dir, int m, int n) const
+    {
+        const int j = index(m, n);
+        const double2* u = t.U[((parity + m + n) & 1) * 4 + dir];
+        M3 r;
+#pragma unroll
+        for (int k = 0; k < 9; k++) {
+            const double2 v = at(u, j, k, 9);
+            r.m[k] = {v.x, v.y};
+        }
+        return r;
+    }
+};
+
+// Products are taken in place, row by row (a = a b, a = a b^dag), so that a chain of links needs the
+// registers of one running product and one link.  hold() keeps the compiler from loading the links of
+// the next products before this one is done (359 registers spilled without it).
+__device__ __forceinline__ void hold(M3& a)
 {
-    int v = c.x[mu] + d;
-    c.x[mu] = v < 0 ? v + g.L[mu] : (v >= g.L[mu] ? v - g.L[mu] : v);
-    return c;
+#pragma unroll
+    for (int k = 0; k < 9; k++) asm volatile("" : "+v"(a.m[k].re), "+v"(a.m[k].im));
+    asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void m3_mul_by(M3& a, const M3& b)
+{
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        const c64 r0 = a.m[i * 3], r1 = a.m[i * 3 + 1], r2 = a.m[i * 3 + 2];
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            c64 s = cmul(r0, b.m[k]);
+            s = cmac(s, r1, b.m[3 + k]);
+            s = cmac(s, r2, b.m[6 + k]);
+            a.m[i * 3 + k] = s;
+        }
+    }
+    hold(a);
+}
+__device__ __forceinline__ void m3_mul_by_dag(M3& a, const M3& b)
+{
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        const c64 r0 = a.m[i * 3], r1 = a.m[i * 3 + 1], r2 = a.m[i * 3 + 2];
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            c64 s = {0, 0};
+            s = cmac(s, r0, c64{b.m[k * 3 + 0].re, -b.m[k * 3 + 0].im});
+            s = cmac(s, r1, c64{b.m[k * 3 + 1].re, -b.m[k * 3 + 1].im});
+            s = cmac(s, r2, c64{b.m[k * 3 + 2].re, -b.m[k * 3 + 2].im});
+            a.m[i * 3 + k] = s;
+        }
+    }
+    hold(a);
+}
+// a = a^dag b
+__device__ __forceinline__ void m3_dag_mul_by(M3& a, const M3& b)
+{
+    M3 t;
+#pragma unroll
+    for (int i = 0; i < 3; i++)
+#pragma unroll
+        for (int k = 0; k < 3; k++) t.m[i * 3 + k] = a.m[k * 3 + i];
+#pragma unroll
+    for (int i = 0; i < 3; i++)
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            c64 s = {0, 0};
+            s = cmacc(s, t.m[i * 3 + 0], b.m[0 * 3 + k]);
+            s = cmacc(s, t.m[i * 3 + 1], b.m[1 * 3 + k]);
+            s = cmacc(s, t.m[i * 3 + 2], b.m[2 * 3 + k]);
+            a.m[i * 3 + k] = s;
+        }
+    hold(a);
+}
+__device__ __forceinline__ void m3_add(M3& a, const M3& b)
+{
+#pragma unroll
+    for (int k = 0; k < 9; k++) a.m[k] = cadd(a.m[k], b.m[k]);
+    hold(a);
 }
 
-__device__ __forceinline__ M3 link_at(const Geom& g, const double2* const* U, const Coord& c, int mu)
+// the planes mu < nu in order
+__device__ __forceinline__ void plane_of(int p, int& mu, int& nu)
 {
-    const int par = (c.x[0] + c.x[1] + c.x[2] + c.x[3]) & 1;
-    const int lex = c.x[0] + g.L[0] * (c.x[1] + g.L[1] * (c.x[2] + g.L[2] * c.x[3]));
-    const int j = lex >> 1;
-    const double2* b = U[par * 4 + mu];
-    M3 m;
+    mu = p < 3 ? 0 : (p < 5 ? 1 : 2);
+    nu = p < 3 ? p + 1 : (p < 5 ? p - 1 : 3);
+}
+
+// A tile's links U_mu(x) and U_mu(x - mu) in LDS, [2 mu + (1 for x - mu)][entry][lane]
+typedef double2 TileLinks[8][9][kTile];
+
+__device__ __forceinline__ M3 lds_link(const double2 (&t)[9][kTile], int lane)
+{
+    M3 r;
 #pragma unroll
     for (int k = 0; k < 9; k++) {
-        double2 t = at(b, j, k, 9);
-        m.m[k] = {t.x, t.y};
+        const double2 v = t[k][lane];
+        r.m[k] = {v.x, v.y};
     }
-    return m;
+    return r;
 }
 
-// Hermitian traceless G = (Q - Q^dag)/(8i) of the four leaves in plane (mu, nu) at site c
-__device__ M3 field_strength(const Geom& g, const double2* const* U, const Coord& c, int mu, int nu)
+// Hermitian traceless G = (Q - Q^dag)/(8i) of the four leaves in a plane: its three diagonal reals, then
+// its lower triangle (1,0), (2,0), (2,1)
+__device__ __forceinline__ void field_strength(const Plane& x, const LinkTable& U, const TileLinks& t, int lane, int mu,
+                                               int nu, double (&out)[9])
 {
-    const Coord xpm = shift(g, c, mu, +1), xpn = shift(g, c, nu, +1);
-    const Coord xmm = shift(g, c, mu, -1), xmn = shift(g, c, nu, -1);
-    const Coord xpn_mm = shift(g, xpn, mu, -1);
-    const Coord xmm_mn = shift(g, xmm, nu, -1);
-    const Coord xmn_pm = shift(g, xmn, mu, +1);
-
-    const M3 Umu_x = link_at(g, U, c, mu), Unu_x = link_at(g, U, c, nu);
-    M3 Q;
     // leaf 1: U_mu(x) U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
-    {
-        M3 a = m3_mul(Umu_x, link_at(g, U, xpm, nu));
-        a = m3_mul_nd(a, link_at(g, U, xpn, mu));
-        Q = m3_mul_nd(a, Unu_x);
-    }
+    M3 Q = lds_link(t[2 * mu], lane);
+    m3_mul_by(Q, x.link(U, nu, 1, 0));
+    m3_mul_by_dag(Q, x.link(U, mu, 0, 1));
+    m3_mul_by_dag(Q, lds_link(t[2 * nu], lane));
     // leaf 2: U_nu(x) U_mu(x+nu-mu)^dag U_nu(x-mu)^dag U_mu(x-mu)
     {
-        M3 a = m3_mul_nd(Unu_x, link_at(g, U, xpn_mm, mu));
-        a = m3_mul_nd(a, link_at(g, U, xmm, nu));
-        a = m3_mul(a, link_at(g, U, xmm, mu));
-#pragma unroll
-        for (int k = 0; k < 9; k++) Q.m[k] = cadd(Q.m[k], a.m[k]);
+        M3 a = lds_link(t[2 * nu], lane);
+        m3_mul_by_dag(a, x.link(U, mu, -1, 1));
+        m3_mul_by_dag(a, x.link(U, nu, -1, 0));
+        m3_mul_by(a, lds_link(t[2 * mu + 1], lane));
+        m3_add(Q, a);
     }
     // leaf 3: U_mu(x-mu)^dag U_nu(x-mu-nu)^dag U_mu(x-mu-nu) U_nu(x-nu)
     {
         // U_mu(x-mu)^dag U_nu(x-mu-nu)^dag = (U_nu(x-mu-nu) U_mu(x-mu))^dag
-        const M3 ba = m3_mul(link_at(g, U, xmm_mn, nu), link_at(g, U, xmm, mu));
-        M3 t;
+        M3 a = x.link(U, nu, -1, -1);
+        m3_mul_by(a, lds_link(t[2 * mu + 1], lane));
+        M3 ad;
 #pragma unroll
         for (int i = 0; i < 3; i++)
 #pragma unroll
-            for (int k = 0; k < 3; k++) t.m[i * 3 + k] = {ba.m[k * 3 + i].re, -ba.m[k * 3 + i].im};
-        t = m3_mul(t, link_at(g, U, xmm_mn, mu));
-        t = m3_mul(t, link_at(g, U, xmn, nu));
-#pragma unroll
-        for (int k = 0; k < 9; k++) Q.m[k] = cadd(Q.m[k], t.m[k]);
+            for (int k = 0; k < 3; k++) ad.m[i * 3 + k] = {a.m[k * 3 + i].re, -a.m[k * 3 + i].im};
+        m3_mul_by(ad, x.link(U, mu, -1, -1));
+        m3_mul_by(ad, lds_link(t[2 * nu + 1], lane));
+        m3_add(Q, ad);
     }
     // leaf 4: U_nu(x-nu)^dag U_mu(x-nu) U_nu(x-nu+mu) U_mu(x)^dag
     {
-        M3 a = m3_mul_dn(link_at(g, U, xmn, nu), link_at(g, U, xmn, mu));
-        a = m3_mul(a, link_at(g, U, xmn_pm, nu));
-        a = m3_mul_nd(a, Umu_x);
-#pragma unroll
-        for (int k = 0; k < 9; k++) Q.m[k] = cadd(Q.m[k], a.m[k]);
+        M3 a = lds_link(t[2 * nu + 1], lane);
+        m3_dag_mul_by(a, x.link(U, mu, 0, -1));
+        m3_mul_by(a, x.link(U, nu, 1, -1));
+        m3_mul_by_dag(a, lds_link(t[2 * mu], lane));
+        m3_add(Q, a);
     }
     // G = (Q - Q^dag) / (8 i): G_ik = -i (Q_ik - conj(Q_ki)) / 8
-    M3 G;
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int k = 0; k < 3; k++) {
-            const c64 d = {Q.m[i * 3 + k].re - Q.m[k * 3 + i].re, Q.m[i * 3 + k].im + Q.m[k * 3 + i].im};
-            G.m[i * 3 + k] = {d.im * 0.125, -d.re * 0.125};
-        }
-    const double tr = (G.m[0].re + G.m[4].re + G.m[8].re) / 3.0;
-    G.m[0].re -= tr;
-    G.m[4].re -= tr;
-    G.m[8].re -= tr;
-    return G;
+    auto G = [&](int i, int k) {
+        const c64 d = {Q.m[i * 3 + k].re - Q.m[k * 3 + i].re, Q.m[i * 3 + k].im + Q.m[k * 3 + i].im};
+        return c64{d.im * 0.125, -d.re * 0.125};
+    };
+    const double g0 = G(0, 0).re, g1 = G(1, 1).re, g2 = G(2, 2).re;
+    const double tr = (g0 + g1 + g2) / 3.0;
+    out[0] = g0 - tr;
+    out[1] = g1 - tr;
+    out[2] = g2 - tr;
+    const c64 l10 = G(1, 0), l20 = G(2, 0), l21 = G(2, 1);
+    out[3] = l10.re;
+    out[4] = l10.im;
+    out[5] = l20.re;
+    out[6] = l20.im;
+    out[7] = l21.re;
+    out[8] = l21.im;
 }
 
 // dense Hermitian 6x6 block helpers
@@ -163,19 +223,36 @@ struct H6 {
     c64 a[36];
 };
 
-__device__ __forceinline__ void pack_store(double2* T, int j, int blk, const H6& A)
+// where one clover field (T or its inverse) goes in each storage precision; null: nowhere
+struct CloverOut {
+    double2* d;
+    float2* f;
+    uint2* h;
+};
+
+__device__ __forceinline__ void pack_store(const CloverOut& T, int j, int blk, const H6& A)
 {
-    if (T == nullptr) return;
-    at(T, j, blk * 18 + 0, 36) = make_double2(A.a[0].re, A.a[7].re);
-    at(T, j, blk * 18 + 1, 36) = make_double2(A.a[14].re, A.a[21].re);
-    at(T, j, blk * 18 + 2, 36) = make_double2(A.a[28].re, A.a[35].re);
+    c64 c[18];
+    c[0] = {A.a[0].re, A.a[7].re};
+    c[1] = {A.a[14].re, A.a[21].re};
+    c[2] = {A.a[28].re, A.a[35].re};
 #pragma unroll
     for (int i = 1; i < 6; i++)
 #pragma unroll
-        for (int k = 0; k < i; k++) {
-            const c64 v = A.a[i * 6 + k];
-            at(T, j, blk * 18 + 3 + i * (i - 1) / 2 + k, 36) = make_double2(v.re, v.im);
-        }
+        for (int k = 0; k < i; k++) c[3 + i * (i - 1) / 2 + k] = A.a[i * 6 + k];
+    if (T.d)
+#pragma unroll
+        for (int k = 0; k < 18; k++) st_stream(&at(T.d, j, blk * 18 + k, 36), make_double2(c[k].re, c[k].im));
+    if (T.f)
+#pragma unroll
+        for (int k = 0; k < 18; k += 2)  // units 2m and 2m + 1 of a site lie side by side
+            *(float4*)&at(T.f, j, blk * 18 + k, 36) =
+                make_float4((float)c[k].re, (float)c[k].im, (float)c[k + 1].re, (float)c[k + 1].im);
+    if (T.h)
+#pragma unroll
+        for (int k = 0; k < 18; k += 2)
+            at(T.h, j, blk * 9 + k / 2, 18) = CxIO<P16, 2>::pack(cx<float>{(float)c[k].re, (float)c[k].im},
+                                                                 cx<float>{(float)c[k + 1].re, (float)c[k + 1].im});
 }
 
 __device__ __forceinline__ H6 pack_load(const double2* T, int j, int blk)
@@ -257,86 +334,106 @@ __device__ bool hpd_inverse(const H6& A, H6& Ai)
     return ok;
 }
 
-// B block (without identity and kappa c_SW) from X1, X2, X3
-__device__ __forceinline__ H6 block_from(const M3& X1, const M3& X2, const M3& X3)
+// B (the clover blocks without identity and kappa c_SW) of one tile per workgroup, one wavefront per
+// plane: its field strengths meet in LDS, then wavefront 3 * block + part assembles and stores six of
+// the block's 18 packed units.  Bound by the fills of the L1: the leaves of six planes read 96 links
+// per site, 48 of them the links U_mu(x) and U_mu(x - mu) that three planes each read twice; those
+// come from LDS here (24^3x48, both parities: 808 us with one thread per site for all planes, 790 with
+// one wavefront per plane, 545 with the eight links in LDS).
+__global__ __launch_bounds__(6 * kTile) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_clover_build(
+    const Geom g, const LinkTable U, double2* __restrict__ B0, double2* __restrict__ B1)
 {
-    H6 B;
+    __shared__ TileLinks sl;
+    double(*sg)[9][kTile] = (double(*)[9][kTile])sl;  // after the links: [plane][real of G][lane]
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> kTileLog), lane = threadIdx.x & (kTile - 1);
+    const int lb = xcd_remap(blockIdx.x, gridDim.x);  // the two parities of a tile side by side
+    const int parity = lb & 1;
+    const int j = (lb >> 1) * kTile + lane;
+    double2* __restrict__ B = parity ? B1 : B0;
+    const bool in = j < g.Vh;
+    const Site s = site_of(g, parity, in ? j : 0);
+    for (int h = w; h < 8; h += 6) {
+        const int mu = h >> 1, bw = h & 1;
+        const double2* u = U.U[(parity ^ bw) * 4 + mu];
+        const int jl = Plane(g, s, parity, mu, (mu + 1) & 3).index(-bw, 0);
 #pragma unroll
-    for (int a = 0; a < 3; a++)
-#pragma unroll
-        for (int b = 0; b < 3; b++) {
-            const c64 x1 = X1.m[a * 3 + b], x2 = X2.m[a * 3 + b], x3 = X3.m[a * 3 + b];
-            B.a[a * 6 + b] = x3;                                   // (0,0): X3
-            B.a[(3 + a) * 6 + 3 + b] = {-x3.re, -x3.im};           // (1,1): -X3
-            B.a[a * 6 + 3 + b] = {x1.re + x2.im, x1.im - x2.re};   // (0,1): X1 - i X2
-            B.a[(3 + a) * 6 + b] = {x1.re - x2.im, x1.im + x2.re}; // (1,0): X1 + i X2
-        }
-    return B;
-}
-
-__global__ __launch_bounds__(64) void k_clover_build(const CloverBuild c, int parity)
-{
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= c.g.Vh) return;
-    const Site s = site_of(c.g, parity, j);
-    Coord x;
-    x.x[0] = s.x;
-    x.x[1] = s.y;
-    x.x[2] = s.z;
-    x.x[3] = s.t;
-    const double2* U[8];
-    for (int k = 0; k < 8; k++) U[k] = c.U64[k];
-    const M3 G01 = field_strength(c.g, U, x, 0, 1), G02 = field_strength(c.g, U, x, 0, 2);
-    const M3 G03 = field_strength(c.g, U, x, 0, 3), G12 = field_strength(c.g, U, x, 1, 2);
-    const M3 G13 = field_strength(c.g, U, x, 1, 3), G23 = field_strength(c.g, U, x, 2, 3);
-    bool ok = true;
-#pragma unroll
-    for (int blk = 0; blk < 2; blk++) {
-        const double sg = blk == 0 ? -1.0 : +1.0;  // block 0: X3 = G01 - G23, X2 = G02 + G13, X1 = G12 - G03
-        M3 X1, X2, X3;
-#pragma unroll
-        for (int k = 0; k < 9; k++) {
-            X3.m[k] = {G01.m[k].re + sg * G23.m[k].re, G01.m[k].im + sg * G23.m[k].im};
-            X2.m[k] = {G02.m[k].re - sg * G13.m[k].re, G02.m[k].im - sg * G13.m[k].im};
-            X1.m[k] = {G12.m[k].re + sg * G03.m[k].re, G12.m[k].im + sg * G03.m[k].im};
-        }
-        const H6 B = block_from(X1, X2, X3);
-        if (c.B[parity]) pack_store(c.B[parity], j, blk, B);
-        H6 T;
-#pragma unroll
-        for (int k = 0; k < 36; k++) T.a[k] = cscale(c.ckappa, B.a[k]);
-#pragma unroll
-        for (int i = 0; i < 6; i++) T.a[i * 6 + i].re += 1.0;
-        if (c.T[parity]) pack_store(c.T[parity], j, blk, T);
-        if (c.Tinv[parity]) {
-            H6 Ti;
-            ok = hpd_inverse(T, Ti) && ok;
-            pack_store(c.Tinv[parity], j, blk, Ti);
-        }
+        for (int k = 0; k < 9; k++) sl[h][k][lane] = at(u, jl, k, 9);
     }
-    if (!ok && c.bad) *c.bad = 1;
+    __syncthreads();
+    {
+        int mu, nu;
+        plane_of(w, mu, nu);
+        double G[9];
+        field_strength(Plane(g, s, parity, mu, nu), U, sl, lane, mu, nu, G);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 9; k++) sg[w][k][lane] = G[k];
+    }
+    __syncthreads();
+    if (!in) return;
+    // block 0: X3 = G01 - G23, X2 = G02 + G13, X1 = G12 - G03; block 1 with the other signs
+    const int blk = w / 3, part = w % 3;
+    const double sgn = blk == 0 ? -1.0 : +1.0;
+    auto low = [&](int p, int a, int b) {  // G_p[a][b]
+        if (a == b) return c64{sg[p][a][lane], 0.0};
+        const int e = a > b ? (a == 1 ? 3 : (b == 0 ? 5 : 7)) : (b == 1 ? 3 : (a == 0 ? 5 : 7));
+        const double re = sg[p][e][lane], im = sg[p][e + 1][lane];
+        return c64{re, a > b ? im : -im};
+    };
+    auto X3 = [&](int a, int b) {
+        const c64 u = low(0, a, b), v = low(5, a, b);
+        return c64{u.re + sgn * v.re, u.im + sgn * v.im};
+    };
+    auto X21 = [&](int a, int b) {  // X1 + i X2
+        const c64 u = low(1, a, b), v = low(4, a, b), p = low(3, a, b), q = low(2, a, b);
+        const c64 x2 = {u.re - sgn * v.re, u.im - sgn * v.im}, x1 = {p.re + sgn * q.re, p.im + sgn * q.im};
+        return c64{x1.re - x2.im, x1.im + x2.re};
+    };
+    auto put = [&](int unit, c64 v) { st_stream(&at(B, j, blk * 18 + unit, 36), make_double2(v.re, v.im)); };
+    if (part == 0) {  // diagonal (x3, -x3) and the lower triangle of rows 1, 2
+        const double d0 = X3(0, 0).re, d1 = X3(1, 1).re, d2 = X3(2, 2).re;
+        put(0, {d0, d1});
+        put(1, {d2, -d0});
+        put(2, {-d1, -d2});
+        put(3, X3(1, 0));
+        put(4, X3(2, 0));
+        put(5, X3(2, 1));
+    } else if (part == 1) {  // rows 3, 4, columns 0..2
+#pragma unroll
+        for (int b = 0; b < 3; b++) put(3 + 3 + b, X21(0, b));
+#pragma unroll
+        for (int b = 0; b < 3; b++) put(3 + 6 + b, X21(1, b));
+    } else {  // row 5, columns 0..2, and -X3 below the diagonal of rows 4, 5
+#pragma unroll
+        for (int b = 0; b < 3; b++) put(3 + 10 + b, X21(2, b));
+        const c64 a = X3(1, 0), b = X3(2, 0), c = X3(2, 1);
+        put(3 + 9, {-a.re, -a.im});
+        put(3 + 13, {-b.re, -b.im});
+        put(3 + 14, {-c.re, -c.im});
+    }
 }
 
-__global__ __launch_bounds__(64) void k_clover_from_B(const Geom g, const double2* B, double ck, double2* T, double2* Tinv, int* bad)
+// T = 1 + ck B and its inverse in every storage precision asked for, one thread per site and block.
+// Bound by HBM: with the conversions as passes of their own over the FP64 results, 24^3x48 took 381
+// us per parity for the three precisions, now 154 (860 MB, 5.6 TB/s).
+__global__ __launch_bounds__(64) void k_clover_from_B(const Geom g, const double2* __restrict__ B, double ck, CloverOut T,
+                                                      CloverOut Tinv, int* bad)
 {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= g.Vh) return;
-    bool ok = true;
-#pragma unroll 1
-    for (int blk = 0; blk < 2; blk++) {
-        H6 A = pack_load(B, j, blk);
+    const int blk = blockIdx.y;
+    H6 A = pack_load(B, j, blk);
 #pragma unroll
-        for (int k = 0; k < 36; k++) A.a[k] = cscale(ck, A.a[k]);
+    for (int k = 0; k < 36; k++) A.a[k] = cscale(ck, A.a[k]);
 #pragma unroll
-        for (int i = 0; i < 6; i++) A.a[i * 6 + i].re += 1.0;
-        if (T) pack_store(T, j, blk, A);
-        if (Tinv) {
-            H6 Ai;
-            ok = hpd_inverse(A, Ai) && ok;
-            pack_store(Tinv, j, blk, Ai);
-        }
+    for (int i = 0; i < 6; i++) A.a[i * 6 + i].re += 1.0;
+    pack_store(T, j, blk, A);
+    if (Tinv.d || Tinv.f || Tinv.h) {
+        H6 Ai;
+        const bool ok = hpd_inverse(A, Ai);
+        pack_store(Tinv, j, blk, Ai);
+        if (!ok && bad) *bad = 1;
     }
-    if (!ok && bad) *bad = 1;
 }
 
 struct CloverCols {
@@ -382,57 +479,43 @@ __global__ void k_clover_apply(const Geom g, const typename P::unit* C0, SpinorP
     store_spinor(out, c, j, y);
 }
 
-// FP64 -> FP32 clover, one storage unit of one site per thread (the two precisions' tiles
-// order their units differently)
-__global__ void k_clover_convert32(const double2* src, float2* dst, int Vh)
+// sum over the 6 planes of Re tr U_{mu nu}(x) / 3, one FP64 partial per tile; one wavefront per plane, the
+// planes of a site summed in order.  The tile's own four links are read once, into LDS (24^3x48: 227 ->
+// 126 us).
+__global__ __launch_bounds__(6 * kTile) void k_plaquette(const Geom g, const LinkTable U, double* partial, int nwaves)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    const int u = blockIdx.y;
-    if (j >= Vh) return;
-    const double2 t = at(src, j, u, 36);
-    at(dst, j, u, 36) = make_float2((float)t.x, (float)t.y);
-}
-
-// FP64 packed clover (36 complex/site) -> FP16 (18 units of 2 complex/site)
-__global__ void k_clover_convert16(const double2* src, uint2* dst, int Vh)
-{
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    const int u = blockIdx.y;  // 0..17
-    if (j >= Vh) return;
-    double2 a = at(src, j, 2 * u, 36), b = at(src, j, 2 * u + 1, 36);
-    at(dst, j, u, 18) = CxIO<P16, 2>::pack(cx<float>{(float)a.x, (float)a.y}, cx<float>{(float)b.x, (float)b.y});
-}
-
-// sum over the 6 planes of Re tr U_{mu nu}(x) / 3, one FP64 partial per wavefront
-struct LinkTable {
-    const double2* U[8];
-};
-
-__global__ __launch_bounds__(64) void k_plaquette_v(const Geom g, const LinkTable t, int parity, double* partial, int nwaves)
-{
-    // kernel arguments cannot hold a pointer-to-pointer into host memory; copy the table into registers
-    const double2* U[8];
-    for (int k = 0; k < 8; k++) U[k] = t.U[k];
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    double acc = 0.0;
-    if (j < g.Vh) {
-        const Site s = site_of(g, parity, j);
-        Coord x;
-        x.x[0] = s.x;
-        x.x[1] = s.y;
-        x.x[2] = s.z;
-        x.x[3] = s.t;
-        for (int mu = 0; mu < 4; mu++)
-            for (int nu = mu + 1; nu < 4; nu++) {
-                M3 a = m3_mul(link_at(g, U, x, mu), link_at(g, U, shift(g, x, mu, +1), nu));
-                a = m3_mul_nd(a, link_at(g, U, shift(g, x, nu, +1), mu));
-                a = m3_mul_nd(a, link_at(g, U, x, nu));
-                acc += (a.m[0].re + a.m[4].re + a.m[8].re) / 3.0;
-            }
+    __shared__ double2 own[4][9][kTile];
+    __shared__ double sp[6][kTile];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> kTileLog), lane = threadIdx.x & (kTile - 1);
+    const int lb = xcd_remap(blockIdx.x, gridDim.x);  // the two parities of a tile side by side
+    const int parity = lb & 1, tile = lb >> 1;
+    const int j = tile * kTile + lane;
+    const bool in = j < g.Vh;
+    if (w < 4) {
+        const double2* u = U.U[parity * 4 + w];
+#pragma unroll
+        for (int k = 0; k < 9; k++) own[w][k][lane] = at(u, in ? j : 0, k, 9);
     }
+    __syncthreads();
+    {
+        const Site s = site_of(g, parity, in ? j : 0);
+        int mu, nu;
+        plane_of(w, mu, nu);
+        const Plane x(g, s, parity, mu, nu);
+        M3 a = lds_link(own[mu], lane);
+        m3_mul_by(a, x.link(U, nu, 1, 0));
+        m3_mul_by_dag(a, x.link(U, mu, 0, 1));
+        m3_mul_by_dag(a, lds_link(own[nu], lane));
+        sp[w][lane] = (a.m[0].re + a.m[4].re + a.m[8].re) / 3.0;
+    }
+    __syncthreads();
+    if (w != 0) return;
+    double acc = 0.0;
+    if (in)
+#pragma unroll
+        for (int p = 0; p < 6; p++) acc += sp[p][lane];
     acc = wave_sum(acc);
-    const int w = j >> kTileLog;
-    if ((threadIdx.x & 63) == 0 && w < nwaves) partial[w] = acc;
+    if (lane == 0 && tile < nwaves) partial[parity * nwaves + tile] = acc;
 }
 
 }  // namespace
@@ -444,25 +527,24 @@ hipError_t launch_plaquette(const Geom& g, const double2* const U64[8], double* 
     for (int k = 0; k < 8; k++) t.U[k] = U64[k];
     const int nw = pad_sites(g.Vh) / kTile;
     if (nparts < 2 * nw) return hipErrorInvalidValue;
-    for (int p = 0; p < 2; p++)
-        hipLaunchKernelGGL(k_plaquette_v, dim3((g.Vh + 63) / 64), dim3(64), 0, st, g, t, p, partial + p * nw, nw);
+    hipLaunchKernelGGL(k_plaquette, dim3(2 * nw), dim3(6 * kTile), 0, st, g, t, partial, nw);
     return hipGetLastError();
 }
 
-hipError_t launch_clover_build(const CloverBuild& c, hipStream_t st)
+hipError_t launch_clover_build(const Geom& g, const double2* const U64[8], double2* const B[2], hipStream_t st)
 {
-    const int bs = 64;
-    for (int p = 0; p < 2; p++)
-        hipLaunchKernelGGL(k_clover_build, dim3((c.g.Vh + bs - 1) / bs), dim3(bs), 0, st, c, p);
+    LinkTable t;
+    for (int k = 0; k < 8; k++) t.U[k] = U64[k];
+    hipLaunchKernelGGL(k_clover_build, dim3(2 * g.ntiles), dim3(6 * kTile), 0, st, g, t, B[0], B[1]);
     return hipGetLastError();
 }
 
-hipError_t launch_clover_from_B(const Geom& g, int parity, const double2* B, double ck, double2* T, double2* Tinv,
+hipError_t launch_clover_from_B(const Geom& g, const double2* B, double ck, void* const T[3], void* const Tinv[3],
                                 int* bad, hipStream_t st)
 {
-    (void)parity;
-    const int bs = 64;
-    hipLaunchKernelGGL(k_clover_from_B, dim3((g.Vh + bs - 1) / bs), dim3(bs), 0, st, g, B, ck, T, Tinv, bad);
+    const CloverOut t = {(double2*)T[PREC_F64], (float2*)T[PREC_F32], (uint2*)T[PREC_F16]};
+    const CloverOut ti = {(double2*)Tinv[PREC_F64], (float2*)Tinv[PREC_F32], (uint2*)Tinv[PREC_F16]};
+    hipLaunchKernelGGL(k_clover_from_B, dim3(g.ntiles, 2), dim3(kTile), 0, st, g, B, ck, t, ti, bad);
     return hipGetLastError();
 }
 
@@ -494,20 +576,6 @@ hipError_t launch_clover_apply(int prec, const Geom& g, const void* clov, FieldA
                            SpinorPtr<P16>{(uint2*)out.d, out.s, out.cstride, out.sstride}, ncol, percol, cc, status, statmask);
         break;
     default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_clover_convert(int prec, const double2* src, void* dst, int Vh, hipStream_t st)
-{
-    const int bs = 256;
-    const int Vp = pad_sites(Vh);
-    if (prec == PREC_F32) {
-        hipLaunchKernelGGL(k_clover_convert32, dim3((Vp + bs - 1) / bs, 36), dim3(bs), 0, st, src, (float2*)dst, Vp);
-    } else if (prec == PREC_F16) {
-        hipLaunchKernelGGL(k_clover_convert16, dim3((Vh + bs - 1) / bs, 18), dim3(bs), 0, st, src, (uint2*)dst, Vh);
-    } else {
-        return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }

@@ -66,35 +66,30 @@ hipError_t launch_hop(const HopLaunch& L, hipStream_t st);
 bool hop_variant_exists(int prec, int rprec, int recon, int R, int epi);
 
 // clover
-struct CloverBuild {
-    Geom g{};
-    const double2* U64[8] = {};   // FP64 links, 18 reals
-    double ckappa = 0;            // kappa * c_SW
-    double2* T[2] = {};           // out: T on parity 0/1 (packed blocks, FP64); may be null
-    double2* Tinv[2] = {};        // out: T^-1 on parity 0/1; may be null
-    double2* B[2] = {};           // out: sum_{mu<nu} sigma (x) F (kappa-independent), may be null
-    int* bad = nullptr;           // set to 1 if some block is not positive definite
-};
-hipError_t launch_clover_build(const CloverBuild& c, hipStream_t st);
-// T = 1 + ck*B and T^-1 from a stored B (per-kappa rebuild)
-hipError_t launch_clover_from_B(const Geom& g, int parity, const double2* B, double ck, double2* T, double2* Tinv,
+// B = sum_{mu<nu} sigma (x) F per parity (independent of kappa and c_SW) from the FP64 18-real links
+hipError_t launch_clover_build(const Geom& g, const double2* const U64[8], double2* const B[2], hipStream_t st);
+// T = 1 + ck*B and T^-1 of one parity, packed, in each storage precision whose pointer is not null;
+// bad is set to 1 if a block is not positive definite (checked where an inverse is asked for)
+hipError_t launch_clover_from_B(const Geom& g, const double2* B, double ck, void* const T[3], void* const Tinv[3],
                                 int* bad, hipStream_t st);
 hipError_t launch_clover_apply(int prec, const Geom& g, const void* clov, FieldArg in, FieldArg out, int ncol,
                                hipStream_t st, const void* const* cclov = nullptr, const int* status = nullptr,
                                int statmask = 0);
-hipError_t launch_clover_convert(int prec, const double2* src, void* dst, int Vh, hipStream_t st);
 
 // layout conversion
-hipError_t launch_links_import(const double2* canon, const Geom& g, int parity, int prec, int recon, void* const dst[4],
-                               hipStream_t st);
+// canonical links into the 18-real forms ([parity*4 + mu]); partial: links_take_parts maxima of the
+// links' distance from SU(3)
+int links_take_parts(const Geom& g);
+hipError_t launch_links_take(const double2* canon, const Geom& g, const void* const d18[8], const void* const f18[8],
+                             double* partial, hipStream_t st);
+// the two-row forms from the FP64 18-real one; entries of a form that is not kept are null
+hipError_t launch_links_rows(const void* const d18[8], int Vh, const void* const d12[8], const void* const f12[8],
+                             const void* const h12[8], hipStream_t st);
 // np parities from p0 on at once; dst / src: the field of parity p0, half_units (half_sites: scales) to the next
 hipError_t launch_spinor_import(const double2* canon, int ncol, const Geom& g, int p0, int np, int prec, FieldArg dst,
                                 size_t half_units, size_t half_sites, hipStream_t st);
 hipError_t launch_spinor_export(FieldArg src, int ncol, const Geom& g, int p0, int np, int prec, size_t half_units,
                                 size_t half_sites, double2* canon, hipStream_t st);
-// distance of the canonical FP64 links from SU(3): one partial maximum per part (see link_su3_parts)
-int link_su3_parts(size_t nlinks);
-hipError_t launch_link_su3_dev(const double2* canon, size_t nlinks, double* partial, hipStream_t st);
 hipError_t launch_plaquette(const Geom& g, const double2* const U64[8], double* partial, int nparts, hipStream_t st);
 
 // BLAS-1 and reductions
@@ -266,6 +261,7 @@ struct CgScalars {
 hipError_t launch_fin_alpha(const CgScalars& s, const double* partial, int nwaves, int ncol, hipStream_t st);
 hipError_t launch_fin_beta(const CgScalars& s, const double* partial, int nwaves, int ncol, hipStream_t st);
 hipError_t launch_fin_reliable(const CgScalars& s, const double* partial, int nwaves, int ncol, hipStream_t st);
+hipError_t launch_fin_max(const double* partial, int n, double* out, hipStream_t st);  // the largest of n
 hipError_t launch_fin_sum(const double* partial, int nwaves, int ncol, double* out, hipStream_t st);
 // stop2 = tol2 * rho, rmax2 = rho, counters cleared, status from rho (rho holds |b|^2 on entry);
 // with `sel` only columns with sel[c] != 0 are initialised, and tol2 is per column (tol2c) if given
