@@ -1052,7 +1052,10 @@ __global__ __launch_bounds__(lds_max_threads<P>()) __attribute__((amdgpu_waves_p
     }
     const int tile = tile_at(A.g, lt);                // lt < ntiles: one tile per workgroup
     const int base = tile * kTile;
-    // 1. stage the tile's links (8 half hops x 64 sites) and clover
+    // 1. stage the tile's links (8 half hops x 64 sites) and clover.  One workgroup (one per chunk of
+    // columns) reads them, so they stream past the neighbour spinors in the L2: the launch is bound by
+    // what the L2s miss (32^3x64 x 12, FP32: 6.5 GB in 0.9 ms).  Mhat at 24^3x48, cached -> streamed: FP32 x
+    // 12 755 -> 731 us, FP64 x 4 667 -> 640, x 16 2362 -> 2304, FP16 x 8 368 -> 361
     for (int t = threadIdx.x; t < 8 * kTile; t += blockDim.x) {
         const int site = t & (kTile - 1), H = t >> kTileLog;
         const int mu = H >> 1;
@@ -1063,7 +1066,8 @@ __global__ __launch_bounds__(lds_max_threads<P>()) __attribute__((amdgpu_waves_p
             const Site st = site_of(A.g, A.parity, j);
             const int jn = nbr(A.g, st, mu, bw ? -1 : +1);
             Raw<P, link_cx<RECON>()> raw;
-            load_units<P, link_cx<RECON>(), LA>(buf_rsrc(A.U[(bw ? 1 - A.parity : A.parity) * 4 + mu]), bw ? jn : j, raw);
+            load_units<P, link_cx<RECON>(), kBufNT>(buf_rsrc(A.U[(bw ? 1 - A.parity : A.parity) * 4 + mu]), bw ? jn : j,
+                                                    raw);
             link_from_raw<P, RECON>(raw, u);
         } else {
 #pragma unroll
@@ -1078,7 +1082,7 @@ __global__ __launch_bounds__(lds_max_threads<P>()) __attribute__((amdgpu_waves_p
         const __amdgpu_buffer_rsrc_t rs = buf_rsrc(C);
         for (int t = threadIdx.x; t < (NU / 2) * kTile; t += blockDim.x) {
             const int site = t & (kTile - 1), q = t >> kTileLog;
-            const bq_u4v v = buf_load16<LA>(rs, (uint32_t)toff<U>(site, 2 * q, NU) * 8u);
+            const bq_u4v v = buf_load16<kBufNT>(rs, (uint32_t)toff<U>(site, 2 * q, NU) * 8u);
             sc[(2 * q) * kTile + site] = __builtin_bit_cast(U, bq_u2v_b{v.x, v.y});
             sc[(2 * q + 1) * kTile + site] = __builtin_bit_cast(U, bq_u2v_b{v.z, v.w});
         }
