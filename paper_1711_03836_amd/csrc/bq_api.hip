@@ -1184,14 +1184,12 @@ static int block_engine(bq_op op, const Vec& B, int ncol, int nshift, const doub
         f.p[s] = v.all();
     }
     // device state
-    const int nb = (ncol + 3) / 4;
-    const int ngroups = (tiles + kGramTiles - 1) / kGramTiles;
     const size_t ns = (size_t)nshift * ncol;
     DevBuf mats, dd, ii, part, rpart;
     CHK(mats.alloc(ctx, sizeof(double2) * (size_t)kBlockMats * kBlockMax * kBlockMax));
     CHK(dd.alloc(ctx, sizeof(double) * (size_t)ncol * 2));
     CHK(ii.alloc(ctx, sizeof(int) * (BC_COUNT + ncol + 2 * ns)));
-    CHK(part.alloc(ctx, sizeof(double2) * (size_t)ngroups * nb * nb * 16));
+    CHK(part.alloc(ctx, sizeof(double2) * (size_t)block_gram_parts(tiles) * kBlockMax * kBlockMax, CLEAR_NONE));
     CHK(rpart.alloc(ctx, sizeof(double) * (size_t)tiles * ncol));
     BlockState S{};
     S.mats = mats.as<double2>();
@@ -1262,7 +1260,7 @@ static int block_engine(bq_op op, const Vec& B, int ncol, int nshift, const doub
         HIPCHK(launch_convert(PREC_F64, R.all(), PREC_F64, P.all(), n, ncol, nullptr, 0, st));
         for (int s = 0; s < nshift; s++)
             if (s != base) HIPCHK(launch_convert(PREC_F64, R.all(), PREC_F64, f.p[s], n, ncol, nullptr, 0, st));
-        HIPCHK(launch_block_gram(R.all(), R.all(), FieldArg(), 0.0, S, g.Vh, tiles, pt, st));
+        HIPCHK(launch_block_gram(R.all(), R.all(), 0.0, S, g.Vh, tiles, pt, st));
         HIPCHK(launch_block_gram_fin(S, pt, tiles, BM_RR, st));
         HIPCHK(launch_block_step(S, 0, st));
         runs++;
@@ -1273,12 +1271,12 @@ static int block_engine(bq_op op, const Vec& B, int ncol, int nshift, const doub
                 CHK(tv(c, 0, 1, T.all(), P.all(), Q.all(), -kap * kap, nullptr, tiles, tiles));
                 CHK(k1(c, 1, Q.all(), T.all()));
                 CHK(tv(c, 1, 1, T.all(), Q.all(), W.all(), -kap * kap, nullptr, tiles, tiles));
-                HIPCHK(launch_block_gram(P.all(), W.all(), P.all(), S.sigma_b, S, g.Vh, tiles, pt, st));
+                HIPCHK(launch_block_gram(P.all(), W.all(), S.sigma_b, S, g.Vh, tiles, pt, st));
                 HIPCHK(launch_block_gram_fin(S, pt, tiles, BM_PQ, st));
                 HIPCHK(launch_block_step(S, 1, st));
                 if (nshift > 1) HIPCHK(launch_block_shift(S, f, R.all(), units, st));
                 HIPCHK(launch_block_xr(S, f.x[base], P.all(), W.all(), R.all(), units, st));
-                HIPCHK(launch_block_gram(R.all(), R.all(), FieldArg(), 0.0, S, g.Vh, tiles, pt, st));
+                HIPCHK(launch_block_gram(R.all(), R.all(), 0.0, S, g.Vh, tiles, pt, st));
                 HIPCHK(launch_block_gram_fin(S, pt, tiles, BM_RRN, st));
                 HIPCHK(launch_block_step(S, 2, st));
                 HIPCHK(launch_block_p(S, P.all(), R.all(), units, st));

@@ -7,6 +7,8 @@
 // the field updates are column combinations with those matrices.  Fields are FP64 odd-site
 // spinors in the site-tiled layout, so unit t of every column belongs to the same site and
 // spin-colour component and a column combination is a loop over units.
+#include <algorithm>
+
 #include "bq_kernels.h"
 
 namespace bq {
@@ -49,90 +51,74 @@ __device__ __forceinline__ bool on(unsigned mask, int i) { return (mask >> i) & 
 // Gram matrices
 // --------------------------------------------------------------------------
 
-// One wavefront per group of kGramTiles tiles (lane = site of the tile), one 4 x 4 block of
-// (i, j) column pairs per grid row; the 16 sums are reduced over the wave by a fixed butterfly,
-// so the partials depend only on the lattice and the columns.
-__global__ __launch_bounds__(256) void k_block_gram(FieldArg X, FieldArg Y, FieldArg Z, double s, BlockState S,
-                                                    int vh, int tiles, double2* partial)
+// G = X^dag (Y + s Z) for all columns at once on the FP64 matrix cores.  A 16 x 16 x 4 product takes the
+// real (or imaginary) parts of four units of every column as its left and right operands: lane l holds
+// the unit l / 16 of column l mod 16 of both, so each value is loaded once, where 4 x 4 blocks of
+// column pairs in registers read every column once per block of columns (three times for 12).
+// Columns that are not in the block (or do not exist) enter as zeros.  Four products per four units
+// into two accumulators; the four wavefronts of a workgroup meet in LDS and leave one partial per
+// matrix entry, partial[entry][workgroup].  Sums run over units in an order fixed by the lattice.
+// 16^3x32 x 12: 153 us in the mean of both uses before, now P^dag A P 84 and R^dag R 37 (HBM needs 46 and
+// 23, the products, 64 cycles each, 23).
+typedef double d4 __attribute__((ext_vector_type(4)));
+
+// SAME: Y is X (and there is no Z); otherwise Z, if any, is X
+template <bool SAME>
+__global__ __launch_bounds__(256) void k_block_gram(FieldArg X, FieldArg Y, double s, BlockState S, int vh, int tiles,
+                                                    double2* partial)
 {
     if (S.ctrl[BC_STOP]) return;
-    const int lane = threadIdx.x & 63;
-    const int g = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int ngroups = (tiles + kGramTiles - 1) / kGramTiles;
-    if (g >= ngroups) return;  // uniform over the wave
-    const int nb = (S.ncol + 3) / 4;
-    const int i0 = 4 * ((int)blockIdx.y / nb), j0 = 4 * ((int)blockIdx.y % nb);
-    const unsigned mask = (unsigned)S.ctrl[BC_MASK];
-    const double2* x = (const double2*)X.d;
-    const double2* y = (const double2*)Y.d;
-    const double2* z = (const double2*)Z.d;
-    bool xon[4], yon[4];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int col = lane & 15, k = lane >> 4;
+    const bool use = col < S.ncol && on((unsigned)S.ctrl[BC_MASK], col);
+    const double2* x = (const double2*)X.d + (use ? (size_t)col * X.cstride : 0);
+    const double2* y = (const double2*)Y.d + (use ? (size_t)col * Y.cstride : 0);
+    d4 re = {0.0, 0.0, 0.0, 0.0}, im = re;
+    // pieces of 16 units: the four of lane (col, k) are 4 k .. 4 k + 3 of the piece
+    const int npiece = tiles * 12 * 4;
+    const int stride = gridDim.x * 4;
+    for (int p = blockIdx.x * 4 + w; p < npiece; p += stride) {
+        const int u = p * 16 + 4 * k;
+        const int site = u / (12 * 64) * 64 + (u & 63);
+        double2 xv[4], yv[4];
 #pragma unroll
-    for (int a = 0; a < 4; a++) {
-        xon[a] = i0 + a < S.ncol && on(mask, i0 + a);
-        yon[a] = j0 + a < S.ncol && on(mask, j0 + a);
-    }
-    double2 acc[4][4];
+        for (int q = 0; q < 4; q++) {
+            const bool in = use && site + q < vh;
+            xv[q] = in ? x[u + q] : cz();
+            if constexpr (SAME) yv[q] = xv[q];
+            else yv[q] = in ? y[u + q] : cz();
+        }
 #pragma unroll
-    for (int a = 0; a < 4; a++)
-#pragma unroll
-        for (int b = 0; b < 4; b++) acc[a][b] = cz();
-    const int t1 = min(tiles, (g + 1) * kGramTiles);
-    for (int tile = g * kGramTiles; tile < t1; tile++) {
-        const bool site = tile * 64 + lane < vh;
-        const size_t u0 = (size_t)tile * 12 * 64 + lane;
-        for (int c = 0; c < 12; c++) {
-            const size_t u = u0 + (size_t)c * 64;
-            double2 xv[4], yv[4];
-#pragma unroll
-            for (int a = 0; a < 4; a++) {
-                xv[a] = (xon[a] && site) ? x[(size_t)(i0 + a) * X.cstride + u] : cz();
-                double2 v = cz();
-                if (yon[a] && site) {
-                    v = y[(size_t)(j0 + a) * Y.cstride + u];
-                    if (z) {
-                        const double2 w = z[(size_t)(j0 + a) * Z.cstride + u];
-                        v.x = fma(s, w.x, v.x);
-                        v.y = fma(s, w.y, v.y);
-                    }
-                }
-                yv[a] = v;
+        for (int q = 0; q < 4; q++) {
+            if constexpr (!SAME) {
+                yv[q].x = fma(s, xv[q].x, yv[q].x);
+                yv[q].y = fma(s, xv[q].y, yv[q].y);
             }
-#pragma unroll
-            for (int a = 0; a < 4; a++)
-#pragma unroll
-                for (int b = 0; b < 4; b++) cfmac(acc[a][b], xv[a], yv[b]);
+            // conj(x) y = (xr yr + xi yi) + i (xr yi - xi yr)
+            re = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[q].x, yv[q].x, re, 0, 0, 0);
+            im = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[q].x, yv[q].y, im, 0, 0, 0);
+            re = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[q].y, yv[q].y, re, 0, 0, 0);
+            im = __builtin_amdgcn_mfma_f64_16x16x4f64(-xv[q].y, yv[q].x, im, 0, 0, 0);
         }
     }
+    // element r of lane l is entry (l / 16 + 4 r, l mod 16)
+    __shared__ double2 sum[4][LD * LD];
 #pragma unroll
-    for (int a = 0; a < 4; a++)
-#pragma unroll
-        for (int b = 0; b < 4; b++)
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                acc[a][b].x += __shfl_xor(acc[a][b].x, o);
-                acc[a][b].y += __shfl_xor(acc[a][b].y, o);
-            }
-    if (lane == 0) {
-        double2* out = partial + ((size_t)g * nb * nb + blockIdx.y) * 16;
-#pragma unroll
-        for (int a = 0; a < 4; a++)
-#pragma unroll
-            for (int b = 0; b < 4; b++) out[a * 4 + b] = acc[a][b];
-    }
+    for (int r = 0; r < 4; r++) sum[w][(k + 4 * r) * LD + col] = make_double2(re[r], im[r]);
+    __syncthreads();
+    const int e = threadIdx.x;
+    partial[(size_t)e * gridDim.x + blockIdx.x] = cadd(cadd(sum[0][e], sum[1][e]), cadd(sum[2][e], sum[3][e]));
 }
 
-// One workgroup per matrix entry (i, j): the group partials summed in a fixed order.
-__global__ __launch_bounds__(256) void k_block_gram_fin(BlockState S, const double2* partial, int tiles, int slot)
+// One workgroup per matrix entry (i, j): the partials summed in a fixed order.
+__global__ __launch_bounds__(256) void k_block_gram_fin(BlockState S, const double2* partial, int nparts, int slot)
 {
     if (S.ctrl[BC_STOP]) return;
     const int N = S.ncol;
     const int i = blockIdx.x / N, j = blockIdx.x % N;
-    const int nb = (N + 3) / 4;
-    const int blk = (i / 4) * nb + j / 4, e = (i % 4) * 4 + j % 4;
-    const int ngroups = (tiles + kGramTiles - 1) / kGramTiles;
+    const double2* p = partial + (size_t)(i * LD + j) * nparts;
     double2 a = cz();
-    for (int g = threadIdx.x; g < ngroups; g += 256) a = cadd(a, partial[((size_t)g * nb * nb + blk) * 16 + e]);
+    for (int g = threadIdx.x; g < nparts; g += 256) a = cadd(a, p[g]);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         a.x += __shfl_xor(a.x, o);
@@ -565,7 +551,22 @@ __global__ __launch_bounds__(64) void k_block_step(BlockState S, int phase)
 
 // --------------------------------------------------------------------------
 // column combinations (one thread per unit = site and spin-colour component)
+//
+// The step matrices are the same for every thread: read through the constant address space they come
+// as scalar operands.  (As vector loads, 288 per thread at 12 columns, they were what these kernels
+// waited for: 16^3x32 x 12, x and r 270 -> 134 us, p 138 -> 71; HBM needs 137 and 69.)  Their rows
+// and columns outside the block are zero, so the sums run over all NM columns without tests.
 // --------------------------------------------------------------------------
+typedef const __attribute__((address_space(4))) double* ConstMat;
+
+__device__ __forceinline__ ConstMat const_mat(const double2* m) { return (ConstMat)(uintptr_t)m; }
+// v += p[.] M[.][m]
+template <int NM>
+__device__ __forceinline__ void combine(double2& v, const double2 (&p)[NM], ConstMat M, int m)
+{
+#pragma unroll
+    for (int i = 0; i < NM; i++) cfma(v, p[i], make_double2(M[2 * (i * LD + m)], M[2 * (i * LD + m) + 1]));
+}
 
 template <int NM>
 __global__ __launch_bounds__(256) void k_block_xr(BlockState S, FieldArg X, FieldArg P, FieldArg W, FieldArg R,
@@ -574,8 +575,8 @@ __global__ __launch_bounds__(256) void k_block_xr(BlockState S, FieldArg X, Fiel
     if (S.ctrl[BC_STOP]) return;
     const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= units) return;
-    const unsigned mask = (unsigned)S.ctrl[BC_MASK];
-    const double2* A = mat(S, BM_ALPHA);
+    const unsigned mask = __builtin_amdgcn_readfirstlane(S.ctrl[BC_MASK]);
+    const ConstMat A = const_mat(mat(S, BM_ALPHA));
     const double2* pp = (const double2*)P.d;
     const double2* wp = (const double2*)W.d;
     double2* xp = (double2*)X.d;
@@ -587,25 +588,21 @@ __global__ __launch_bounds__(256) void k_block_xr(BlockState S, FieldArg X, Fiel
         w[i] = cz();
         if (i < S.ncol && on(mask, i)) {
             p[i] = pp[(size_t)i * P.cstride + t];
-            const double2 v = wp[(size_t)i * W.cstride + t];
+            const double2 v = ld_stream(&wp[(size_t)i * W.cstride + t]);
             w[i] = make_double2(fma(S.sigma_b, p[i].x, v.x), fma(S.sigma_b, p[i].y, v.y));
         }
     }
 #pragma unroll
     for (int m = 0; m < NM; m++) {
         if (m >= S.ncol || !on(mask, m)) continue;
-        double2 dx = cz(), dr = cz();
-#pragma unroll
-        for (int i = 0; i < NM; i++) {
-            if (i >= S.ncol || !on(mask, i)) continue;
-            const double2 a = A[i * LD + m];
-            cfma(dx, p[i], a);
-            cfma(dr, w[i], a);
-        }
         double2& xr = xp[(size_t)m * X.cstride + t];
         double2& rr = rp[(size_t)m * R.cstride + t];
-        xr = cadd(xr, dx);
-        rr = csub(rr, dr);
+        const double2 x0 = ld_stream(&xr), r0 = rr;
+        double2 dx = cz(), dr = cz();
+        combine(dx, p, A, m);
+        combine(dr, w, A, m);
+        st_stream(&xr, cadd(x0, dx));
+        rr = csub(r0, dr);
     }
 }
 
@@ -615,8 +612,8 @@ __global__ __launch_bounds__(256) void k_block_p(BlockState S, FieldArg P, Field
     if (S.ctrl[BC_STOP]) return;
     const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= units) return;
-    const unsigned mask = (unsigned)S.ctrl[BC_MASK];
-    const double2* B = mat(S, BM_BETA);
+    const unsigned mask = __builtin_amdgcn_readfirstlane(S.ctrl[BC_MASK]);
+    const ConstMat B = const_mat(mat(S, BM_BETA));
     double2* pp = (double2*)P.d;
     const double2* rp = (const double2*)R.d;
     double2 p[NM];
@@ -626,9 +623,7 @@ __global__ __launch_bounds__(256) void k_block_p(BlockState S, FieldArg P, Field
     for (int m = 0; m < NM; m++) {
         if (m >= S.ncol || !on(mask, m)) continue;
         double2 v = rp[(size_t)m * R.cstride + t];
-#pragma unroll
-        for (int i = 0; i < NM; i++)
-            if (i < S.ncol && on(mask, i)) cfma(v, p[i], B[i * LD + m]);
+        combine(v, p, B, m);
         pp[(size_t)m * P.cstride + t] = v;
     }
 }
@@ -640,11 +635,11 @@ __global__ __launch_bounds__(256) void k_block_shift(BlockState S, BlockFields f
     if (S.ctrl[BC_STOP] || s == S.base || S.ctrl[BC_FROZEN + s]) return;
     const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= units) return;
-    const unsigned mask = (unsigned)S.ctrl[BC_MASK];
+    const unsigned mask = __builtin_amdgcn_readfirstlane(S.ctrl[BC_MASK]);
     const double2* sm = mat(S, BM_SHIFT + 6 * s);
-    const double2* Xi = sm + 3 * LD * LD;
-    const double2* As = sm + 4 * LD * LD;
-    const double2* Bs = sm + 5 * LD * LD;
+    const ConstMat Xi = const_mat(sm + 3 * LD * LD);
+    const ConstMat As = const_mat(sm + 4 * LD * LD);
+    const ConstMat Bs = const_mat(sm + 5 * LD * LD);
     const double2* rp = (const double2*)R.d;
     double2* pp = (double2*)f.p[s].d;
     double2* xp = (double2*)f.x[s].d;
@@ -663,9 +658,9 @@ __global__ __launch_bounds__(256) void k_block_shift(BlockState S, BlockFields f
         double2 v = cz();
 #pragma unroll
         for (int i = 0; i < NM; i++) {
-            if (i >= S.ncol || !on(mask, i)) continue;
-            cfma(v, r[i], Xi[i * LD + m]);
-            cfma(v, p[i], Bs[i * LD + m]);
+            const int e = 2 * (i * LD + m);
+            cfma(v, r[i], make_double2(Xi[e], Xi[e + 1]));
+            cfma(v, p[i], make_double2(Bs[e], Bs[e + 1]));
         }
         pn[m] = v;
         pp[(size_t)m * pc + t] = v;
@@ -674,9 +669,7 @@ __global__ __launch_bounds__(256) void k_block_shift(BlockState S, BlockFields f
     for (int m = 0; m < NM; m++) {
         if (m >= S.ncol || !on(mask, m)) continue;
         double2 v = xp[(size_t)m * xc + t];
-#pragma unroll
-        for (int i = 0; i < NM; i++)
-            if (i < S.ncol && on(mask, i)) cfma(v, pn[i], As[i * LD + m]);
+        combine(v, pn, As, m);
         xp[(size_t)m * xc + t] = v;
     }
 }
@@ -685,21 +678,26 @@ inline dim3 unit_grid(size_t units, int y = 1) { return dim3((unsigned)((units +
 
 }  // namespace
 
-hipError_t launch_block_gram(FieldArg X, FieldArg Y, FieldArg Z, double s, const BlockState& S, int vh, int tiles,
-                             double2* partial, hipStream_t st)
+// workgroups of a Gram launch: two to four pieces of 16 units per wavefront on small lattices, at most
+// eight workgroups per CU
+int block_gram_parts(int tiles) { return std::min(2048, tiles); }
+
+hipError_t launch_block_gram(FieldArg X, FieldArg Y, double s, const BlockState& S, int vh, int tiles, double2* partial,
+                             hipStream_t st)
 {
     if (S.ncol < 1 || S.ncol > kBlockMax) return hipErrorInvalidValue;
-    const int ngroups = (tiles + kGramTiles - 1) / kGramTiles;
-    const int nb = (S.ncol + 3) / 4;
-    hipLaunchKernelGGL(k_block_gram, dim3((ngroups + 3) / 4, nb * nb), dim3(256), 0, st, X, Y, Z, s, S, vh, tiles,
-                       partial);
+    const dim3 grid(block_gram_parts(tiles));
+    if (X.d == Y.d)
+        hipLaunchKernelGGL(k_block_gram<true>, grid, dim3(256), 0, st, X, Y, 0.0, S, vh, tiles, partial);
+    else
+        hipLaunchKernelGGL(k_block_gram<false>, grid, dim3(256), 0, st, X, Y, s, S, vh, tiles, partial);
     return hipGetLastError();
 }
 
 hipError_t launch_block_gram_fin(const BlockState& S, const double2* partial, int tiles, int slot, hipStream_t st)
 {
     if (S.ncol < 1 || S.ncol > kBlockMax) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_block_gram_fin, dim3(S.ncol * S.ncol), dim3(256), 0, st, S, partial, tiles, slot);
+    hipLaunchKernelGGL(k_block_gram_fin, dim3(S.ncol * S.ncol), dim3(256), 0, st, S, partial, block_gram_parts(tiles), slot);
     return hipGetLastError();
 }
 

@@ -165,7 +165,6 @@ hipError_t launch_ms_update2(const MsState& s, const MsFields& f, int n, int nco
 // round trip per iteration
 // ---------------------------------------------------------------------------
 constexpr int kBlockMax = 16;   // columns of a block solve
-constexpr int kGramTiles = 8;   // 64-site tiles one wavefront sums before it writes its partial
 // control words
 enum { BC_K = 0, BC_STOP = 1, BC_BREAK = 2, BC_NA = 3, BC_MASK = 4, BC_IDX = 5,
        BC_FROZEN = BC_IDX + kBlockMax, BC_COUNT = BC_FROZEN + kMaxShifts };
@@ -197,10 +196,11 @@ struct BlockFields {
     FieldArg x[kMaxShifts];        // solutions (x[base] is the base iterate)
     FieldArg p[kMaxShifts];        // directions (p[base] is the base direction)
 };
-// partial Gram sums of <X_i, Y_j + s Z_j> over the active columns (Z may be null); one set of
-// kBlockMax^2 complex numbers per group of kGramTiles tiles
-hipError_t launch_block_gram(FieldArg X, FieldArg Y, FieldArg Z, double s, const BlockState& S, int vh, int tiles,
-                             double2* partial, hipStream_t st);
+// partial Gram sums of <X_i, Y_j + s X_j> over the active columns (s = 0 where Y is X): per workgroup
+// (block_gram_parts of them) one complex number per entry of a kBlockMax^2 matrix
+int block_gram_parts(int tiles);
+hipError_t launch_block_gram(FieldArg X, FieldArg Y, double s, const BlockState& S, int vh, int tiles, double2* partial,
+                             hipStream_t st);
 // fixed-order sum of the partials into matrix slot `slot` (full)
 hipError_t launch_block_gram_fin(const BlockState& S, const double2* partial, int tiles, int slot, hipStream_t st);
 // 0: start of a run (active list from colstat and the Gram matrix in BM_RR, dependent columns
