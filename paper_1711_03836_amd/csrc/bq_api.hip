@@ -551,6 +551,10 @@ static Tune get_tune(bq_context ctx, int prec, int ncol)
     return it != ctx->tune.end() ? it->second : default_tune(prec, ncol);
 }
 
+// One round of the hop-split kernel's workgroups on 256 CUs: two FP64 or four FP32/FP16 per CU by their
+// registers and LDS (one per tile and column).
+static bool split_fits(const Geom& g, int prec, int nact) { return (long)g.ntiles * nact <= (prec == PREC_F64 ? 512 : 1024); }
+
 // The kernel of a launch whose configuration nobody chose, by tiles and columns (nact: the columns
 // that are worked on).  Times are of Mhat (K1 + K2, 18-real links; FP16 12) in us on one MI355X.
 static void pick_kernel(HopLaunch& L, const Geom& g, int nact, int& order)
@@ -559,12 +563,11 @@ static void pick_kernel(HopLaunch& L, const Geom& g, int nact, int& order)
     const long items = (long)g.ntiles * nact;
     const bool f64 = L.prec == PREC_F64, f16 = L.prec == PREC_F16;
     L.march = L.lds = 0;
-    // One round of the hop-split kernel's workgroups on 256 CUs (two FP64 or four FP32/FP16 per CU
-    // by their registers and LDS).  Within it a launch is one chain of memory latencies and the
-    // split shortens it (8^4: FP64 20.7 -> 10.6, FP32 x 8 43 -> 10.3; 12^3x24 FP32 x 3 20.7 -> 19.2);
+    // Within one round of its workgroups a launch is one chain of memory latencies and the hop split
+    // shortens it (8^4: FP64 20.7 -> 10.6, FP32 x 8 43 -> 10.3; 12^3x24 FP32 x 3 20.7 -> 19.2);
     // beyond it the kernels that use fewer waves per site win (12^3x24 FP64 x 2 31.1 against 28.7,
     // FP32 x 4 25.3 against 24.8)
-    if (items <= (f64 ? 512 : 1024)) {
+    if (split_fits(g, L.prec, nact)) {
         L.split = 1;
         L.R = 1;
         return;
@@ -660,6 +663,8 @@ struct OpCall {
     hipStream_t st;
     const ColTable* ct = nullptr;
     int nact = 0;  // columns in use, where they are fewer than ncol (0: all)
+    const double* pap = nullptr;     // tvr takes alpha from these partials and cg's states itself
+    const CgScalars* cg = nullptr;   // (hop-split launches only)
 };
 
 // switch a launch to per-column operators: clover per column (parity `par`, inverse or not), f by mode
@@ -736,6 +741,13 @@ static int tvr(const OpCall& c, int dag, int parity, FieldArg in, FieldArg v, Fi
     L.pstride = pstride;
     L.status = c.status;
     L.statmask = c.statmask;
+    if (c.pap) {
+        L.pap = c.pap;
+        L.cg_rho = c.cg->rho;
+        L.cg_alpha = c.cg->alpha;
+        L.cg_pAp = c.cg->pAp;
+        L.cg_status = c.cg->status;
+    }
     apply_cols(c, L, parity, false, fk);
     return run_hop(L, c.st);
 }
@@ -819,7 +831,9 @@ struct Workspace {
     // scalars and partials
     DevBuf scal, ints, part;
     CgScalars cs{};
+    CgScalars cs2{};             // the states between the two iterations of a pair (cg_pair)
     double* partial = nullptr;
+    double* partial2 = nullptr;  // a second set, for partials written while the first is read
     double* dtmp = nullptr;  // ncol * 4 doubles for sums
     int hw = 0, pstride = 0;
     int* h_status = nullptr;  // pinned
@@ -867,8 +881,9 @@ static int ws_init(bq_context ctx, const Geom& g, int ncol, int prec, int full, 
     w->pstride = w->hw * nh;
     CHK(w->part.alloc(ctx, sizeof(double) * (size_t)w->pstride * ncol * 2));
     w->partial = w->part.as<double>();
-    CHK(w->scal.alloc(ctx, sizeof(double) * (size_t)ncol * 10));
-    CHK(w->ints.alloc(ctx, sizeof(int) * (size_t)ncol * 4));
+    w->partial2 = w->partial + (size_t)w->pstride * ncol;
+    CHK(w->scal.alloc(ctx, sizeof(double) * (size_t)ncol * 12));
+    CHK(w->ints.alloc(ctx, sizeof(int) * (size_t)ncol * 6));
     double* sc = w->scal.as<double>();
     int* i = w->ints.as<int>();
     w->cs.rho = sc;
@@ -882,6 +897,11 @@ static int ws_init(bq_context ctx, const Geom& g, int ncol, int prec, int full, 
     w->cs.iters = i + ncol;
     w->cs.restart = i + 2 * ncol;
     w->cs.nrel = i + 3 * ncol;
+    w->cs2 = w->cs;
+    w->cs2.rho = sc + 10 * ncol;
+    w->cs2.rmax2 = sc + 11 * ncol;
+    w->cs2.status = i + 4 * ncol;
+    w->cs2.iters = i + 5 * ncol;
     HIPCHK(hipHostMalloc((void**)&w->h_status, sizeof(int) * ncol * 4));
     return BQ_OK;
 }
@@ -931,7 +951,7 @@ static double iter_col_bytes(bq_op op, int prec, int full)
     return stencil + update;
 }
 static double iter_shared_bytes(bq_op op, int prec) { return 4 * stencil_shared(op, prec); }
-static const int kIterLaunches = 7;
+static const int kIterLaunches = 7, kFusedLaunches = 5;
 
 // reliable pass per selected column: x += x_inner, FP64 r = b' - A x
 static double rel_col_bytes(bq_op op, int prec, int full)
@@ -972,6 +992,45 @@ static int cg_iteration(bq_op op, Workspace* w, int prec, hipStream_t st)
     return BQ_OK;
 }
 
+// The same iteration for launches that use the hop-split kernel, in five launches instead of seven: the
+// second adjoint stencil takes alpha from the first one's partials, the vector update beta from the
+// second one's, and the states after it go to a second set (nxt), so that no launch reads what another
+// of its workgroups writes.
+static int cg_iteration_fused(bq_op op, Workspace* w, int prec, const CgScalars& cur, const CgScalars& nxt, hipStream_t st)
+{
+    bq_context ctx = op->gauge->ctx;
+    OpCall c{op, prec, get_tune(ctx, prec, w->ncol), w->ncol, cur.status, kIterMask, st};
+    c.ct = w->ct;
+    c.nact = w->nact;
+    CHK(op_fwd(c, 0, w->ps, w->qs, w->ts, w->partial, w->hw));
+    c.pap = w->partial;
+    c.cg = &cur;
+    CHK(op_dag_r(c, 0, w->qs, w->ts, w->rs, w->rs, nullptr, w->partial2, w->hw));
+    HIPCHK(launch_cg_update_beta(w->xs.prec, w->xs.all(), w->ps.prec, w->ps.all(), w->rs.prec, w->rs.all(), w->xs.sites(),
+                                 w->ncol, cur, nxt, w->partial2, w->pstride, st));
+    return BQ_OK;
+}
+
+// whether the workspace's iterations run fused
+static bool cg_fused(bq_op op, const Workspace* w, int prec)
+{
+    return !w->full && w->hw <= kFusedParts && !get_tune(op->gauge->ctx, prec, w->ncol).chosen &&
+           split_fits(op->gauge->g, prec, w->nact > 0 ? w->nact : w->ncol);
+}
+
+// k CG iterations, in pairs of fused ones where they apply (a pair ends in the first set of states)
+static int cg_iterations(bq_op op, Workspace* w, int prec, int k, hipStream_t st)
+{
+    int i = 0;
+    if (cg_fused(op, w, prec))
+        for (w->cs2.delta2 = w->cs.delta2; i + 1 < k; i += 2) {
+            CHK(cg_iteration_fused(op, w, prec, w->cs, w->cs2, st));
+            CHK(cg_iteration_fused(op, w, prec, w->cs2, w->cs, st));
+        }
+    for (; i < k; i++) CHK(cg_iteration(op, w, prec, st));
+    return BQ_OK;
+}
+
 // FP64 true residual r = b' - A x for the columns selected by statmask (status == nullptr: all),
 // partials of |r|^2 left in w->partial
 static int true_residual(bq_op op, Workspace* w, const int* status, int statmask, hipStream_t st)
@@ -999,7 +1058,7 @@ static int reliable_pass(bq_op op, Workspace* w, int prec, hipStream_t st)
 
 static int chunk(bq_op op, Workspace* w, int prec, int k, hipStream_t st)
 {
-    for (int i = 0; i < k; i++) CHK(cg_iteration(op, w, prec, st));
+    CHK(cg_iterations(op, w, prec, k, st));
     return reliable_pass(op, w, prec, st);
 }
 
@@ -1069,6 +1128,7 @@ static int cg_solve(bq_op op, Workspace* w, const bq_solve_params& prm, hipStrea
     const double rcol = rel_col_bytes(op, prec, w->full), rshr = iter_shared_bytes(op, PREC_F64);
     const double scol = restart_col_bytes(op, prec, w->full);
     const int rel_launches = (prec != PREC_F64) + 4 + 2;
+    const int fewer = cg_fused(op, w, prec) ? k / 2 * 2 * (kIterLaunches - kFusedLaunches) : 0;
     const auto read_states = [&]() -> int {
         HIPCHK(hipMemcpyAsync(w->h_status, w->cs.status, sizeof(int) * 4 * ncol, hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
@@ -1083,7 +1143,7 @@ static int cg_solve(bq_op op, Workspace* w, const bq_solve_params& prm, hipStrea
             // The reliable pass is launched only after a chunk in which some column stopped for one
             // (one chunk in five on 16^3x32): its seven launches find nothing to do otherwise, but
             // cost 3-5 us each on a small lattice and 22 us for each FP64 stencil on 12 columns of 24^3x48.
-            for (int i = 0; i < k; i++) CHK(cg_iteration(op, w, prec, st));
+            CHK(cg_iterations(op, w, prec, k, st));
             CHK(read_states());
             pass = false;
             for (int c = 0; c < ncol; c++) pass |= (kRelMask >> w->h_status[c]) & 1;
@@ -1093,7 +1153,7 @@ static int cg_solve(bq_op op, Workspace* w, const bq_solve_params& prm, hipStrea
             }
         }
         done_iters += k;
-        acct.launches += (long long)k * kIterLaunches + (pass ? rel_launches : 0);
+        acct.launches += (long long)k * kIterLaunches - fewer + (pass ? rel_launches : 0);
         acct.chunks++;
         // Within a chunk a column is active for a prefix of the iterations (it can only stop
         // there, and restarts in the chunk's reliable pass), so the counters give exact counts.

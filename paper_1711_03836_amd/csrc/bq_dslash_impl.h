@@ -400,6 +400,12 @@ struct Args {
     int percol;
     const typename P::unit* cclov[kMaxCols];
     typename P::real cf[kMaxCols];
+    // hop-split EPI_TVR (see HopLaunch)
+    const double* pap;
+    const double* cg_rho;
+    double* cg_alpha;
+    double* cg_pAp;
+    int* cg_status;
 };
 
 template <bool PC, class P, class PR>
@@ -1187,7 +1193,7 @@ constexpr int kSplitWaves = 8;
 template <class P>
 constexpr int split_lds_bytes()
 {
-    return kSplitWaves * 6 * kTile * (int)sizeof(typename LinkLds<P>::C) + kSplitWaves * kTile * 4 + kTile * 8;
+    return kSplitWaves * 6 * kTile * (int)sizeof(typename LinkLds<P>::C) + kSplitWaves * kTile * 4 + kTile * 8 + 4 * 8;
 }
 
 // y = U (1 + S gamma_mu) psi of half hop H at every site of the tile, into LDS
@@ -1277,13 +1283,24 @@ __global__ __launch_bounds__(kSplitWaves * kTile) void k_hop_split(const Args<P,
     int lt, c;
     item_of(A.g, lb, A.nblk, A.nch, lt, c);
     c = __builtin_amdgcn_readfirstlane(c);
-    if (!col_selected(A.status, A.statmask, c)) return;  // uniform over the workgroup
+    const bool own_alpha = EPI == EPI_TVR && A.pap != nullptr;  // uniform over the launch
+    const bool first = lt == 0 && threadIdx.x == 0;             // writes the column's state
+    if (!col_selected(A.status, A.statmask, c)) {  // uniform over the workgroup
+        if (own_alpha && first && A.cg_status[c] == COL_JUST_STOPPED) A.cg_status[c] = COL_STOPPED;
+        return;
+    }
+    double pap = 0.0;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> kTileLog);
     const int lane = threadIdx.x & (kTile - 1);
     const int j = tile_at(A.g, lt) * kTile + lane;  // lt < ntiles
     const bool act = j < A.g.Vh;
     const Site s = site_of(A.g, A.parity, act ? j : 0);
     SplitIn<P, PR, EPI> in;
+    if (own_alpha && w >= 2 && w < 6) {
+        // the four wavefronts that have no epilogue sum the column's partials as block_sum does
+        const double* part = A.pap + (size_t)c * A.pstride;
+        for (int i = threadIdx.x - 2 * kTile; i < A.nwaves; i += 4 * kTile) pap += part[i];
+    }
     switch (w) {
     case 0: split_hop<P, PR, DAG, RECON, 0, LA>(A, s, act, c, lane, yb, kb); break;
     case 1: split_hop<P, PR, DAG, RECON, 1, LA>(A, s, act, c, lane, yb, kb); break;
@@ -1296,7 +1313,27 @@ __global__ __launch_bounds__(kSplitWaves * kTile) void k_hop_split(const Args<P,
     }
     if (act && w == 0) split_load<P, PR, EPI, PC, LA, 0>(A, j, c, in);
     if (act && w == 1) split_load<P, PR, EPI, PC, LA, 1>(A, j, c, in);
+    double* pw = nb + kTile;
+    if (own_alpha && w >= 2 && w < 6) {
+        pap = wave_sum(pap);
+        if (lane == 0) pw[w - 2] = pap;
+    }
     __syncthreads();
+    double alpha = 1.0;
+    if constexpr (EPI == EPI_TVR) {
+        if (own_alpha) {
+            pap = (pw[0] + pw[1]) + (pw[2] + pw[3]);
+            const bool ok = pap > 0.0 && isfinite(pap);
+            alpha = ok ? A.cg_rho[c] / pap : 0.0;
+            if (first) {
+                A.cg_pAp[c] = pap;
+                A.cg_alpha[c] = alpha;
+                if (!ok) A.cg_status[c] = COL_FAILED;  // the others' residuals stay as they are (alpha 0)
+            }
+        } else if (A.alpha) {
+            alpha = A.alpha[c];
+        }
+    }
     cx<T> o[6];
     double term[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, sum = 0.0;  // |out|^2 of this block, term by term and summed
     if (w < 2 && act) {
@@ -1329,7 +1366,7 @@ __global__ __launch_bounds__(kSplitWaves * kTile) void k_hop_split(const Args<P,
                 term[k] = (double)o[k].re * o[k].re + (double)o[k].im * o[k].im;
             }
         } else {
-            const TR al = A.alpha ? (TR)A.alpha[c] : TR(1);
+            const TR al = (TR)alpha;
             clover_mul(in.cb, in.v, o);
             typename PR::unit* rb = A.rout.d + c * A.rout.cstride;
 #pragma unroll
@@ -1430,6 +1467,11 @@ hipError_t launch_t(const HopLaunch& L, hipStream_t st)
     A.eb_bc = (T)(L.eb * L.tbc);
     A.f = (T)L.f;
     A.a = (T)L.a;
+    A.pap = L.pap;
+    A.cg_rho = L.cg_rho;
+    A.cg_alpha = L.cg_alpha;
+    A.cg_pAp = L.cg_pAp;
+    A.cg_status = L.cg_status;
     A.percol = L.percol;
     for (int c = 0; c < kMaxCols; c++) {
         A.cclov[c] = (const typename P::unit*)L.cclov[c];

@@ -60,6 +60,13 @@ struct HopLaunch {
     int percol = 0;                    // 1: column c uses cclov[c] and cf[c] instead of clov and f
     const void* cclov[kMaxCols] = {};
     double cf[kMaxCols] = {};
+    // hop-split EPI_TVR only: alpha = cg_rho / (the sum of column c's nwaves partials at pap + c * pstride) is
+    // taken by the kernel itself, which also writes alpha, pAp and the states k_fin_alpha would
+    const double* pap = nullptr;
+    const double* cg_rho = nullptr;
+    double* cg_alpha = nullptr;
+    double* cg_pAp = nullptr;
+    int* cg_status = nullptr;
 };
 
 hipError_t launch_hop(const HopLaunch& L, hipStream_t st);
@@ -258,6 +265,13 @@ struct CgScalars {
     int* restart;
     int* nrel;        // reliable updates per column
 };
+// launch_fin_beta and launch_cg_update in one, for up to kFusedParts partials per column: every workgroup
+// takes its column's sum itself; the states after the iteration go to `next` (its rho, rmax2, status
+// and iters; for every column)
+constexpr int kFusedParts = 1024;
+hipError_t launch_cg_update_beta(int xprec, FieldArg x, int pprec, FieldArg p, int rprec, FieldArg r, int n, int ncol,
+                                 const CgScalars& cur, const CgScalars& next, const double* partial, int nwaves,
+                                 hipStream_t st);
 hipError_t launch_fin_alpha(const CgScalars& s, const double* partial, int nwaves, int ncol, hipStream_t st);
 hipError_t launch_fin_beta(const CgScalars& s, const double* partial, int nwaves, int ncol, hipStream_t st);
 hipError_t launch_fin_reliable(const CgScalars& s, const double* partial, int nwaves, int ncol, hipStream_t st);

@@ -57,6 +57,8 @@ def test_solves_are_bitwise_the_plain_kernels(bq, dims, n):
     b, x = (bq.Field(ctx, dims, bq.BQ_FULL, bq.BQ_F64, n) for _ in range(2))
     b.put(inputs.gaussian_spinor(dims, n, seed=74))
     runs = [dict(inner_prec=p, system=s) for p in (0, 1, 2) for s in (bq.BQ_SYS_M,)]
+    runs += [dict(inner_prec=1, system=bq.BQ_SYS_M, **kw) for kw in (dict(chunk=1), dict(chunk=3), dict(use_graph=True))]
+    runs += [dict(inner_prec=1, system=bq.BQ_SYS_M, maxiter=7, raise_on_error=False)]
     runs += [dict(inner_prec=0, system=bq.BQ_SYS_FULL_NORMAL),
              dict(inner_prec=1, system=bq.BQ_SYS_M, solver=bq.BQ_SOLVER_BICGSTAB)]
     got = []
