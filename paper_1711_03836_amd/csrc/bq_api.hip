@@ -664,7 +664,7 @@ struct OpCall {
     const ColTable* ct = nullptr;
     int nact = 0;  // columns in use, where they are fewer than ncol (0: all)
     const double* pap = nullptr;     // tvr takes alpha from these partials and cg's states itself
-    const CgScalars* cg = nullptr;   // (hop-split launches only)
+    const CgScalars* cg = nullptr;   // (not in marching or lane-exchange launches)
 };
 
 // switch a launch to per-column operators: clover per column (parity `par`, inverse or not), f by mode
@@ -992,7 +992,7 @@ static int cg_iteration(bq_op op, Workspace* w, int prec, hipStream_t st)
     return BQ_OK;
 }
 
-// The same iteration for launches that use the hop-split kernel, in five launches instead of seven: the
+// The same iteration on small lattices, in five launches instead of seven: the
 // second adjoint stencil takes alpha from the first one's partials, the vector update beta from the
 // second one's, and the states after it go to a second set (nxt), so that no launch reads what another
 // of its workgroups writes.
@@ -1014,8 +1014,8 @@ static int cg_iteration_fused(bq_op op, Workspace* w, int prec, const CgScalars&
 // whether the workspace's iterations run fused
 static bool cg_fused(bq_op op, const Workspace* w, int prec)
 {
-    return !w->full && w->hw <= kFusedParts && !get_tune(op->gauge->ctx, prec, w->ncol).chosen &&
-           split_fits(op->gauge->g, prec, w->nact > 0 ? w->nact : w->ncol);
+    const Tune t = get_tune(op->gauge->ctx, prec, w->ncol);
+    return !w->full && w->hw <= kFusedParts && t.march == 0 && t.lds < 2;
 }
 
 // k CG iterations, in pairs of fused ones where they apply (a pair ends in the first set of states)

@@ -400,7 +400,7 @@ struct Args {
     int percol;
     const typename P::unit* cclov[kMaxCols];
     typename P::real cf[kMaxCols];
-    // hop-split EPI_TVR (see HopLaunch)
+    // EPI_TVR (see HopLaunch)
     const double* pap;
     const double* cg_rho;
     double* cg_alpha;
@@ -545,6 +545,41 @@ __device__ __forceinline__ void hop_all(const Args<P, PR>& A, const Site& s, con
     hh_step<P, PR, R, DAG, RECON, 7, PF, LA>(A, s, act, c0, d, acc);
 }
 
+// The scalars of a CG step whose stencil takes alpha itself (A.pap): every wavefront sums its column's
+// partials, in the order of block_sum (256 threads of a workgroup, here in four turns), so all get
+// the same alpha.
+__device__ __forceinline__ double wave_partials(const double* __restrict__ part, int n, int lane)
+{
+    double s[4];
+#pragma unroll
+    for (int v = 0; v < 4; v++) {
+        s[v] = 0.0;
+        for (int i = v * kTile + lane; i < n; i += 4 * kTile) s[v] += part[i];
+    }
+#pragma unroll
+    for (int v = 0; v < 4; v++) s[v] = wave_sum(s[v]);
+    return (s[0] + s[1]) + (s[2] + s[3]);
+}
+
+template <class P, class PR>
+__device__ __forceinline__ double cg_alpha_of(const Args<P, PR>& A, int c, double pap, bool first)
+{
+    const bool ok = pap > 0.0 && isfinite(pap);
+    const double alpha = ok ? A.cg_rho[c] / pap : 0.0;
+    if (first) {
+        A.cg_pAp[c] = pap;
+        A.cg_alpha[c] = alpha;
+        if (!ok) A.cg_status[c] = COL_FAILED;  // the others' residuals stay as they are (alpha 0)
+    }
+    return alpha;
+}
+// a column that stopped in the last iteration has taken its last update of x
+template <class P, class PR>
+__device__ __forceinline__ void cg_mark_stopped(const Args<P, PR>& A, int c)
+{
+    if (c < A.ncol && A.cg_status[c] == COL_JUST_STOPPED) A.cg_status[c] = COL_STOPPED;
+}
+
 // Epilogue of one tile for R columns: the linear combination and clover factor the caller
 // asked for (EPI), the store, and for EPI_TV / EPI_TVR the per-wave |.|^2 partials.  Lanes with
 // no active column pass nrm = 0 to the wave reduction.
@@ -578,6 +613,25 @@ __device__ __forceinline__ void epilogue(const Args<P, PR>& A, int j, const bool
     double nrm[R];
 #pragma unroll
     for (int r = 0; r < R; r++) nrm[r] = 0.0;
+    double alpha[R];
+    if constexpr (EPI == EPI_TVR) {
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const int c = c0 + r;
+            alpha[r] = 1.0;
+            if (c >= A.ncol) continue;
+            if (A.pap == nullptr) {
+                if (A.alpha) alpha[r] = A.alpha[c];
+                continue;
+            }
+            const int lane = threadIdx.x & (kTile - 1);
+            const bool first = j == 0;  // lane 0 of tile 0
+            if (col_selected(A.status, A.statmask, c))
+                alpha[r] = cg_alpha_of(A, c, wave_partials(A.pap + (size_t)c * A.pstride, A.nwaves, lane), first);
+            else if (first)
+                cg_mark_stopped(A, c);
+        }
+    }
     if (any) {
     if constexpr (EPI == EPI_HOP || EPI == EPI_TINV) {
         // w = a*v + f*hop
@@ -656,7 +710,7 @@ __device__ __forceinline__ void epilogue(const Args<P, PR>& A, int j, const bool
                 const int c = c0 + r;
                 if constexpr (PC) load_clover_block<P, CA>(A.cclov[c], j, blk, cb);
                 const T f = colf<PC>(A, c);
-                const TR al = A.alpha ? (TR)A.alpha[c] : TR(1);
+                const TR al = (TR)alpha[r];
                 cx<T> x[6], y[6];
                 load_spinor_part(A.v, c, j, blk, x);
                 cmul_blk(cb, blk, x, y);
@@ -1054,7 +1108,12 @@ __global__ __launch_bounds__(lds_max_threads<P>()) __attribute__((amdgpu_waves_p
         bool sel = false;
         for (int c = chunk * A.gw * R; c < (chunk + 1) * A.gw * R && c < A.ncol; c++)
             sel |= col_selected(A.status, A.statmask, c);
-        if (!sel) return;
+        if (!sel) {
+            if constexpr (EPI == EPI_TVR)
+                if (A.pap && tile_at(A.g, lt) == 0 && threadIdx.x == 0)
+                    for (int c = chunk * A.gw * R; c < (chunk + 1) * A.gw * R; c++) cg_mark_stopped(A, c);
+            return;
+        }
     }
     const int tile = tile_at(A.g, lt);                // lt < ntiles: one tile per workgroup
     const int base = tile * kTile;
@@ -1286,7 +1345,7 @@ __global__ __launch_bounds__(kSplitWaves * kTile) void k_hop_split(const Args<P,
     const bool own_alpha = EPI == EPI_TVR && A.pap != nullptr;  // uniform over the launch
     const bool first = lt == 0 && threadIdx.x == 0;             // writes the column's state
     if (!col_selected(A.status, A.statmask, c)) {  // uniform over the workgroup
-        if (own_alpha && first && A.cg_status[c] == COL_JUST_STOPPED) A.cg_status[c] = COL_STOPPED;
+        if (own_alpha && first) cg_mark_stopped(A, c);
         return;
     }
     double pap = 0.0;
@@ -1322,14 +1381,7 @@ __global__ __launch_bounds__(kSplitWaves * kTile) void k_hop_split(const Args<P,
     double alpha = 1.0;
     if constexpr (EPI == EPI_TVR) {
         if (own_alpha) {
-            pap = (pw[0] + pw[1]) + (pw[2] + pw[3]);
-            const bool ok = pap > 0.0 && isfinite(pap);
-            alpha = ok ? A.cg_rho[c] / pap : 0.0;
-            if (first) {
-                A.cg_pAp[c] = pap;
-                A.cg_alpha[c] = alpha;
-                if (!ok) A.cg_status[c] = COL_FAILED;  // the others' residuals stay as they are (alpha 0)
-            }
+            alpha = cg_alpha_of(A, c, (pw[0] + pw[1]) + (pw[2] + pw[3]), first);
         } else if (A.alpha) {
             alpha = A.alpha[c];
         }

@@ -60,7 +60,7 @@ struct HopLaunch {
     int percol = 0;                    // 1: column c uses cclov[c] and cf[c] instead of clov and f
     const void* cclov[kMaxCols] = {};
     double cf[kMaxCols] = {};
-    // hop-split EPI_TVR only: alpha = cg_rho / (the sum of column c's nwaves partials at pap + c * pstride) is
+    // EPI_TVR, up to kFusedParts partials: alpha = cg_rho / (the sum of column c's nwaves partials at pap + c * pstride) is
     // taken by the kernel itself, which also writes alpha, pAp and the states k_fin_alpha would
     const double* pap = nullptr;
     const double* cg_rho = nullptr;
