@@ -2603,17 +2603,22 @@ int bq_solve_multishift(bq_op op, bq_field b, int nshift, const double* shifts, 
     double* pr = pq + (size_t)hw * ncol;
     double* pp = pr + (size_t)hw * ncol;
     const size_t ns = (size_t)ncol * nshift;
-    CHK(scal.alloc(ctx, sizeof(double) * (8 * (size_t)ncol + 5 * ns)));
-    CHK(ints.alloc(ctx, sizeof(int) * (2 * (size_t)ncol + 2 * ns)));
+    CHK(scal.alloc(ctx, sizeof(double) * (11 * (size_t)ncol + 6 * ns)));
+    CHK(ints.alloc(ctx, sizeof(int) * (4 * (size_t)ncol + 4 * ns)));
     MsState S{};
+    double* sums = nullptr;  // 3 * ncol: a lattice's many partials summed in a launch of its own
     {
         double* d = scal.as<double>();
-        S.rho = d; S.alpha = d + ncol; S.alpha_prev = d + 2 * ncol; S.beta = d + 3 * ncol;
-        S.beta_prev = d + 4 * ncol; S.stop2 = d + 5 * ncol;
-        double* e = d + 8 * (size_t)ncol;
-        S.zeta = e; S.zeta_prev = e + ns; S.zeta_new = e + 2 * ns; S.ak = e + 3 * ns; S.bk = e + 4 * ns;
         int* i = ints.as<int>();
-        S.status = i; S.iters = i + ncol; S.act = i + 2 * ncol; S.kiters = i + 2 * ncol + ns;
+        for (MsSet* m : {&S.cur, &S.next}) {
+            m->rho = d; m->alpha_prev = d + ncol; m->beta_prev = d + 2 * ncol;
+            m->zeta = d + 3 * ncol; m->zeta_prev = d + 3 * ncol + ns;
+            d += 3 * ncol + 2 * ns;
+            m->status = i; m->iters = i + ncol; m->act = i + 2 * ncol; m->kiters = i + 2 * ncol + ns;
+            i += 2 * ncol + 2 * ns;
+        }
+        S.alpha = d; S.stop2 = d + ncol; sums = d + 2 * ncol;
+        S.zeta_new = d + 5 * ncol; S.ak = S.zeta_new + ns;
         S.nshift = nshift;
         S.base = base;
         for (int k = 0; k < nshift; k++) S.shift[k] = shifts[k] - sb;
@@ -2631,32 +2636,46 @@ int bq_solve_multishift(bq_op op, bq_field b, int nshift, const double* shifts, 
         if (k != base) HIPCHK(launch_convert(PREC_F64, bo, PREC_F64, f.pk[k], n, ncol, nullptr, 0, st));
     }
     HIPCHK(launch_norm2(PREC_F64, f.p, n, ncol, pp, hw, st));
-    HIPCHK(launch_fin_sum(pp, hw, ncol, S.rho, st));
+    HIPCHK(launch_fin_sum(pp, hw, ncol, S.cur.rho, st));
     HIPCHK(launch_ms_init(S, ncol, prm.tol * prm.tol, st));
     std::vector<double> b2(ncol);
-    HIPCHK(hipMemcpyAsync(b2.data(), S.rho, sizeof(double) * ncol, hipMemcpyDeviceToHost, st));
+    HIPCHK(hipMemcpyAsync(b2.data(), S.cur.rho, sizeof(double) * ncol, hipMemcpyDeviceToHost, st));
 
     const int kchunk = prm.chunk > 0 ? prm.chunk : 8;
     const long maxiter = prm.maxiter > 0 ? prm.maxiter : 100000;
-    OpCall c{op, PREC_F64, get_tune(ctx, PREC_F64, ncol), ncol, S.status, 1 << COL_ACTIVE, st};
+    OpCall c{op, PREC_F64, get_tune(ctx, PREC_F64, ncol), ncol, S.cur.status, 1 << COL_ACTIVE, st};
     std::vector<int> hs(ncol);
     long done_iters = 0;
+    // Up to kFusedParts partials are summed by every workgroup that needs them; more of them once
+    const bool pre = hw > kFusedParts;
+    const auto parts = [&](const double*& from, int which) -> int {
+        if (!pre) return BQ_OK;
+        HIPCHK(launch_fin_sum(from, hw, ncol, sums + which * ncol, st));
+        from = sums + which * ncol;
+        return BQ_OK;
+    };
+    const int nparts = pre ? 1 : hw;
+    const int per_iter = 6 + (pre ? (sb != 0.0 ? 3 : 2) : 0);
     while (true) {
         for (int it = 0; it < kchunk; it++) {
+            const double *q2 = pq, *p2 = pp, *r2 = pr;
+            c.status = S.cur.status;
             CHK(k1(c, 0, f.p, t.all()));
             CHK(tv(c, 0, 1, t.all(), f.p, q.all(), -kap * kap, pq, hw, hw));
-            HIPCHK(launch_fin_ms_alpha(S, pq, pp, hw, ncol, sb, st));
             CHK(k1(c, 1, q.all(), t.all()));
             CHK(tv(c, 1, 1, t.all(), q.all(), f.w, -kap * kap, nullptr, hw, hw));
-            HIPCHK(launch_ms_update1(S, f, sb, n, ncol, pr, hw, st));
-            HIPCHK(launch_fin_ms_beta(S, pr, hw, ncol, st));
-            HIPCHK(launch_ms_update2(S, f, n, ncol, pp, hw, st));
+            CHK(parts(q2, 0));
+            if (sb != 0.0) CHK(parts(p2, 1));
+            HIPCHK(launch_ms_residual(S, f, q2, p2, nparts, sb, n, ncol, pr, hw, st));
+            CHK(parts(r2, 2));
+            HIPCHK(launch_ms_directions(S, f, r2, nparts, n, ncol, pp, hw, st));
+            std::swap(S.cur, S.next);
         }
         done_iters += kchunk;
         acct.chunks++;
         acct.iterations += kchunk;
-        acct.launches += 8L * kchunk;
-        HIPCHK(hipMemcpyAsync(hs.data(), S.status, sizeof(int) * ncol, hipMemcpyDeviceToHost, st));
+        acct.launches += (long)per_iter * kchunk;
+        HIPCHK(hipMemcpyAsync(hs.data(), S.cur.status, sizeof(int) * ncol, hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
         bool all = true;
         for (int cc = 0; cc < ncol; cc++)
@@ -2664,9 +2683,9 @@ int bq_solve_multishift(bq_op op, bq_field b, int nshift, const double* shifts, 
         if (all || done_iters >= maxiter) break;
     }
     std::vector<int> kit(ns), act(ns), cit(ncol);
-    HIPCHK(hipMemcpyAsync(kit.data(), S.kiters, sizeof(int) * ns, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(act.data(), S.act, sizeof(int) * ns, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(cit.data(), S.iters, sizeof(int) * ncol, hipMemcpyDeviceToHost, st));
+    HIPCHK(hipMemcpyAsync(kit.data(), S.cur.kiters, sizeof(int) * ns, hipMemcpyDeviceToHost, st));
+    HIPCHK(hipMemcpyAsync(act.data(), S.cur.act, sizeof(int) * ns, hipMemcpyDeviceToHost, st));
+    HIPCHK(hipMemcpyAsync(cit.data(), S.cur.iters, sizeof(int) * ncol, hipMemcpyDeviceToHost, st));
     // true residuals |b - (Mhat^dag Mhat + sigma_k) x_k| in FP64
     std::vector<double> r2(ns);
     OpCall c64{op, PREC_F64, get_tune(ctx, PREC_F64, ncol), ncol, nullptr, 1, st};
@@ -2676,8 +2695,8 @@ int bq_solve_multishift(bq_op op, bq_field b, int nshift, const double* shifts, 
         CHK(op_fwd(c64, 0, xk, q, t, nullptr, hw));
         CHK(op_dag_r(c64, 0, q, t, bv, w, nullptr, nullptr, hw));
         HIPCHK(launch_axpy_norm(xk.all(), f.w, -shifts[k], n, ncol, pr, hw, st));
-        HIPCHK(launch_fin_sum(pr, hw, ncol, S.rho, st));
-        HIPCHK(hipMemcpyAsync(r2.data() + (size_t)k * ncol, S.rho, sizeof(double) * ncol, hipMemcpyDeviceToHost, st));
+        HIPCHK(launch_fin_sum(pr, hw, ncol, sums, st));
+        HIPCHK(hipMemcpyAsync(r2.data() + (size_t)k * ncol, sums, sizeof(double) * ncol, hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
     }
     HIPCHK(hipEventRecord(e1, st));
@@ -2687,7 +2706,8 @@ int bq_solve_multishift(bq_op op, bq_field b, int nshift, const double* shifts, 
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     // bytes: per iteration the four stencil launches, per active column their spinors and the base
-    // vectors, per active shift its x (rw) and direction (r, and rw unless it is the base)
+    // vectors (residual: r rw, w, p; directions: r, p rw), per active shift its x (rw) and, unless it is
+    // the base, its direction (rw)
     {
         const double Vh = g.Vh, s64 = sp_bytes(PREC_F64);
         long long colit = 0, shit = 0, shit_nb = 0;
@@ -2700,8 +2720,8 @@ int bq_solve_multishift(bq_op op, bq_field b, int nshift, const double* shifts, 
         int lock = 0;
         for (int cc = 0; cc < ncol; cc++) lock = std::max(lock, cit[cc]);
         acct.bytes += lock * iter_shared_bytes(op, PREC_F64);
-        acct.bytes += colit * Vh * s64 * (9 + 4 + 1 + 3);   // stencils, update1 base, update2 base
-        acct.bytes += shit * Vh * s64 * 3 + shit_nb * Vh * s64 * 2;
+        acct.bytes += colit * Vh * s64 * (9 + (sb != 0.0 ? 4 : 3) + 3);
+        acct.bytes += shit * Vh * s64 * 2 + shit_nb * Vh * s64 * 2;
         acct.bytes += nshift * (iter_shared_bytes(op, PREC_F64) + ncol * Vh * s64 * 13);  // true residuals
     }
     op->last.bytes = acct.bytes;

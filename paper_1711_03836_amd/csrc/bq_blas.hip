@@ -879,116 +879,153 @@ __global__ void k_ms_init(const MsState s, int ncol, double tol2)
 {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= ncol) return;
-    const double r2 = s.rho[c];
+    const double r2 = s.cur.rho[c];
     s.stop2[c] = tol2 * r2;
-    s.alpha_prev[c] = 1.0;
-    s.beta_prev[c] = 0.0;
-    s.iters[c] = 0;
+    s.cur.alpha_prev[c] = 1.0;
+    s.cur.beta_prev[c] = 0.0;
+    s.cur.iters[c] = 0;
     const int st = !isfinite(r2) ? COL_FAILED : (r2 > 0.0 ? COL_ACTIVE : COL_DONE);
-    s.status[c] = st;
+    s.cur.status[c] = st;
     for (int k = 0; k < s.nshift; k++) {
         const int i = c * s.nshift + k;
-        s.zeta[i] = s.zeta_prev[i] = s.zeta_new[i] = 1.0;
-        s.ak[i] = s.bk[i] = 0.0;
-        s.act[i] = st == COL_ACTIVE;
-        s.kiters[i] = 0;
+        s.cur.zeta[i] = s.cur.zeta_prev[i] = s.zeta_new[i] = 1.0;
+        s.ak[i] = 0.0;
+        s.cur.act[i] = st == COL_ACTIVE;
+        s.cur.kiters[i] = 0;
     }
 }
 
-// alpha of the base system and, per active shift, zeta_{j+1} and the shift's alpha
-__global__ void k_fin_ms_alpha(const MsState s, const double* pq, const double* pp, int nwaves, double sigma_b)
-{
-    const int c = blockIdx.x;
-    if (s.status[c] != COL_ACTIVE) return;  // uniform per block
-    const double qq = block_sum(pq + (size_t)c * nwaves, nwaves);
-    const double ppn = sigma_b != 0.0 ? block_sum(pp + (size_t)c * nwaves, nwaves) : 0.0;
-    if (threadIdx.x != 0) return;
-    const double pAp = qq + sigma_b * ppn;
-    if (!(pAp > 0.0) || !isfinite(pAp)) {
-        s.status[c] = COL_FAILED;
-        return;
-    }
-    const double al = s.rho[c] / pAp, ap = s.alpha_prev[c], bp = s.beta_prev[c];
-    s.alpha[c] = al;
-    for (int k = 0; k < s.nshift; k++) {
-        const int i = c * s.nshift + k;
-        if (!s.act[i]) continue;
-        const double z = s.zeta[i], zp = s.zeta_prev[i];
-        const double zn = z * zp * ap / (al * bp * (zp - z) + zp * ap * (1.0 + s.shift[k] * al));
-        s.zeta_new[i] = zn;
-        s.ak[i] = al * zn / z;
-    }
-}
-
-// beta of the base system; per shift: beta, convergence (|zeta_{j+1}| |r_{j+1}| <= tol |b|), rotation
-__global__ void k_fin_ms_beta(const MsState s, const double* pr, int nwaves)
-{
-    const int c = blockIdx.x;
-    if (s.status[c] != COL_ACTIVE) return;
-    const double rho = block_sum(pr + (size_t)c * nwaves, nwaves);
-    if (threadIdx.x != 0) return;
-    s.iters[c] += 1;
-    if (!isfinite(rho)) {
-        s.status[c] = COL_FAILED;
-        return;
-    }
-    const double be = rho / s.rho[c];
-    int any = 0;
-    for (int k = 0; k < s.nshift; k++) {
-        const int i = c * s.nshift + k;
-        if (!s.act[i]) continue;
-        const double z = s.zeta[i], zn = s.zeta_new[i];
-        const double q = zn / z;
-        s.bk[i] = be * q * q;
-        s.kiters[i] += 1;
-        if (zn * zn * rho <= s.stop2[c] || !isfinite(zn)) {
-            s.act[i] = 0;
-        } else {
-            s.zeta_prev[i] = z;
-            s.zeta[i] = zn;
-            any = 1;
-        }
-    }
-    s.alpha_prev[c] = s.alpha[c];
-    s.beta_prev[c] = be;
-    s.beta[c] = be;
-    s.rho[c] = rho;
-    if (!any) s.status[c] = COL_DONE;
-}
-
-__global__ void k_ms_update1(const MsState s, const MsFields f, double sigma_b, int n, double* partial, int nwaves)
+// The vector work of a multishift iteration in two launches.  Every workgroup takes its column's sums
+// itself (block_sum, the order of a launch of their own) and the first one of a column writes the
+// scalars that others read later.  The shifts' x_k wait for the second launch, which has their p_k in
+// registers anyway: 37 vectors are read or written for 8 shifts instead of 44, in one workgroup per
+// 256 sites and shift instead of one for all shifts.  Bound by memory: 16^3x32, 8 shifts: 49.2 + 25.7 us,
+// with the two launches for the scalars 87.7, now 14.7 + 51.0.
+__global__ __launch_bounds__(256) void k_ms_residual(const MsState s, const MsFields f, const double* pq, const double* pp,
+                                                     int nparts, double sigma_b, int n, double* partial, int nwaves)
 {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     const int c = blockIdx.y;
-    const bool on = s.status[c] == COL_ACTIVE;  // uniform per block
-    double nr = 0.0;
-    if (on && j < n) {
-        const SpinorPtr<P64> r = sp<P64>(f.r), w = sp<P64>(f.w), p = sp<P64>(f.p);
-        const double al = s.alpha[c];
-        cx<double> rv[12], wv[12], pv[12];
+    if (s.cur.status[c] != COL_ACTIVE) return;  // uniform per block
+    const SpinorPtr<P64> r = sp<P64>(f.r), w = sp<P64>(f.w), p = sp<P64>(f.p);
+    cx<double> rv[12], wv[12], pv[12];
+    if (j < n) {
         load_spinor(r, c, j, rv);
         load_spinor(w, c, j, wv);
-        load_spinor(p, c, j, pv);
+        if (sigma_b != 0.0) load_spinor(p, c, j, pv);
+    }
+    const double qq = block_sum(pq + (size_t)c * nparts, nparts);
+    const double ppn = sigma_b != 0.0 ? block_sum(pp + (size_t)c * nparts, nparts) : 0.0;
+    const double pAp = qq + sigma_b * ppn;
+    const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+    if (!(pAp > 0.0) || !isfinite(pAp)) {  // every workgroup of the column finds the same
+        if (first) s.cur.status[c] = COL_FAILED;
+        return;
+    }
+    const double al = s.cur.rho[c] / pAp;
+    if (first) {
+        const double ap = s.cur.alpha_prev[c], bp = s.cur.beta_prev[c];
+        s.alpha[c] = al;
+        for (int k = 0; k < s.nshift; k++) {
+            const int i = c * s.nshift + k;
+            if (!s.cur.act[i]) continue;
+            const double z = s.cur.zeta[i], zp = s.cur.zeta_prev[i];
+            const double zn = z * zp * ap / (al * bp * (zp - z) + zp * ap * (1.0 + s.shift[k] * al));
+            s.zeta_new[i] = zn;
+            s.ak[i] = al * zn / z;
+        }
+    }
+    double nr = 0.0;
+    if (j < n) {
 #pragma unroll
         for (int k = 0; k < 12; k++) {
-            rv[k].re = fmadd(-al, fmadd(sigma_b, pv[k].re, wv[k].re), rv[k].re);
-            rv[k].im = fmadd(-al, fmadd(sigma_b, pv[k].im, wv[k].im), rv[k].im);
+            if (sigma_b != 0.0) {
+                wv[k].re = fmadd(sigma_b, pv[k].re, wv[k].re);
+                wv[k].im = fmadd(sigma_b, pv[k].im, wv[k].im);
+            }
+            rv[k].re = fmadd(-al, wv[k].re, rv[k].re);
+            rv[k].im = fmadd(-al, wv[k].im, rv[k].im);
             nr += rv[k].re * rv[k].re + rv[k].im * rv[k].im;
         }
         store_spinor(r, c, j, rv);
-        for (int q = 0; q < s.nshift; q++) {
-            const int i = c * s.nshift + q;
-            if (!s.act[i]) continue;
-            const double a = s.ak[i];
-            cx<double> xv[12], pk[12];
-            const SpinorPtr<P64> X = sp<P64>(f.x[q]);
-            load_spinor(X, c, j, xv);
-            if (q == s.base) {
-#pragma unroll
-                for (int k = 0; k < 12; k++) pk[k] = pv[k];
-            } else {
-                load_spinor(sp<P64>(f.pk[q]), c, j, pk);
+    }
+    nr = wave_sum(nr);
+    const int wave = j >> kTileLog;
+    if ((threadIdx.x & 63) == 0 && wave < nwaves) partial[(size_t)c * nwaves + wave] = nr;
+}
+
+// a shift has converged in this iteration: |zeta_{j+1} r_{j+1}| <= tol |b| (or its recurrence broke down)
+__device__ __forceinline__ bool ms_done(const MsState& s, int c, int i, double rho)
+{
+    const double zn = s.zeta_new[i];
+    return zn * zn * rho <= s.stop2[c] || !isfinite(zn);
+}
+
+__global__ __launch_bounds__(256) void k_ms_directions(const MsState s, const MsFields f, const double* pr, int nparts,
+                                                       int n, double* partial, int nwaves)
+{
+    const int c = blockIdx.y;
+    // the shifts of the same sites side by side on one XCD: they share r in its L2
+    const int lb = xcd_remap(blockIdx.x, gridDim.x);
+    const int blk = lb / s.nshift, q = lb - blk * s.nshift;
+    const int j = blk * 256 + threadIdx.x;
+    const bool first = lb == 0 && threadIdx.x == 0;
+    const int st = s.cur.status[c];
+    const MsSet &cu = s.cur, &nx = s.next;
+    if (st != COL_ACTIVE) {  // uniform per block
+        if (first) {
+            nx.rho[c] = cu.rho[c];
+            nx.alpha_prev[c] = cu.alpha_prev[c];
+            nx.beta_prev[c] = cu.beta_prev[c];
+            nx.status[c] = st;
+            nx.iters[c] = cu.iters[c];
+            for (int k = 0; k < s.nshift; k++) {
+                const int i = c * s.nshift + k;
+                nx.zeta[i] = cu.zeta[i];
+                nx.zeta_prev[i] = cu.zeta_prev[i];
+                nx.act[i] = cu.act[i];
+                nx.kiters[i] = cu.kiters[i];
             }
+        }
+        return;
+    }
+    const int iq = c * s.nshift + q;
+    const bool act = cu.act[iq], base = q == s.base;
+    const SpinorPtr<P64> X = sp<P64>(f.x[q]), P = sp<P64>(base ? f.p : f.pk[q]);
+    cx<double> xv[12], pk[12], rv[12];
+    if ((act || base) && j < n) {
+        load_spinor(P, c, j, pk);
+        if (act) load_spinor(X, c, j, xv);
+        load_spinor(sp<P64>(f.r), c, j, rv);
+    }
+    const double rho0 = cu.rho[c];
+    const double rho = block_sum(pr + (size_t)c * nparts, nparts);
+    const bool ok = isfinite(rho);
+    const double be = rho / rho0;
+    bool any = false;
+    for (int k = 0; k < s.nshift; k++) {
+        const int i = c * s.nshift + k;
+        any = any || (cu.act[i] && !ms_done(s, c, i, rho));
+    }
+    if (first) {
+        nx.iters[c] = cu.iters[c] + 1;
+        nx.alpha_prev[c] = ok ? s.alpha[c] : cu.alpha_prev[c];
+        nx.beta_prev[c] = ok ? be : cu.beta_prev[c];
+        nx.rho[c] = ok ? rho : rho0;
+        nx.status[c] = !ok ? COL_FAILED : (any ? COL_ACTIVE : COL_DONE);
+        for (int k = 0; k < s.nshift; k++) {
+            const int i = c * s.nshift + k;
+            const bool a = cu.act[i], go = a && ok && !ms_done(s, c, i, rho);
+            nx.act[i] = ok ? go : (int)a;
+            nx.kiters[i] = cu.kiters[i] + (a && ok);
+            nx.zeta_prev[i] = go ? cu.zeta[i] : cu.zeta_prev[i];
+            nx.zeta[i] = go ? s.zeta_new[i] : cu.zeta[i];
+        }
+    }
+    double np = 0.0;
+    if (j < n) {
+        if (act) {
+            const double a = s.ak[iq];
 #pragma unroll
             for (int k = 0; k < 12; k++) {
                 xv[k].re = fmadd(a, pk[k].re, xv[k].re);
@@ -996,29 +1033,16 @@ __global__ void k_ms_update1(const MsState s, const MsFields f, double sigma_b, 
             }
             store_spinor(X, c, j, xv);
         }
-    }
-    nr = wave_sum(nr);
-    const int w = j >> kTileLog;
-    if (on && (threadIdx.x & 63) == 0 && w < nwaves) partial[(size_t)c * nwaves + w] = nr;
-}
-
-__global__ void k_ms_update2(const MsState s, const MsFields f, int n, double* partial, int nwaves)
-{
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    const int c = blockIdx.y;
-    const bool on = s.status[c] == COL_ACTIVE;
-    double np = 0.0;
-    if (on && j < n) {
-        const SpinorPtr<P64> r = sp<P64>(f.r), p = sp<P64>(f.p);
-        cx<double> rv[12], pv[12];
-        load_spinor(r, c, j, rv);
-        for (int q = 0; q < s.nshift; q++) {
-            const int i = c * s.nshift + q;
-            if (q == s.base || !s.act[i]) continue;
-            const double z = s.zeta[i], b = s.bk[i];
-            const SpinorPtr<P64> P = sp<P64>(f.pk[q]);
-            cx<double> pk[12];
-            load_spinor(P, c, j, pk);
+        if (ok && any && base) {
+#pragma unroll
+            for (int k = 0; k < 12; k++) {
+                pk[k].re = fmadd(be, pk[k].re, rv[k].re);
+                pk[k].im = fmadd(be, pk[k].im, rv[k].im);
+                np += pk[k].re * pk[k].re + pk[k].im * pk[k].im;
+            }
+            store_spinor(P, c, j, pk);
+        } else if (ok && act && !base && !ms_done(s, c, iq, rho)) {
+            const double z = s.zeta_new[iq], g = z / cu.zeta[iq], b = be * g * g;
 #pragma unroll
             for (int k = 0; k < 12; k++) {
                 pk[k].re = fmadd(b, pk[k].re, z * rv[k].re);
@@ -1026,19 +1050,11 @@ __global__ void k_ms_update2(const MsState s, const MsFields f, int n, double* p
             }
             store_spinor(P, c, j, pk);
         }
-        load_spinor(p, c, j, pv);
-        const double be = s.beta[c];
-#pragma unroll
-        for (int k = 0; k < 12; k++) {
-            pv[k].re = fmadd(be, pv[k].re, rv[k].re);
-            pv[k].im = fmadd(be, pv[k].im, rv[k].im);
-            np += pv[k].re * pv[k].re + pv[k].im * pv[k].im;
-        }
-        store_spinor(p, c, j, pv);
     }
+    if (!base) return;  // uniform per block
     np = wave_sum(np);
     const int w = j >> kTileLog;
-    if (on && (threadIdx.x & 63) == 0 && w < nwaves) partial[(size_t)c * nwaves + w] = np;
+    if ((threadIdx.x & 63) == 0 && w < nwaves) partial[(size_t)c * nwaves + w] = np;
 }
 
 }  // namespace
@@ -1056,32 +1072,20 @@ hipError_t launch_ms_init(const MsState& s, int ncol, double tol2, hipStream_t s
     return hipGetLastError();
 }
 
-hipError_t launch_fin_ms_alpha(const MsState& s, const double* pq, const double* pp, int nwaves, int ncol,
-                               double sigma_b, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_fin_ms_alpha, dim3(ncol), dim3(256), 0, st, s, pq, pp, nwaves, sigma_b);
-    return hipGetLastError();
-}
-
-hipError_t launch_fin_ms_beta(const MsState& s, const double* pr, int nwaves, int ncol, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_fin_ms_beta, dim3(ncol), dim3(256), 0, st, s, pr, nwaves);
-    return hipGetLastError();
-}
-
-hipError_t launch_ms_update1(const MsState& s, const MsFields& f, double sigma_b, int n, int ncol, double* partial,
-                             int nwaves, hipStream_t st)
+hipError_t launch_ms_residual(const MsState& s, const MsFields& f, const double* pq, const double* pp, int nparts,
+                              double sigma_b, int n, int ncol, double* partial, int nwaves, hipStream_t st)
 {
     if (s.nshift < 1 || s.nshift > kMaxShifts) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_ms_update1, grid2(n, ncol), dim3(kBS), 0, st, s, f, sigma_b, n, partial, nwaves);
+    hipLaunchKernelGGL(k_ms_residual, grid2(n, ncol), dim3(kBS), 0, st, s, f, pq, pp, nparts, sigma_b, n, partial, nwaves);
     return hipGetLastError();
 }
 
-hipError_t launch_ms_update2(const MsState& s, const MsFields& f, int n, int ncol, double* partial, int nwaves,
-                             hipStream_t st)
+hipError_t launch_ms_directions(const MsState& s, const MsFields& f, const double* pr, int nparts, int n, int ncol,
+                                double* partial, int nwaves, hipStream_t st)
 {
     if (s.nshift < 1 || s.nshift > kMaxShifts) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_ms_update2, grid2(n, ncol), dim3(kBS), 0, st, s, f, n, partial, nwaves);
+    hipLaunchKernelGGL(k_ms_directions, dim3((n + kBS - 1) / kBS * s.nshift, ncol), dim3(kBS), 0, st, s, f, pr, nparts, n,
+                       partial, nwaves);
     return hipGetLastError();
 }
 

@@ -129,24 +129,27 @@ hipError_t launch_axpy_norm(FieldArg x, FieldArg y, double a, int n, int ncol, d
 // A + sigma_b (sigma_b the smallest shift), with collinear shifted residuals r_k = zeta_k r
 // ---------------------------------------------------------------------------
 constexpr int kMaxShifts = 16;
-struct MsState {
+// The states an iteration reads (cur) and leaves behind (next): two sets, so that no workgroup of the
+// launch that ends an iteration reads what another one writes.
+struct MsSet {
     // per column
-    double* rho;      // |r|^2
-    double* alpha;    // base alpha_j
+    double* rho;       // |r|^2
     double* alpha_prev;
-    double* beta;     // base beta_j
     double* beta_prev;
-    double* stop2;    // (tol |b|)^2
-    int* status;      // COL_ACTIVE / COL_DONE / COL_FAILED
+    int* status;       // COL_ACTIVE / COL_DONE / COL_FAILED
     int* iters;
     // per column and shift, index c * nshift + k
     double* zeta;      // zeta_j
     double* zeta_prev; // zeta_{j-1}
-    double* zeta_new;  // zeta_{j+1}
-    double* ak;        // shift alpha
-    double* bk;        // shift beta
     int* act;          // shift still iterating
     int* kiters;       // iterations of the shift
+};
+struct MsState {
+    MsSet cur, next;
+    double* alpha;     // per column: base alpha_j
+    double* stop2;     // (tol |b|)^2
+    double* zeta_new;  // per column and shift: zeta_{j+1}
+    double* ak;        // shift alpha
     int nshift, base;
     double shift[kMaxShifts];  // sigma_k - sigma_b
 };
@@ -156,15 +159,14 @@ struct MsFields {
     FieldArg pk[kMaxShifts];       // shift directions (pk[base] = p)
 };
 hipError_t launch_ms_init(const MsState& s, int ncol, double tol2, hipStream_t st);
-hipError_t launch_fin_ms_alpha(const MsState& s, const double* pq, const double* pp, int nwaves, int ncol,
-                               double sigma_b, hipStream_t st);
-hipError_t launch_fin_ms_beta(const MsState& s, const double* pr, int nwaves, int ncol, hipStream_t st);
-// r -= alpha (w + sigma_b p); x_k += ak p_k (active shifts); |r|^2 partials
-hipError_t launch_ms_update1(const MsState& s, const MsFields& f, double sigma_b, int n, int ncol, double* partial,
-                             int nwaves, hipStream_t st);
-// p_k = zeta_{j+1} r + bk p_k (active shifts other than the base); p = r + beta p; |p|^2 partials
-hipError_t launch_ms_update2(const MsState& s, const MsFields& f, int n, int ncol, double* partial, int nwaves,
-                             hipStream_t st);
+// alpha of the base system from the nparts partials of |q|^2 (and |p|^2 if sigma_b), zeta_{j+1} and alpha of
+// the shifts; r -= alpha (w + sigma_b p); |r|^2 partials
+hipError_t launch_ms_residual(const MsState& s, const MsFields& f, const double* pq, const double* pp, int nparts,
+                              double sigma_b, int n, int ncol, double* partial, int nwaves, hipStream_t st);
+// beta from the nparts partials of |r|^2; per active shift x_k += ak p_k, then p_k = zeta_{j+1} r + bk p_k (base:
+// p = r + beta p) unless it has converged; |p|^2 partials; the states after the iteration into s.next
+hipError_t launch_ms_directions(const MsState& s, const MsFields& f, const double* pr, int nparts, int n, int ncol,
+                                double* partial, int nwaves, hipStream_t st);
 
 // ---------------------------------------------------------------------------
 // block (multishift) CG: one block Krylov space for N <= kBlockMax columns; the N x N step
