@@ -145,19 +145,39 @@ struct StepLds {
     int pos[LD];  // packed position of a column, -1 if not active
 };
 
+// Entry e of a 16 x 16 matrix is lane e mod 64's, four entries each, so that a matrix takes one trip to
+// memory.  Outside the leading n x n part: the identity.
+__device__ __forceinline__ double2 m_pad(int i, int j) { return make_double2(i == j ? 1.0 : 0.0, 0.0); }
+
 __device__ void m_gather(Mat& D, const double2* full, const StepLds& L, int n)
 {
-    const int j = threadIdx.x;
-    if (j < n)
-        for (int i = 0; i < n; i++) D[i][j] = full[L.idx[i] * LD + L.idx[j]];
+    double2 v[4];
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const int e = threadIdx.x + 64 * q, i = e / LD, j = e % LD;
+        v[q] = i < n && j < n ? full[L.idx[i] * LD + L.idx[j]] : m_pad(i, j);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const int e = threadIdx.x + 64 * q;
+        D[e / LD][e % LD] = v[q];
+    }
     __syncthreads();
 }
 
 __device__ void m_load(Mat& D, const double2* packed, int n)
 {
-    const int j = threadIdx.x;
-    if (j < n)
-        for (int i = 0; i < n; i++) D[i][j] = packed[i * LD + j];
+    double2 v[4];
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const int e = threadIdx.x + 64 * q, i = e / LD, j = e % LD;
+        v[q] = i < n && j < n ? packed[i * LD + j] : m_pad(i, j);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const int e = threadIdx.x + 64 * q;
+        D[e / LD][e % LD] = v[q];
+    }
     __syncthreads();
 }
 
@@ -234,40 +254,63 @@ __device__ void m_sub(Mat& C, const Mat& A, const Mat& B, int n)
     __syncthreads();
 }
 
-// X = G^-1 B for Hermitian positive definite G (Cholesky G = L L^dag in W); X distinct from G, B, W
-__device__ bool m_chol_solve(Mat& X, const Mat& G, const Mat& B, int n, Mat& W)
+// X = G^-1 B for Hermitian positive definite G, padded with the identity (m_gather); X and W distinct from
+// each other and from G and B.  Elimination of [G | B] row by row in W and X (for such a G the pivots are
+// the squares of Cholesky's, and positive unless it breaks down), then back substitution: 2 n
+// short steps in which every lane has four entries of each matrix.  A step launch at 12 columns took
+// 30 us with one column per lane, one product after the other, 20 with the columns in registers and
+// all loops unrolled (that code comes cold from memory every time), and takes 15 now.
+__device__ bool m_solve(Mat& X, const Mat& G, const Mat& B, int n, Mat& W)
 {
-    const int j = threadIdx.x;
-    if (j < n)
-        for (int i = 0; i < n; i++) W[i][j] = G[i][j];
+    const int j = threadIdx.x % LD, i0 = threadIdx.x / LD;  // entries (i0 + 4 q, j)
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        W[i0 + 4 * q][j] = G[i0 + 4 * q][j];
+        X[i0 + 4 * q][j] = B[i0 + 4 * q][j];
+    }
     __syncthreads();
     for (int k = 0; k < n; k++) {
-        const double d = W[k][k].x;
+        const double d = W[k][k].x;  // the same on every lane
         if (!(d > 0.0) || !isfinite(d)) return false;
-        const double lk = sqrt(d);
+        const double inv = 1.0 / d;
+        const double2 wk = W[k][j], xk = X[k][j];
+        double2 f[4], w[4], x[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const int i = i0 + 4 * q;
+            f[q] = W[i][k];
+            w[q] = W[i][j];
+            x[q] = X[i][j];
+        }
         __syncthreads();
-        if (j > k && j < n) W[j][k] = cscal(1.0 / lk, W[j][k]);
-        if (j == k) W[k][k] = make_double2(lk, 0.0);
-        __syncthreads();
-        if (j > k && j < n) {
-            const double2 ljk = cconj(W[j][k]);
-            for (int i = j; i < n; i++) W[i][j] = csub(W[i][j], cmul(W[i][k], ljk));
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const int i = i0 + 4 * q;
+            if (i > k) {
+                const double2 g = cscal(inv, f[q]);
+                if (j > k) W[i][j] = csub(w[q], cmul(g, wk));
+                X[i][j] = csub(x[q], cmul(g, xk));
+            }
         }
         __syncthreads();
     }
-    if (j < n) {
-        for (int i = 0; i < n; i++) {
-            double2 y = B[i][j];
-            for (int k = 0; k < i; k++) y = csub(y, cmul(W[i][k], X[k][j]));
-            X[i][j] = cscal(1.0 / W[i][i].x, y);
+    for (int k = n - 1; k >= 0; k--) {
+        const double2 xk = cscal(1.0 / W[k][k].x, X[k][j]);
+        double2 f[4], x[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            f[q] = W[i0 + 4 * q][k];
+            x[q] = X[i0 + 4 * q][j];
         }
-        for (int i = n - 1; i >= 0; i--) {
-            double2 y = X[i][j];
-            for (int k = i + 1; k < n; k++) y = csub(y, cmul(cconj(W[k][i]), X[k][j]));
-            X[i][j] = cscal(1.0 / W[i][i].x, y);
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const int i = i0 + 4 * q;
+            if (i < k) X[i][j] = csub(x[q], cmul(f[q], xk));
+            else if (i == k) X[i][j] = xk;
         }
+        __syncthreads();
     }
-    __syncthreads();
     return true;
 }
 
@@ -405,7 +448,7 @@ __device__ void step_alpha(const BlockState& S, StepLds& L)
     const int k = S.ctrl[BC_K];
     m_gather(L.a, mat(S, BM_PQ), L, n);
     m_gather(L.b, mat(S, BM_RR), L, n);
-    bool ok = m_chol_solve(L.c, L.a, L.b, n, L.d);  // alpha in L.c
+    bool ok = m_solve(L.c, L.a, L.b, n, L.d);  // alpha in L.c
     if (!ok) {
         stop_run(S, true);
         return;
@@ -521,7 +564,7 @@ __device__ void step_beta(const BlockState& S, StepLds& L)
         return;
     }
     m_gather(L.b, mat(S, BM_RR), L, n);
-    if (!m_chol_solve(L.c, L.b, L.a, n, L.d)) {  // beta in L.c
+    if (!m_solve(L.c, L.b, L.a, n, L.d)) {  // beta in L.c
         stop_run(S, true);
         return;
     }
