@@ -371,11 +371,11 @@ int bq_time_copy(bq_context ctx, uint64_t bytes, int reps, void* stream, double*
  * from there by every wave (march is then ignored; bs may be any multiple of 64 up to 1024);
  * lds: 2 is the same with R = 1 only, where each wave also takes the x and y neighbours that
  * lie in its own tile from the other lanes' registers instead of from memory.
- * order: the traversal of the 64-site tiles by the plain and tile-shared stencils on lattices
- * whose (x,y) planes hold whole tiles: 0 visits them in blocks of 4x4 (z,t) planes; 1 gives each
- * of the 8 XCDs one slab of L_z/gcd(L_z,8) z planes and walks it t plane by t plane (ignored by
- * the t-marching stencil and on other lattices); 2 is order 1 where it applies and, on any lattice
- * with a multiple of 8 tile blocks, has each XCD walk its tile blocks once per column-group chunk
+ * order: the traversal of the 64-site tiles by the plain and tile-shared stencils: 0 visits them in
+ * blocks of 4x4 (z,t) planes where (x,y) planes hold whole tiles, else in memory order; 1 cuts each
+ * time slice into up to 8 slabs, one per XCD, and walks each slab slice by slice (where time slices
+ * hold whole tiles; elsewhere memory order; ignored by the t-marching stencil); 2 is order 1
+ * and, on a lattice with a multiple of 8 tile blocks, has each XCD walk its tile blocks once per column-group chunk
  * (fewer columns in flight per XCD; links and clover are read once per chunk).  Errors: BQ_ERR_INVALID for a configuration
  * that is not compiled or out of range.  Results do not depend on the configuration.
  * A configuration of the default's shape (R, bs, march, lds and order as bq_tune_get gives them when

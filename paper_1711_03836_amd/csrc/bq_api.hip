@@ -110,32 +110,60 @@ struct Tune {
     int lds = 0;    // 1: tile-shared stencil (links and clover staged in LDS) for several column groups per tile;
                     // 2: with a lane exchange of x/y neighbours
     int order = 0;  // tile traversal of the plain and tile-shared stencils: 0 blocks of 4x4 (z,t) planes,
-                    // 1 one z slab per XCD walked plane by plane in t, 2 as 1 with the column-group
+                    // 1 one slab per XCD walked slice by slice in t, 2 as 1 with the column-group
                     // chunks walked one after another on each XCD
     bool chosen = false;  // set by the user or the autotuner; otherwise the launch's size picks the kernel
 };
 
-// The geometry a stencil launch walks for traversal order `order` (tile_at, item_of).  Order 1 cuts the
-// z extent into 8 slabs of Lz / gcd(Lz, 8) planes, one per XCD (each XCD takes one contiguous
-// range of logical tiles), and walks each slab t plane by t plane, so that the 8 XCDs work on
-// the same few time planes at any moment and the +-t neighbours of a plane are still in the
-// last-level cache when they are read again.
-static Geom with_order(Geom g, int order)
+// The walk of g by blocks of ub tiles x zb planes x tb time slices, planes of nu tiles (tile_at).
+static void set_walk(Geom& g, int nu, int ub, int zb, int tb)
 {
-    g.cmajor = order == 2;
-    if (order < 1 || !g.blocked) return g;
-    int a = g.L[2], b = 8;
+    g.blocked = 1;
+    g.nu = nu;
+    g.ub = ub;
+    g.zb = zb;
+    g.tb = tb;
+    g.nub = nu / ub;
+    g.nzb = g.nps / (nu * zb);
+    g.inv_ub = 1.0f / (float)g.ub;
+    g.inv_zb = 1.0f / (float)g.zb;
+    g.inv_tb = 1.0f / (float)g.tb;
+    g.inv_nub = 1.0f / (float)g.nub;
+    g.inv_nzb = 1.0f / (float)g.nzb;
+}
+
+static int gcd_of(int a, int b)
+{
     while (b) {
         const int r = a % b;
         a = b;
         b = r;
     }
-    g.zb = g.L[2] / a;
-    g.tb = g.L[3];
-    g.nzb = g.L[2] / g.zb;
-    g.inv_zb = 1.0f / (float)g.zb;
-    g.inv_tb = 1.0f / (float)g.tb;
-    g.inv_nzb = 1.0f / (float)g.nzb;
+    return a;
+}
+
+// The geometry a stencil launch walks for traversal order `order` (tile_at, item_of).  Order 1 cuts each
+// time slice into up to 8 slabs, one per XCD (each XCD takes one contiguous range of logical tiles),
+// and walks each slab slice by slice, so that the 8 XCDs work on the same few slices at any moment
+// and the +-t neighbours of a slice are still in the last-level cache, and in part in the XCD's L2,
+// when they are read again.  Where (x,y) planes hold whole tiles a slab is Lz / gcd(Lz, 8) planes
+// thick, then trades y extent for thickness while it is more than twice as wide: fewer of its sites
+// have neighbours in another slab (32^3x64 x 12, K1: 32 x 4 rows FP64 2154 us, FP32 850, FP16 653;
+// 16 x 8 2064, 848, 664).  Where only whole slices do (24^3x48) it is any gcd(tiles, 8)th of the slice
+// (K1 x 12 against walking slice after slice: FP64 744 -> 667 us, FP32 302 -> 292, FP16 219 -> 214).
+static Geom with_order(Geom g, int order)
+{
+    g.cmajor = order == 2;
+    if (order < 1) return g;
+    if (g.blocked) {
+        int ub = g.nu, zb = g.L[2] / gcd_of(g.L[2], 8);
+        const double rows = (double)g.L[1] / g.nu;  // per tile
+        while (ub % 2 == 0 && g.L[2] % (2 * zb) == 0 && ub * rows > 2 * zb) ub /= 2, zb *= 2;
+        set_walk(g, g.nu, ub, zb, g.L[3]);
+    } else if (g.ntiles * kTile == g.Vh && g.ntiles % g.L[3] == 0) {
+        const int part = g.nps / gcd_of(g.nps, 8);
+        set_walk(g, part, part, 1, g.L[3]);
+    }
     return g;
 }
 
@@ -361,15 +389,10 @@ static Geom make_geom(const int* d)
     g.inv_Lz = 1.0f / (float)d[2];
     g.ntiles = pad_sites(g.Vh) / kTile;
     const int plane = g.Lxh * d[1];
-    g.zb = d[2] % 4 == 0 ? 4 : (d[2] % 2 == 0 ? 2 : 1);
-    g.tb = d[3] % 4 == 0 ? 4 : (d[3] % 2 == 0 ? 2 : 1);
-    g.blocked = plane % kTile == 0 && (g.zb > 1 || g.tb > 1);
-    g.nu = g.blocked ? plane / kTile : 1;
-    g.nzb = d[2] / g.zb;
-    g.inv_nu = 1.0f / (float)g.nu;
-    g.inv_zb = 1.0f / (float)g.zb;
-    g.inv_tb = 1.0f / (float)g.tb;
-    g.inv_nzb = 1.0f / (float)g.nzb;
+    g.nps = g.ntiles / d[3];  // whole where a walk uses it
+    const int zb = d[2] % 4 == 0 ? 4 : (d[2] % 2 == 0 ? 2 : 1);
+    const int tb = d[3] % 4 == 0 ? 4 : (d[3] % 2 == 0 ? 2 : 1);
+    if (plane % kTile == 0 && (zb > 1 || tb > 1)) set_walk(g, plane / kTile, plane / kTile, zb, tb);
     return g;
 }
 
@@ -572,19 +595,19 @@ static void pick_kernel(HopLaunch& L, const Geom& g, int nact, int& order)
         L.R = 1;
         return;
     }
-    // The z-slab traversal keeps the +-t planes in the last-level cache; lattices that fit there
-    // whole lose a little L2 locality to it (FP32 x 1: 16^3x32 28.1 in order 0, 29.0 in order 1;
-    // 32^3x64 415 and 386)
+    // The slab walk keeps the +-t slices in the last-level cache; columns that fit there whole lose a
+    // little L2 locality to it (one column: 16^3x32 FP32 28.1 in order 0, 29.0 in order 1; 32^3x64 415 and
+    // 386.  K1 of several: FP64 x 12 on 16^3x64, 302 MB, 284 and 272, on 16^3x32, 151 MB, 138 and 140; FP32 x 16 on
+    // 16^3x32, 101 MB, 74 and 81)
     order = g.ntiles >= 4096 ? 1 : 0;
     // From these column counts on, links and clover read once per tile into LDS beat reading them
     // per wave (32^3x64: FP64 x 3 1442 against 1572, x 2 1307 against 1176; FP32 x 6 1176 against
-    // 1211, x 5 1100 against 1077; FP16 x 8 967 against 1015, x 6 852 against 770).  Over 12
-    // columns in two chunks, one after the other per XCD (24^3x48 FP32 x 16: 978 against 1046)
+    // 1211, x 5 1100 against 1077; FP16 x 8 967 against 1015, x 6 852 against 770)
     if (n >= (f64 ? 3 : f16 ? 8 : 6)) {
         L.lds = 1;
         L.R = 1;
         L.bs = 768;
-        if (n > 12) order = 2;
+        if (items * kTile * 12 * (f64 ? 16 : f16 ? 4 : 8) > 256L << 20) order = 1;
         return;
     }
     // Two columns per wave halve the link reads but also the waves: worth it beyond 4096 one-column
@@ -614,6 +637,7 @@ static HopLaunch hop_base(bq_op op, int prec, const Tune& t, int dagger, int out
     if (!t.chosen) pick_kernel(L, G->g, nact > 0 ? nact : ncol, order);
     L.dagger = dagger;
     L.g = with_order(G->g, order);
+    L.last_t = order >= 1;
     L.parity = out_parity;
     const LinkSet* ls = G->get(prec, L.recon);
     for (int k = 0; k < 8; k++) L.U[k] = ls ? ls->U[k] : nullptr;
@@ -3054,13 +3078,12 @@ int bq_autotune(bq_op op, int prec, int nrhs)
             bt = c.second;
             break;
         }
-    // pass 3: the winner in the other traversals (z slabs per XCD; and those with the column-group
+    // pass 3: the winner in the other traversals (slabs per XCD; and those with the column-group
     // chunks one after another per XCD), kept if 2% faster
     if (bt.chosen && bt.march == 0) {
         double tb = time_of(bt, 20);
         const Tune base = bt;
         for (int order : {1, 2}) {
-            if (order == 1 && !g.blocked) continue;
             Tune ot = base;
             ot.order = order;
             const double t = time_of(ot, 20);

@@ -442,10 +442,10 @@ struct HalfHop {
     float sc[P::id == PREC_F16 ? R : 1];  // FP16 spinor scales
 };
 
-template <class P, class PR, int R, int RECON>
+template <class P, class PR, int R, int RECON, int SA = 0>
 __device__ __forceinline__ void hh_load_spinor(const Args<P, PR>& A, int c, int r, HalfHop<P, R, RECON>& d)
 {
-    load_units<P, 12, 0>(buf_rsrc(A.in.d + c * A.in.cstride), d.jn, d.sp[r]);
+    load_units<P, 12, SA>(buf_rsrc(A.in.d + c * A.in.cstride), d.jn, d.sp[r]);
     if constexpr (P::id == PREC_F16) d.sc[r] = buf_load4f(buf_rsrc(A.in.s + c * A.in.sstride), (uint32_t)d.jn * 4u);
 }
 
@@ -1028,7 +1028,15 @@ __device__ __forceinline__ void hh_xchg(const Args<P, PR>& A, const Site& s, boo
     phase_end(a1, acc1);
 }
 
-template <class P, class PR, int R, int RECON, int NB, int H>
+// Issue the neighbour spinors of half hop H.  LT: the launch walks its tiles down in t, slice by slice, so
+// the +t neighbour's slice is not read again; it is then streamed past what the L2 still needs
+// (32^3x64 x 12, K1: FP32 867 -> 850 us, FP64 2243 -> 2154; 24^3x48 x 12: FP32 297 -> 292, FP64 698 -> 667).  In
+// blocks of 4x4 planes it is read again (16^3x32 x 12 streamed: FP32 58 -> 64 us), and FP16 gains
+// nothing.  A branch in the kernel would cost far more: it keeps the loads from running ahead of the
+// arithmetic (FP32 850 -> 1138).
+template <class P, int R, bool PC> constexpr bool has_last_t() { return P::id != PREC_F16 && R == 1 && !PC; }
+
+template <class P, class PR, int R, int RECON, int NB, int H, bool LT>
 __device__ __forceinline__ void lds_issue(const Args<P, PR>& A, const Site& s, const bool (&act)[R], int c0,
                                           HalfHop<P, R, RECON> (&d)[NB])
 {
@@ -1037,11 +1045,11 @@ __device__ __forceinline__ void lds_issue(const Args<P, PR>& A, const Site& s, c
         nx.jn = nbr(A.g, s, H >> 1, (H & 1) ? -1 : +1);
 #pragma unroll
         for (int r = 0; r < R; r++)
-            if (act[r]) hh_load_spinor(A, c0 + r, r, nx);
+            if (act[r]) hh_load_spinor<P, PR, R, RECON, H == 6 && LT ? kBufNT : 0>(A, c0 + r, r, nx);
     }
 }
 
-template <class P, class PR, int R, int DAG, int RECON, int NB, int H>
+template <class P, class PR, int R, int DAG, int RECON, int NB, int H, bool LT>
 __device__ __forceinline__ void hh_step_lds(const Args<P, PR>& A, const Site& s, const bool (&act)[R], int c0,
                                             const typename LinkLds<P>::C* __restrict__ lk, int lane,
                                             HalfHop<P, R, RECON> (&d)[NB], cx<typename P::real> (&acc)[R][12])
@@ -1050,7 +1058,7 @@ __device__ __forceinline__ void hh_step_lds(const Args<P, PR>& A, const Site& s,
     constexpr int MU = H >> 1;
     constexpr bool BW = H & 1;
     constexpr int S = (DAG ? +1 : -1) * (BW ? -1 : +1);
-    lds_issue<P, PR, R, RECON, NB, H + NB - 1>(A, s, act, c0, d);
+    lds_issue<P, PR, R, RECON, NB, H + NB - 1, LT>(A, s, act, c0, d);
     HalfHop<P, R, RECON>& cur = d[H % NB];
     PLink<P, RECON, BW> L;
 #pragma unroll
@@ -1089,7 +1097,7 @@ template <class P, int R, bool XCHG> constexpr int lds_min_waves()
     return P::id != PREC_F64 && R == 1 && !XCHG ? 6 : 1;
 }
 
-template <class P, class PR, int R, int DAG, int EPI, int RECON, bool PC, int LA, bool XCHG>
+template <class P, class PR, int R, int DAG, int EPI, int RECON, bool PC, int LA, bool XCHG, bool LT>
 __global__ __launch_bounds__(lds_max_threads<P>()) __attribute__((amdgpu_waves_per_eu(lds_min_waves<P, R, XCHG>(), 8))) void k_hop_lds(const Args<P, PR> A)
 {
     using T = typename P::real;
@@ -1193,12 +1201,12 @@ __global__ __launch_bounds__(lds_max_threads<P>()) __attribute__((amdgpu_waves_p
         hh_xchg<P, PR, DAG, RECON, 0>(A, s, act0, c0, base, own, own_sc, lk, lane, acc[0]);
         hh_xchg<P, PR, DAG, RECON, 1>(A, s, act0, c0, base, own, own_sc, lk, lane, acc[0]);
         hh_xchg<P, PR, DAG, RECON, 2>(A, s, act0, c0, base, own, own_sc, lk, lane, acc[0]);
-        lds_issue<P, PR, R, RECON, NB, 4>(A, s, act, c0, d);
+        lds_issue<P, PR, R, RECON, NB, 4, LT>(A, s, act, c0, d);
         hh_xchg<P, PR, DAG, RECON, 3>(A, s, act0, c0, base, own, own_sc, lk, lane, acc[0]);
-        hh_step_lds<P, PR, R, DAG, RECON, NB, 4>(A, s, act, c0, lk, lane, d, acc);
-        hh_step_lds<P, PR, R, DAG, RECON, NB, 5>(A, s, act, c0, lk, lane, d, acc);
-        hh_step_lds<P, PR, R, DAG, RECON, NB, 6>(A, s, act, c0, lk, lane, d, acc);
-        hh_step_lds<P, PR, R, DAG, RECON, NB, 7>(A, s, act, c0, lk, lane, d, acc);
+        hh_step_lds<P, PR, R, DAG, RECON, NB, 4, LT>(A, s, act, c0, lk, lane, d, acc);
+        hh_step_lds<P, PR, R, DAG, RECON, NB, 5, LT>(A, s, act, c0, lk, lane, d, acc);
+        hh_step_lds<P, PR, R, DAG, RECON, NB, 6, LT>(A, s, act, c0, lk, lane, d, acc);
+        hh_step_lds<P, PR, R, DAG, RECON, NB, 7, LT>(A, s, act, c0, lk, lane, d, acc);
     } else if (any) {
         const Site s = site_of(A.g, A.parity, j);
 #pragma unroll
@@ -1207,16 +1215,16 @@ __global__ __launch_bounds__(lds_max_threads<P>()) __attribute__((amdgpu_waves_p
             for (int k = 0; k < 12; k++) acc[r][k] = {T(0), T(0)};
         constexpr int NB = lds_ring<P, R>();
         HalfHop<P, R, RECON> d[NB];
-        lds_issue<P, PR, R, RECON, NB, 0>(A, s, act, c0, d);
-        if constexpr (NB > 2) lds_issue<P, PR, R, RECON, NB, 1>(A, s, act, c0, d);
-        hh_step_lds<P, PR, R, DAG, RECON, NB, 0>(A, s, act, c0, lk, lane, d, acc);
-        hh_step_lds<P, PR, R, DAG, RECON, NB, 1>(A, s, act, c0, lk, lane, d, acc);
-        hh_step_lds<P, PR, R, DAG, RECON, NB, 2>(A, s, act, c0, lk, lane, d, acc);
-        hh_step_lds<P, PR, R, DAG, RECON, NB, 3>(A, s, act, c0, lk, lane, d, acc);
-        hh_step_lds<P, PR, R, DAG, RECON, NB, 4>(A, s, act, c0, lk, lane, d, acc);
-        hh_step_lds<P, PR, R, DAG, RECON, NB, 5>(A, s, act, c0, lk, lane, d, acc);
-        hh_step_lds<P, PR, R, DAG, RECON, NB, 6>(A, s, act, c0, lk, lane, d, acc);
-        hh_step_lds<P, PR, R, DAG, RECON, NB, 7>(A, s, act, c0, lk, lane, d, acc);
+        lds_issue<P, PR, R, RECON, NB, 0, LT>(A, s, act, c0, d);
+        if constexpr (NB > 2) lds_issue<P, PR, R, RECON, NB, 1, LT>(A, s, act, c0, d);
+        hh_step_lds<P, PR, R, DAG, RECON, NB, 0, LT>(A, s, act, c0, lk, lane, d, acc);
+        hh_step_lds<P, PR, R, DAG, RECON, NB, 1, LT>(A, s, act, c0, lk, lane, d, acc);
+        hh_step_lds<P, PR, R, DAG, RECON, NB, 2, LT>(A, s, act, c0, lk, lane, d, acc);
+        hh_step_lds<P, PR, R, DAG, RECON, NB, 3, LT>(A, s, act, c0, lk, lane, d, acc);
+        hh_step_lds<P, PR, R, DAG, RECON, NB, 4, LT>(A, s, act, c0, lk, lane, d, acc);
+        hh_step_lds<P, PR, R, DAG, RECON, NB, 5, LT>(A, s, act, c0, lk, lane, d, acc);
+        hh_step_lds<P, PR, R, DAG, RECON, NB, 6, LT>(A, s, act, c0, lk, lane, d, acc);
+        hh_step_lds<P, PR, R, DAG, RECON, NB, 7, LT>(A, s, act, c0, lk, lane, d, acc);
     }
     epilogue<P, PR, R, EPI, PC, LA, CL>(A, j, act, any, c0, acc, CL ? sc : nullptr);
 }
@@ -1590,11 +1598,17 @@ hipError_t launch_t(const HopLaunch& L, hipStream_t st)
         if constexpr (R == 1) {
             if (L.lds == 2) {
                 static bool attr_x = false;
-                return launch(k_hop_lds<P, PR, R, DAG, EPI, RECON, PC, 0, true>, attr_x);
+                return launch(k_hop_lds<P, PR, R, DAG, EPI, RECON, PC, 0, true, false>, attr_x);
+            }
+        }
+        if constexpr (has_last_t<P, R, PC>()) {
+            if (L.last_t) {
+                static bool attr_t = false;
+                return launch(k_hop_lds<P, PR, R, DAG, EPI, RECON, PC, 0, false, true>, attr_t);
             }
         }
         static bool attr = false;
-        return launch(k_hop_lds<P, PR, R, DAG, EPI, RECON, PC, 0, false>, attr);
+        return launch(k_hop_lds<P, PR, R, DAG, EPI, RECON, PC, 0, false, false>, attr);
     }
     // L.bs = sites per workgroup (a multiple of 64); at most 512 threads per workgroup
     const int tpb = std::max(1, L.bs / kTile);

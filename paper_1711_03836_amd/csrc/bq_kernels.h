@@ -42,6 +42,7 @@ struct HopLaunch {
                              //    several column groups; 2: the same with one column per wave and the
                              //    x and y neighbour spinors exchanged between lanes
     int split = 0;           // 1: hop-split kernel, one workgroup per tile and column (R = 1; march and lds ignored)
+    int last_t = 0;          // 1: the tiles are walked down in t, slice by slice (the +t neighbour's last read)
     Geom g{};
     int parity = 0;          // output parity
     int ncol = 1;
