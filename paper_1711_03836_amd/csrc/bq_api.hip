@@ -574,8 +574,8 @@ static Tune get_tune(bq_context ctx, int prec, int ncol)
     return it != ctx->tune.end() ? it->second : default_tune(prec, ncol);
 }
 
-// One round of the hop-split kernel's workgroups on 256 CUs: two FP64 or four FP32/FP16 per CU by their
-// registers and LDS (one per tile and column).
+// Two rounds of the hop-split kernel's workgroups (one per tile and column) on 256 CUs, which by their
+// registers hold one FP64 or two FP32/FP16 of them at a time.
 static bool split_fits(const Geom& g, int prec, int nact) { return (long)g.ntiles * nact <= (prec == PREC_F64 ? 512 : 1024); }
 
 // The kernel of a launch whose configuration nobody chose, by tiles and columns (nact: the columns
@@ -586,7 +586,7 @@ static void pick_kernel(HopLaunch& L, const Geom& g, int nact, int& order)
     const long items = (long)g.ntiles * nact;
     const bool f64 = L.prec == PREC_F64, f16 = L.prec == PREC_F16;
     L.march = L.lds = 0;
-    // Within one round of its workgroups a launch is one chain of memory latencies and the hop split
+    // Within two rounds of its workgroups a launch is one or two chains of memory latencies and the hop split
     // shortens it (8^4: FP64 20.7 -> 10.6, FP32 x 8 43 -> 10.3; 12^3x24 FP32 x 3 20.7 -> 19.2);
     // beyond it the kernels that use fewer waves per site win (12^3x24 FP64 x 2 31.1 against 28.7,
     // FP32 x 4 25.3 against 24.8)
