@@ -770,7 +770,6 @@ static int tvr(const OpCall& c, int dag, int parity, FieldArg in, FieldArg v, Fi
         L.cg_rho = c.cg->rho;
         L.cg_alpha = c.cg->alpha;
         L.cg_pAp = c.cg->pAp;
-        L.cg_status = c.cg->status;
     }
     apply_cols(c, L, parity, false, fk);
     return run_hop(L, c.st);
@@ -855,7 +854,7 @@ struct Workspace {
     // scalars and partials
     DevBuf scal, ints, part;
     CgScalars cs{};
-    CgScalars cs2{};             // the states between the two iterations of a pair (cg_pair)
+    CgScalars cs2{};             // the states between the two iterations of a pair (cg_iterations)
     double* partial = nullptr;
     double* partial2 = nullptr;  // a second set, for partials written while the first is read
     double* dtmp = nullptr;  // ncol * 4 doubles for sums

@@ -523,9 +523,12 @@ __global__ __launch_bounds__(256) void k_cg_update_beta(SpinorPtr<PX> x, SpinorP
     const bool first = blockIdx.x == 0 && threadIdx.x == 0;
     const int st = cur.status[c];
     double rho = cur.rho[c], rmax2 = cur.rmax2[c];
-    if (st != COL_ACTIVE) {  // uniform over the workgroup
+    const double pAp = cur.pAp[c];
+    const bool broken = st == COL_ACTIVE && (!(pAp > 0.0) || !isfinite(pAp));
+    if (st != COL_ACTIVE || broken) {  // uniform over the workgroup
         if (first) {
-            next.status[c] = st;
+            // (a column that stopped in the last iteration has taken its last update of x)
+            next.status[c] = broken ? COL_FAILED : (st == COL_JUST_STOPPED ? COL_STOPPED : st);
             next.iters[c] = cur.iters[c];
             next.rho[c] = rho;
             next.rmax2[c] = rmax2;

@@ -405,7 +405,6 @@ struct Args {
     const double* cg_rho;
     double* cg_alpha;
     double* cg_pAp;
-    int* cg_status;
 };
 
 template <bool PC, class P, class PR>
@@ -547,7 +546,9 @@ __device__ __forceinline__ void hop_all(const Args<P, PR>& A, const Site& s, con
 
 // The scalars of a CG step whose stencil takes alpha itself (A.pap): every wavefront sums its column's
 // partials, in the order of block_sum (256 threads of a workgroup, here in four turns), so all get
-// the same alpha.
+// the same alpha.  No launch writes the states that it reads: whether the step broke down (pAp not
+// positive or not finite; alpha is 0 then, and r, which may hold NaN, is not read again) is for
+// k_cg_update_beta to see from pAp.
 __device__ __forceinline__ double wave_partials(const double* __restrict__ part, int n, int lane)
 {
     double s[4];
@@ -564,20 +565,12 @@ __device__ __forceinline__ double wave_partials(const double* __restrict__ part,
 template <class P, class PR>
 __device__ __forceinline__ double cg_alpha_of(const Args<P, PR>& A, int c, double pap, bool first)
 {
-    const bool ok = pap > 0.0 && isfinite(pap);
-    const double alpha = ok ? A.cg_rho[c] / pap : 0.0;
+    const double alpha = pap > 0.0 && isfinite(pap) ? A.cg_rho[c] / pap : 0.0;
     if (first) {
         A.cg_pAp[c] = pap;
         A.cg_alpha[c] = alpha;
-        if (!ok) A.cg_status[c] = COL_FAILED;  // the others' residuals stay as they are (alpha 0)
     }
     return alpha;
-}
-// a column that stopped in the last iteration has taken its last update of x
-template <class P, class PR>
-__device__ __forceinline__ void cg_mark_stopped(const Args<P, PR>& A, int c)
-{
-    if (c < A.ncol && A.cg_status[c] == COL_JUST_STOPPED) A.cg_status[c] = COL_STOPPED;
 }
 
 // Epilogue of one tile for R columns: the linear combination and clover factor the caller
@@ -628,8 +621,6 @@ __device__ __forceinline__ void epilogue(const Args<P, PR>& A, int j, const bool
             const bool first = j == 0;  // lane 0 of tile 0
             if (col_selected(A.status, A.statmask, c))
                 alpha[r] = cg_alpha_of(A, c, wave_partials(A.pap + (size_t)c * A.pstride, A.nwaves, lane), first);
-            else if (first)
-                cg_mark_stopped(A, c);
         }
     }
     if (any) {
@@ -1116,12 +1107,7 @@ __global__ __launch_bounds__(lds_max_threads<P>()) __attribute__((amdgpu_waves_p
         bool sel = false;
         for (int c = chunk * A.gw * R; c < (chunk + 1) * A.gw * R && c < A.ncol; c++)
             sel |= col_selected(A.status, A.statmask, c);
-        if (!sel) {
-            if constexpr (EPI == EPI_TVR)
-                if (A.pap && tile_at(A.g, lt) == 0 && threadIdx.x == 0)
-                    for (int c = chunk * A.gw * R; c < (chunk + 1) * A.gw * R; c++) cg_mark_stopped(A, c);
-            return;
-        }
+        if (!sel) return;
     }
     const int tile = tile_at(A.g, lt);                // lt < ntiles: one tile per workgroup
     const int base = tile * kTile;
@@ -1351,11 +1337,8 @@ __global__ __launch_bounds__(kSplitWaves * kTile) void k_hop_split(const Args<P,
     item_of(A.g, lb, A.nblk, A.nch, lt, c);
     c = __builtin_amdgcn_readfirstlane(c);
     const bool own_alpha = EPI == EPI_TVR && A.pap != nullptr;  // uniform over the launch
-    const bool first = lt == 0 && threadIdx.x == 0;             // writes the column's state
-    if (!col_selected(A.status, A.statmask, c)) {  // uniform over the workgroup
-        if (own_alpha && first) cg_mark_stopped(A, c);
-        return;
-    }
+    const bool first = lt == 0 && threadIdx.x == 0;             // writes the column's alpha
+    if (!col_selected(A.status, A.statmask, c)) return;         // uniform over the workgroup
     double pap = 0.0;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> kTileLog);
     const int lane = threadIdx.x & (kTile - 1);
@@ -1531,7 +1514,6 @@ hipError_t launch_t(const HopLaunch& L, hipStream_t st)
     A.cg_rho = L.cg_rho;
     A.cg_alpha = L.cg_alpha;
     A.cg_pAp = L.cg_pAp;
-    A.cg_status = L.cg_status;
     A.percol = L.percol;
     for (int c = 0; c < kMaxCols; c++) {
         A.cclov[c] = (const typename P::unit*)L.cclov[c];

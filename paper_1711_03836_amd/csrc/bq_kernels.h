@@ -62,12 +62,11 @@ struct HopLaunch {
     const void* cclov[kMaxCols] = {};
     double cf[kMaxCols] = {};
     // EPI_TVR, up to kFusedParts partials: alpha = cg_rho / (the sum of column c's nwaves partials at pap + c * pstride) is
-    // taken by the kernel itself, which also writes alpha, pAp and the states k_fin_alpha would
+    // taken by the kernel itself (0 if that sum is not positive and finite), which also writes alpha and pAp
     const double* pap = nullptr;
     const double* cg_rho = nullptr;
     double* cg_alpha = nullptr;
     double* cg_pAp = nullptr;
-    int* cg_status = nullptr;
 };
 
 hipError_t launch_hop(const HopLaunch& L, hipStream_t st);
@@ -268,9 +267,9 @@ struct CgScalars {
     int* restart;
     int* nrel;        // reliable updates per column
 };
-// launch_fin_beta and launch_cg_update in one, for up to kFusedParts partials per column: every workgroup
-// takes its column's sum itself; the states after the iteration go to `next` (its rho, rmax2, status
-// and iters; for every column)
+// launch_fin_beta and launch_cg_update in one, for up to kFusedParts partials per column, after a stencil that
+// took alpha itself: every workgroup takes its column's sum itself; the states after the iteration
+// go to `next` (its rho, rmax2, status and iters; for every column), also those that launch_fin_alpha would set
 constexpr int kFusedParts = 1024;
 hipError_t launch_cg_update_beta(int xprec, FieldArg x, int pprec, FieldArg p, int rprec, FieldArg r, int n, int ncol,
                                  const CgScalars& cur, const CgScalars& next, const double* partial, int nwaves,
