@@ -47,8 +47,8 @@ __device__ __forceinline__ void store_pairs(float2* b, int j, const float2 (&v)[
 }
 
 // Canonical links into the 18-real forms, with the largest distance from SU(3): per link max over
-// max_ab |(U U^dag - 1)_ab| and |det U - 1|, one partial maximum per workgroup (the host takes the
-// maximum of the partials).  One wavefront per tile, parity and direction, turned around in LDS as
+// max_ab |(U U^dag - 1)_ab| and |det U - 1|, infinite if an entry is not finite, one partial maximum per
+// workgroup (k_fin_max takes their maximum).  One wavefront per tile, parity and direction, turned around in LDS as
 // k_spinor_turn does (a link's 9 values are an odd number of 16-byte words already).  Bound by HBM:
 // reading the canonical links once for the check and once for each of five forms and two parities took
 // 1122 us at 24^3x48, now 161 (955 MB, 5.9 TB/s) and 122 in k_links_rows.
@@ -84,6 +84,9 @@ __global__ __launch_bounds__(4 * kTile) void k_links_take(const double2* __restr
             const double2 x = t[lane * 9 + e];
             u[e] = {x.x, x.y};
         }
+        double mag = 0.0;  // not finite if an entry is not (fmax below would drop a NaN)
+#pragma unroll
+        for (int e = 0; e < 9; e++) mag += fabs(u[e].re) + fabs(u[e].im);
         double2* db = d.p[par * 4 + mu];  // uniform over the wavefront
         float2* fb = f.p[par * 4 + mu];
         float2 v[9];
@@ -111,7 +114,7 @@ __global__ __launch_bounds__(4 * kTile) void k_links_take(const double2* __restr
         det = cmac(det, u[2], m2);
         det.re -= 1.0;
         dev = fmax(dev, sqrt(cnorm2(det)));
-        if (!isfinite(dev)) dev = INFINITY;
+        if (!isfinite(mag) || !isfinite(dev)) dev = INFINITY;
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) dev = fmax(dev, __shfl_xor(dev, off, 64));
@@ -453,15 +456,12 @@ __global__ void k_fin_sum(const double* partial, int nwaves, double* out)
     if (threadIdx.x == 0) out[c] = s;
 }
 
-// out[0] = the largest of n partial maxima (infinite if one is not a number)
+// out[0] = the largest of n partial maxima
 __global__ __launch_bounds__(256) void k_fin_max(const double* partial, int n, double* out)
 {
     __shared__ double w[4];
     double m = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) {
-        const double v = partial[i];
-        m = fmax(m, isnan(v) ? (double)INFINITY : v);
-    }
+    for (int i = threadIdx.x; i < n; i += 256) m = fmax(m, partial[i]);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
     if ((threadIdx.x & 63) == 0) w[threadIdx.x >> 6] = m;
