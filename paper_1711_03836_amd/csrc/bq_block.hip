@@ -254,10 +254,27 @@ __device__ void m_sub(Mat& C, const Mat& A, const Mat& B, int n)
     __syncthreads();
 }
 
+// a pivot d > 0 as 2^-e and the reciprocal of its mantissa, and v / d
+struct Pivot {
+    int e;
+    double inv;
+};
+__device__ __forceinline__ Pivot pivot(double d)
+{
+    const int e = ilogb(d);
+    return Pivot{-e, 1.0 / ldexp(d, -e)};
+}
+__device__ __forceinline__ double2 over(double2 v, const Pivot& p)
+{
+    return make_double2(ldexp(v.x, p.e) * p.inv, ldexp(v.y, p.e) * p.inv);
+}
+
 // X = G^-1 B for Hermitian positive definite G, padded with the identity (m_gather); X and W distinct from
 // each other and from G and B.  Elimination of [G | B] row by row in W and X (for such a G the pivots are
 // the squares of Cholesky's, and positive unless it breaks down), then back substitution: 2 n
-// short steps in which every lane has four entries of each matrix.  A step launch at 12 columns took
+// short steps in which every lane has four entries of each matrix.  Rows are divided by a pivot's exponent
+// and mantissa apart: the reciprocal of one below 2^-1022 (columns of norm 1e-154, and they shrink) would
+// be infinite.  A step launch at 12 columns took
 // 30 us with one column per lane, one product after the other, 20 with the columns in registers and
 // all loops unrolled (that code comes cold from memory every time), and takes 15 now.
 __device__ bool m_solve(Mat& X, const Mat& G, const Mat& B, int n, Mat& W)
@@ -272,7 +289,7 @@ __device__ bool m_solve(Mat& X, const Mat& G, const Mat& B, int n, Mat& W)
     for (int k = 0; k < n; k++) {
         const double d = W[k][k].x;  // the same on every lane
         if (!(d > 0.0) || !isfinite(d)) return false;
-        const double inv = 1.0 / d;
+        const Pivot p = pivot(d);
         const double2 wk = W[k][j], xk = X[k][j];
         double2 f[4], w[4], x[4];
 #pragma unroll
@@ -287,7 +304,7 @@ __device__ bool m_solve(Mat& X, const Mat& G, const Mat& B, int n, Mat& W)
         for (int q = 0; q < 4; q++) {
             const int i = i0 + 4 * q;
             if (i > k) {
-                const double2 g = cscal(inv, f[q]);
+                const double2 g = over(f[q], p);
                 if (j > k) W[i][j] = csub(w[q], cmul(g, wk));
                 X[i][j] = csub(x[q], cmul(g, xk));
             }
@@ -295,7 +312,7 @@ __device__ bool m_solve(Mat& X, const Mat& G, const Mat& B, int n, Mat& W)
         __syncthreads();
     }
     for (int k = n - 1; k >= 0; k--) {
-        const double2 xk = cscal(1.0 / W[k][k].x, X[k][j]);
+        const double2 xk = over(X[k][j], pivot(W[k][k].x));
         double2 f[4], x[4];
 #pragma unroll
         for (int q = 0; q < 4; q++) {
