@@ -357,7 +357,7 @@ int bq_time_copy(bq_context ctx, uint64_t bytes, int reps, void* stream, double*
 
 /* Stencil configuration (the project's autotuner; no counterpart in the paper) used for a given
  * precision and column count (set by
- * bq_autotune or explicitly; otherwise a default).  recon: 12 or 18 reals per
+ * bq_autotune or explicitly; otherwise the size of each launch picks the kernel).  recon: 12 or 18 reals per
  * link; R: columns per thread; bs: sites per workgroup (64, 128, 256 or 512;
  * the column groups of those sites run in the same workgroup, up to 512 threads).
  * march: 0, or the length of the time segments of the t-marching stencil, in
@@ -378,12 +378,13 @@ int bq_time_copy(bq_context ctx, uint64_t bytes, int reps, void* stream, double*
  * and, on a lattice with a multiple of 8 tile blocks, has each XCD walk its tile blocks once per column-group chunk
  * (fewer columns in flight per XCD; links and clover are read once per chunk).  Errors: BQ_ERR_INVALID for a configuration
  * that is not compiled or out of range.  Results do not depend on the configuration.
- * A configuration of the default's shape (R, bs, march, lds and order as bq_tune_get gives them when
- * nothing was set; either link form) names the default: the size of each launch picks its kernel, on
- * small lattices one with a workgroup of eight waves, one per half hop, for each tile and column. */
+ * R = 0 and bs = 0 (with march, lds and order 0), which is what bq_tune_get gives when nothing was set:
+ * the size of each launch picks its kernel, on small lattices one with a workgroup of eight waves,
+ * one per half hop, for each tile and column; recon is then the link form that it reads. */
 int bq_tune_get(bq_context ctx, int prec, int nrhs, int* recon, int* R, int* bs, int* march, int* lds, int* order);
 int bq_tune_set(bq_context ctx, int prec, int nrhs, int recon, int R, int bs, int march, int lds, int order);
-/* Time the candidate configurations for (op's lattice, prec, nrhs) on op and keep the fastest. */
+/* Time the candidate configurations for (op's lattice, prec, nrhs) on op, what the size would pick among
+ * them, and keep the fastest. */
 int bq_autotune(bq_op op, int prec, int nrhs);
 
 /* ---------------------------------------------------------------------------

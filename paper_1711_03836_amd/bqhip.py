@@ -220,7 +220,8 @@ class Context:
         return ms.value
 
     def tune_get(self, prec, nrhs):
-        """(recon, R, bs, march, lds, order) of the stencil for this precision and column count."""
+        """(recon, R, bs, march, lds, order) of the stencil for this precision and column count; R = bs = 0:
+        the size of each launch picks the kernel."""
         r, R, bs, m, l, o = C.c_int(), C.c_int(), C.c_int(), C.c_int(), C.c_int(), C.c_int()
         check(bq_tune_get(self.h, prec, nrhs, C.byref(r), C.byref(R), C.byref(bs), C.byref(m), C.byref(l),
                           C.byref(o)))

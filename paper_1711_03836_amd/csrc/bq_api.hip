@@ -105,14 +105,15 @@ static int fail(int code, const char* fmt, ...)
 // ---------------------------------------------------------------------------
 
 struct Tune {
-    int recon, R, bs;
+    int recon;
+    int R = 0, bs = 0;  // both 0: not chosen by the user or the autotuner, the launch's size picks the kernel
     int march = 0;  // > 0: t-marching stencil with segments of this many time planes, where the lattice allows
     int lds = 0;    // 1: tile-shared stencil (links and clover staged in LDS) for several column groups per tile;
                     // 2: with a lane exchange of x/y neighbours
     int order = 0;  // tile traversal of the plain and tile-shared stencils: 0 blocks of 4x4 (z,t) planes,
                     // 1 one slab per XCD walked slice by slice in t, 2 as 1 with the column-group
                     // chunks walked one after another on each XCD
-    bool chosen = false;  // set by the user or the autotuner; otherwise the launch's size picks the kernel
+    bool chosen() const { return bs != 0; }
 };
 
 // The walk of g by blocks of ub tiles x zb planes x tb time slices, planes of nu tiles (tile_at).
@@ -544,34 +545,10 @@ static int alloc_vec(bq_context ctx, const Geom& g, int prec, int nh, int ncol, 
 // kernel configuration
 // ---------------------------------------------------------------------------
 
-static int max_R(int prec) { return prec == PREC_F64 ? 2 : 4; }
-
-static Tune default_tune(int prec, int ncol)
-{
-    Tune t;
-    t.recon = prec == PREC_F16 ? 12 : 18;
-    t.bs = ncol > 1 ? 128 : 256;
-    t.R = 1;
-    for (int r = std::min(max_R(prec), ncol); r >= 1; r--)
-        if (ncol % r == 0) {
-            t.R = r;
-            break;
-        }
-    return t;
-}
-
-// The configuration as tune_set, a tuning file or the autotuner gives it.  One of the default's shape
-// names the default, in the link form it gives: the launch's size picks the kernel (pick_kernel).
-static Tune make_tune(int prec, int ncol, int recon, int R, int bs, int march, int lds, int order)
-{
-    const Tune d = default_tune(prec, ncol);
-    return Tune{recon, R, bs, march, lds, order, R != d.R || bs != d.bs || march != 0 || lds != 0 || order != 0};
-}
-
 static Tune get_tune(bq_context ctx, int prec, int ncol)
 {
     auto it = ctx->tune.find({prec, ncol});
-    return it != ctx->tune.end() ? it->second : default_tune(prec, ncol);
+    return it != ctx->tune.end() ? it->second : Tune{prec == PREC_F16 ? 12 : 18};
 }
 
 // Two rounds of the hop-split kernel's workgroups (one per tile and column) on 256 CUs, which by their
@@ -634,7 +611,7 @@ static HopLaunch hop_base(bq_op op, int prec, const Tune& t, int dagger, int out
     L.lds = t.lds;
     L.ncol = ncol;
     int order = t.order;
-    if (!t.chosen) pick_kernel(L, G->g, nact > 0 ? nact : ncol, order);
+    if (!t.chosen()) pick_kernel(L, G->g, nact > 0 ? nact : ncol, order);
     L.dagger = dagger;
     L.g = with_order(G->g, order);
     L.last_t = order >= 1;
@@ -2990,6 +2967,14 @@ int bq_tune_set(bq_context ctx, int prec, int nrhs, int recon, int R, int bs, in
 {
     if (!ctx) return fail(BQ_ERR_INVALID, "NULL argument");
     const int rprec = prec == PREC_F64 ? PREC_F64 : PREC_F32;
+    if (R == 0 && bs == 0) {  // leave the kernel to the launch's size
+        if (!hop_variant_exists(prec, rprec, recon, 1, EPI_TV) || nrhs < 1)
+            return fail(BQ_ERR_INVALID, "no kernel variant for prec %d recon %d (nrhs %d)", prec, recon, nrhs);
+        if (march != 0 || lds != 0 || order != 0)
+            return fail(BQ_ERR_INVALID, "march, lds and order must be 0 where R and bs are");
+        ctx->tune[{prec, nrhs}] = Tune{recon};
+        return BQ_OK;
+    }
     if (!hop_variant_exists(prec, rprec, recon, R, EPI_TV) || R > nrhs)
         return fail(BQ_ERR_INVALID, "no kernel variant for prec %d recon %d R %d (nrhs %d)", prec, recon, R, nrhs);
     if (bs != 64 && bs != 128 && bs != 256 && bs != 512 && !(lds && bs % 64 == 0 && bs <= 1024))
@@ -2998,7 +2983,7 @@ int bq_tune_set(bq_context ctx, int prec, int nrhs, int recon, int R, int bs, in
     if (lds < 0 || lds > 2) return fail(BQ_ERR_INVALID, "lds must be 0, 1 or 2");
     if (lds == 2 && R != 1) return fail(BQ_ERR_INVALID, "lds 2 (lane exchange) takes one column per thread");
     if (order < 0 || order > 2) return fail(BQ_ERR_INVALID, "order must be 0, 1 or 2");
-    ctx->tune[{prec, nrhs}] = make_tune(prec, nrhs, recon, R, bs, march, lds, order);
+    ctx->tune[{prec, nrhs}] = Tune{recon, R, bs, march, lds, order};
     return BQ_OK;
 }
 
@@ -3022,8 +3007,21 @@ int bq_autotune(bq_op op, int prec, int nrhs)
         double ms = 0;
         return bq_time_apply(op, BQ_OP_K1, fi, fo, reps, nullptr, &ms, nullptr) == BQ_OK ? ms : 1e300;
     };
-    // pass 1: every compiled configuration, a few launches each
+    // pass 1: what the launch's size picks (by name, so that the table says what runs; the hop-split
+    // kernel has none), then every compiled configuration, a few launches each
     std::vector<std::pair<double, Tune>> cand;
+    for (int recon : {12, 18}) {
+        if (!hop_variant_exists(prec, rprec, recon, 1, EPI_TINV)) continue;
+        if (recon == 12 && !op->gauge->get(prec, 12)) continue;  // not an SU(3) field
+        HopLaunch L;
+        L.prec = prec;
+        L.ncol = nrhs;
+        int order = 0;
+        pick_kernel(L, op->gauge->g, nrhs, order);
+        const Tune t = L.split ? Tune{recon} : Tune{recon, L.R, L.bs, 0, L.lds, order};
+        const double ms = time_of(t, 5);
+        if (ms < 1e300) cand.push_back({ms, t});
+    }
     // t-marching segments the lattice allows (whole tiles per (x,y) plane, segment | L_t)
     const Geom& g = op->gauge->g;
     std::vector<int> marches{0};
@@ -3036,7 +3034,7 @@ int bq_autotune(bq_op op, int prec, int nrhs)
                 for (int bs : {64, 128, 256, 512}) {
                     if (!hop_variant_exists(prec, rprec, recon, R, EPI_TINV)) continue;
                     if (recon == 12 && !op->gauge->get(prec, 12)) continue;  // not an SU(3) field
-                    const Tune t = make_tune(prec, nrhs, recon, R, bs, march, 0, 0);
+                    const Tune t = Tune{recon, R, bs, march, 0, 0};
                     const double ms = time_of(t, 5);
                     if (ms < 1e300) cand.push_back({ms, t});
                 }
@@ -3053,7 +3051,7 @@ int bq_autotune(bq_op op, int prec, int nrhs)
                     if (waves > G && waves != 4) continue;  // bs / 64 is only a bound on the waves
                     if (mode == 2 && (R != 1 || waves < std::min(G, 16))) continue;
                     if (prec == PREC_F64 && R > 1) continue;  // spills under the 768-thread bound of FP64
-                    const Tune t = make_tune(prec, nrhs, recon, R, 64 * waves, 0, mode, 0);
+                    const Tune t = Tune{recon, R, 64 * waves, 0, mode, 0};
                     const double ms = time_of(t, 5);
                     if (ms < 1e300) cand.push_back({ms, t});
                 }
@@ -3062,8 +3060,8 @@ int bq_autotune(bq_op op, int prec, int nrhs)
         return fail(BQ_ERR_DEVICE, "no kernel configuration could be timed");
     }
     // pass 2: the configurations within 10% of the fastest, timed again over more launches; of those
-    // within 2% of the new fastest the first in candidate order wins (plain and marching kernels by
-    // (march, recon, R, bs), then the tile-shared ones), so near-ties resolve the same way from run to run
+    // within 2% of the new fastest the first in candidate order wins (the size's pick, plain and marching
+    // kernels by (march, recon, R, bs), then the tile-shared ones), so near-ties resolve the same way from run to run
     double best = 1e300;
     for (auto& c : cand) best = std::min(best, c.first);
     std::vector<std::pair<double, Tune>> fin;
@@ -3079,7 +3077,7 @@ int bq_autotune(bq_op op, int prec, int nrhs)
         }
     // pass 3: the winner in the other traversals (slabs per XCD; and those with the column-group
     // chunks one after another per XCD), kept if 2% faster
-    if (bt.chosen && bt.march == 0) {
+    if (bt.chosen() && bt.march == 0) {
         double tb = time_of(bt, 20);
         const Tune base = bt;
         for (int order : {1, 2}) {

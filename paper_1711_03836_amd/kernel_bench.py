@@ -28,7 +28,7 @@ def main():
     ap.add_argument("--nrhs", type=int, default=12)
     ap.add_argument("--kind", default="K1", help="an operator kind (K1, MHAT, ...) or SOLVE")
     ap.add_argument("--reps", type=int, default=20)
-    ap.add_argument("--tune", default="auto", help="'auto' or recon,R,bs[,march[,lds[,order]]]")
+    ap.add_argument("--tune", default="auto", help="'auto' (timed) or recon,R,bs[,march[,lds[,order]]]; recon,0,0: by size")
     ap.add_argument("--eps", type=float, default=0.2)
     ap.add_argument("--kappa", type=float, default=0.124)
     ap.add_argument("--csw", type=float, default=1.5)
