@@ -168,7 +168,9 @@ typedef void (*bq_dealloc_fn)(void* ptr, void* alloc_ctx);
  *                     device's free memory); an allocation above it fails with BQ_ERR_OOM.
  *                     Without a caller's allocator, blocks that buffers give back are kept for
  *                     the next buffers of their size (at most 8 GiB and an eighth of the budget,
- *                     within the budget) until the context is freed or an allocation needs room.
+ *                     within the budget; the longest unused make room for others) until the
+ *                     context is freed, bq_context_trim is called, an allocation of the
+ *                     library needs room or a context is created with a budget of 0.
  *   alloc, dealloc    route every device allocation of the context (fields, links, clover,
  *                     workspaces) through the caller's allocator; both NULL = hipMalloc/hipFree.
  *                     Before a block goes back to dealloc the library waits for the device
@@ -184,7 +186,12 @@ int bq_context_create(int device, uint64_t hbm_budget_bytes, bq_alloc_fn alloc, 
  * context is freed together with the last of them (so handles may be freed in any order).
  * NULL is a no-op. */
 int bq_context_destroy(bq_context ctx);
-/* Bytes of device memory the context currently holds (its own accounting, padding included). */
+/* Give the blocks that the context keeps for its next buffers back to the device, for another
+ * allocator in the process or another process to use; waits for the device if there are any.
+ * May be called while another thread uses the context.  Errors: BQ_ERR_INVALID (NULL). */
+int bq_context_trim(bq_context ctx);
+/* Bytes of device memory the context currently holds (its own accounting, padding included; without
+ * the blocks that it keeps for its next buffers). */
 int bq_context_hbm_used(bq_context ctx, uint64_t* used);
 
 /* Upload the gauge links U_mu(x) of Eq. 1 (section "Fermion actions").

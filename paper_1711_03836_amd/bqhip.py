@@ -95,6 +95,7 @@ _sig = {
     "bq_last_error": (C.c_char_p, []),
     "bq_context_create": (C.c_int, [C.c_int, C.c_uint64, ALLOC_FN, DEALLOC_FN, C.c_void_p, _P(_h)]),
     "bq_context_destroy": (C.c_int, [_h]),
+    "bq_context_trim": (C.c_int, [_h]),
     "bq_context_hbm_used": (C.c_int, [_h, _P(C.c_uint64)]),
     "bq_gauge_upload": (C.c_int, [_h, _P(C.c_int), C.c_void_p, C.c_int, C.c_int, _P(_h)]),
     "bq_gauge_plaquette": (C.c_int, [_h, _P(C.c_double)]),
@@ -207,6 +208,10 @@ class Context:
             self._afn, self._dfn = ALLOC_FN(), DEALLOC_FN()
         check(bq_context_create(int(device), int(hbm_budget), self._afn, self._dfn, None, C.byref(h)))
         self.h = h
+
+    def trim(self):
+        """Give the device blocks kept for the context's next buffers back (to torch, say)."""
+        check(bq_context_trim(self.h))
 
     def hbm_used(self):
         v = C.c_uint64()

@@ -173,14 +173,35 @@ static Geom with_order(Geom g, int order)
 // block and hipFree, which waits for the device, cost more than the work of many calls: a 24^3x48
 // FP64 Mhat^dag Mhat took 1.1 ms, 0.56 ms of it in its stencils, and a 32^3x64 12-column FP32 one
 // between 7.5 and 113 ms.  The pool holds at most kPoolMost bytes, an eighth of the budget and
-// what the budget leaves; it is given back when an allocation fails anywhere in the process, when
-// the budget needs it, and with the context.
-struct BlockPool {
+// what the budget leaves; a block that comes back to a full pool takes the place of the longest unused
+// ones.  All of it is given back by bq_context_trim, with the context, when an allocation fails in any
+// context, and before a new context asks for its budget how much memory is free; as much as is
+// needed where the budget needs it.
+class BlockPool {
     static const size_t kPoolMost = (size_t)8 << 30;
     std::mutex mu;
-    std::multimap<size_t, void*> idle;  // by size
+    std::map<std::pair<size_t, uint64_t>, void*> idle;  // (size, turn) -> block
+    std::map<uint64_t, size_t> age;                     // turn -> size, the longest unused block first
+    uint64_t turns = 0;
     size_t bytes = 0;
     bool dirty = false;  // a block may still be in use by work queued before it came back
+    void drop_to(size_t most)
+    {
+        if (bytes <= most) return;
+        int cur = device;
+        (void)hipGetDevice(&cur);
+        if (cur != device) (void)hipSetDevice(device);
+        while (bytes > most) {
+            const auto it = idle.find({age.begin()->second, age.begin()->first});
+            (void)hipFree(it->second);  // waits for the device
+            bytes -= it->first.first;
+            idle.erase(it);
+            age.erase(age.begin());
+        }
+        if (cur != device) (void)hipSetDevice(cur);
+    }
+
+public:
     int device = 0;
     BlockPool();
     ~BlockPool();
@@ -189,41 +210,39 @@ struct BlockPool {
     void* take(size_t n)
     {
         std::lock_guard<std::mutex> lk(mu);
-        auto it = idle.find(n);
-        if (it == idle.end()) return nullptr;
+        const auto it = idle.lower_bound({n, 0});
+        if (it == idle.end() || it->first.first != n) return nullptr;
         if (dirty) {
             if (hipDeviceSynchronize() != hipSuccess) return nullptr;
             dirty = false;
         }
         void* p = it->second;
         bytes -= n;
+        age.erase(it->first.second);
         idle.erase(it);
         return p;
     }
-    // keep a block (done: no queued work uses it any more); false if there is no room for it
+    // keep a block (done: no queued work uses it any more); false if it is larger than the pool may be
     bool put(void* p, size_t n, size_t most, bool done)
     {
         std::lock_guard<std::mutex> lk(mu);
-        if (bytes + n > std::min(most, kPoolMost)) return false;
-        idle.emplace(n, p);
+        most = std::min(most, kPoolMost);
+        if (n > most) return false;
+        drop_to(most - n);
+        idle[{n, turns}] = p;
+        age[turns++] = n;
         bytes += n;
         dirty = dirty || !done;
         return true;
     }
-    void trim()
+    // give back what is beyond `most` bytes
+    void shrink(size_t most)
     {
         std::lock_guard<std::mutex> lk(mu);
-        int cur = device;
-        (void)hipGetDevice(&cur);
-        if (cur != device) (void)hipSetDevice(device);
-        for (auto& b : idle) (void)hipFree(b.second);  // waits for the device
-        if (cur != device) (void)hipSetDevice(cur);
-        idle.clear();
-        bytes = 0;
-        dirty = false;
+        drop_to(most);
     }
 };
-// every context's pool, so that an allocation that fails can have all of them given back
+// every context's pool, so that one context can have all of them given back
 static std::mutex pools_mu;
 static std::set<BlockPool*> pools;
 BlockPool::BlockPool()
@@ -237,12 +256,12 @@ BlockPool::~BlockPool()
         std::lock_guard<std::mutex> lk(pools_mu);
         pools.erase(this);
     }
-    trim();
+    shrink(0);
 }
 static void trim_pools()
 {
     std::lock_guard<std::mutex> lk(pools_mu);
-    for (BlockPool* p : pools) p->trim();
+    for (BlockPool* p : pools) p->shrink(0);
 }
 
 struct bq_context_s {
@@ -327,7 +346,7 @@ struct DevBuf {
                 return fail(BQ_ERR_INVALID, "the caller's allocator returned a block not aligned to 256 bytes");
             }
         } else if ((raw = c->pool.take(total)) == nullptr) {
-            if (c->used + total + c->pool.bytes > c->budget) c->pool.trim();
+            c->pool.shrink(c->budget - c->used - total);
             e = hipMalloc(&raw, total);
             if (e == hipErrorOutOfMemory) {
                 (void)hipGetLastError();
@@ -1811,6 +1830,7 @@ int bq_context_create(int device, uint64_t hbm_budget_bytes, bq_alloc_fn alloc, 
     auto c = std::make_unique<bq_context_s>();
     c->device = c->pool.device = device;
     size_t fr = 0, tot = 0;
+    if (!hbm_budget_bytes) trim_pools();  // blocks that other contexts keep count as free
     HIPCHK(hipMemGetInfo(&fr, &tot));
     c->budget = hbm_budget_bytes ? hbm_budget_bytes : (uint64_t)(0.9 * (double)fr);
     c->alloc = alloc;
@@ -1839,6 +1859,13 @@ int bq_context_hbm_used(bq_context ctx, uint64_t* used)
 {
     if (!ctx || !used) return fail(BQ_ERR_INVALID, "NULL argument");
     *used = ctx->used;
+    return BQ_OK;
+}
+
+int bq_context_trim(bq_context ctx)
+{
+    if (!ctx) return fail(BQ_ERR_INVALID, "NULL argument");
+    ctx->pool.shrink(0);
     return BQ_OK;
 }
 
