@@ -1592,8 +1592,9 @@ hipError_t launch_t(const HopLaunch& L, hipStream_t st)
         static bool attr = false;
         return launch(k_hop_lds<P, PR, R, DAG, EPI, RECON, PC, 0, false, false>, attr);
     }
-    // L.bs = sites per workgroup (a multiple of 64); at most 512 threads per workgroup
-    const int tpb = std::max(1, L.bs / kTile);
+    // L.bs = sites per workgroup (a multiple of 64); at most 512 threads per workgroup (a tile-shared
+    // configuration, whose bs may be larger, comes here when a tile has one column group)
+    const int tpb = std::max(1, std::min(L.bs, 512) / kTile);
     A.tpb = tpb;
     A.gw = std::max(1, std::min(G, 512 / (tpb * kTile)));
     A.nch = (G + A.gw - 1) / A.gw;

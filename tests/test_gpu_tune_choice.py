@@ -56,3 +56,20 @@ def test_autotuned_entry_names_its_kernel(dims):
     assert t[1:] == (0,) * 5 or t[1] > 0 and t[2] >= 64
     if np.prod(dims) // 128 * n > 1024:  # beyond the hop split every kernel has a name
         assert t[1] > 0
+
+
+@pytest.mark.parametrize("prec,recon,R,bs", [(0, 18, 1, 768), (1, 18, 1, 1024), (1, 12, 2, 768), (2, 12, 1, 576)])
+def test_tile_shared_with_one_column_group(prec, recon, R, bs):
+    """As many columns as a thread has: nothing to share, so the plain kernel runs, within its 512 threads."""
+    from paper_1711_03836_amd import bqhip as bq
+    dims = (6, 10, 14, 18)  # 119 tiles: not a multiple of the 8 of a workgroup
+    ctx = bq.Context(0)
+    op = bq.Op(bq.Gauge(ctx, dims, inputs.gauge_field(dims, 0.2, seed=78), -1), 0.12, 1.5, 0.1)
+    fi, fo = bq.Field(ctx, dims, bq.BQ_ODD, prec, R), bq.Field(ctx, dims, bq.BQ_ODD, prec, R)
+    fi.put(inputs.gaussian_spinor(dims, R, seed=79))
+    got = []
+    for t in ((recon, 1, 64), (recon, R, bs, 0, 1)):
+        ctx.tune_set(prec, R, *t)
+        op.apply(bq.BQ_OP_MHATDAG_MHAT, fi, fo)
+        got.append(fo.get())
+    assert np.array_equal(*got)
