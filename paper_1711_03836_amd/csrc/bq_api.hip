@@ -572,21 +572,20 @@ static Tune get_tune(bq_context ctx, int prec, int ncol)
 
 // Two rounds of the hop-split kernel's workgroups (one per tile and column) on 256 CUs, which by their
 // registers hold one FP64 or two FP32/FP16 of them at a time.
-static bool split_fits(const Geom& g, int prec, int nact) { return (long)g.ntiles * nact <= (prec == PREC_F64 ? 512 : 1024); }
+static bool split_fits(const Geom& g, int prec, int n) { return (long)g.ntiles * n <= (prec == PREC_F64 ? 512 : 1024); }
 
-// The kernel of a launch whose configuration nobody chose, by tiles and columns (nact: the columns
-// that are worked on).  Times are of Mhat (K1 + K2, 18-real links; FP16 12) in us on one MI355X.
-static void pick_kernel(HopLaunch& L, const Geom& g, int nact, int& order)
+// The kernel of a launch whose configuration nobody chose, by tiles and columns.  Times are of Mhat (K1 + K2, 18-real links; FP16 12) in us on one MI355X.
+static void pick_kernel(HopLaunch& L, const Geom& g, int& order)
 {
     const int n = L.ncol;
-    const long items = (long)g.ntiles * nact;
+    const long items = (long)g.ntiles * n;
     const bool f64 = L.prec == PREC_F64, f16 = L.prec == PREC_F16;
     L.march = L.lds = 0;
     // Within two rounds of its workgroups a launch is one or two chains of memory latencies and the hop split
     // shortens it (8^4: FP64 20.7 -> 10.6, FP32 x 8 43 -> 10.3; 12^3x24 FP32 x 3 20.7 -> 19.2);
     // beyond it the kernels that use fewer waves per site win (12^3x24 FP64 x 2 31.1 against 28.7,
     // FP32 x 4 25.3 against 24.8)
-    if (split_fits(g, L.prec, nact)) {
+    if (split_fits(g, L.prec, n)) {
         L.split = 1;
         L.R = 1;
         return;
@@ -613,35 +612,6 @@ static void pick_kernel(HopLaunch& L, const Geom& g, int nact, int& order)
     const bool many = items > 4096;
     L.R = std::min(n, f64 ? (many ? 1 : 2) : f16 ? (n > 4 ? 2 : 1) : (many ? 2 : 1));
     L.bs = f64 && n > 1 ? 128 : 64;
-}
-
-// hop launch skeleton for op, precision and tune
-static HopLaunch hop_base(bq_op op, int prec, const Tune& t, int dagger, int out_parity, int ncol, int nact = 0)
-{
-    HopLaunch L;
-    const bq_gauge G = op->gauge;
-    L.prec = prec;
-    L.rprec = prec == PREC_F64 ? PREC_F64 : PREC_F32;
-    // two-row links exist only for SU(3) fields (bq_gauge_upload); FP64/FP32 fall back to 18 reals
-    L.recon = (t.recon == 12 && prec != PREC_F16 && !G->get(prec, 12)) ? 18 : t.recon;
-    L.R = std::min(t.R, std::max(ncol, 1));
-    L.bs = t.bs;
-    L.march = (t.march > 0 && G->g.blocked && G->g.L[3] % t.march == 0) ? t.march : 0;
-    L.lds = t.lds;
-    L.ncol = ncol;
-    int order = t.order;
-    if (!t.chosen()) pick_kernel(L, G->g, nact > 0 ? nact : ncol, order);
-    L.dagger = dagger;
-    L.g = with_order(G->g, order);
-    L.last_t = order >= 1;
-    L.parity = out_parity;
-    const LinkSet* ls = G->get(prec, L.recon);
-    for (int k = 0; k < 8; k++) L.U[k] = ls ? ls->U[k] : nullptr;
-    const double ep = std::exp(op->mu), em = std::exp(-op->mu);
-    L.ef = dagger ? em : ep;
-    L.eb = dagger ? ep : em;
-    L.tbc = G->t_bc;
-    return L;
 }
 
 static int run_hop(const HopLaunch& L, hipStream_t st)
@@ -682,10 +652,41 @@ struct OpCall {
     int statmask = 1;
     hipStream_t st;
     const ColTable* ct = nullptr;
-    int nact = 0;  // columns in use, where they are fewer than ncol (0: all)
+    int used = 0;  // the columns in use are among the first `used` (0: all of ncol)
     const double* pap = nullptr;     // tvr takes alpha from these partials and cg's states itself
     const CgScalars* cg = nullptr;   // (not in marching or lane-exchange launches)
 };
+
+// hop launch skeleton of a call
+static HopLaunch hop_base(const OpCall& c, int dagger, int out_parity)
+{
+    HopLaunch L;
+    const bq_gauge G = c.op->gauge;
+    const int prec = c.prec;
+    const Tune& t = c.t;
+    L.prec = prec;
+    L.rprec = prec == PREC_F64 ? PREC_F64 : PREC_F32;
+    // two-row links exist only for SU(3) fields (bq_gauge_upload); FP64/FP32 fall back to 18 reals
+    L.recon = (t.recon == 12 && prec != PREC_F16 && !G->get(prec, 12)) ? 18 : t.recon;
+    L.ncol = c.used > 0 ? c.used : c.ncol;
+    L.R = std::min(t.R, std::max(L.ncol, 1));
+    L.bs = t.bs;
+    L.march = (t.march > 0 && G->g.blocked && G->g.L[3] % t.march == 0) ? t.march : 0;
+    L.lds = t.lds;
+    int order = t.order;
+    if (!t.chosen()) pick_kernel(L, G->g, order);
+    L.dagger = dagger;
+    L.g = with_order(G->g, order);
+    L.last_t = order >= 1;
+    L.parity = out_parity;
+    const LinkSet* ls = G->get(prec, L.recon);
+    for (int k = 0; k < 8; k++) L.U[k] = ls ? ls->U[k] : nullptr;
+    const double ep = std::exp(c.op->mu), em = std::exp(-c.op->mu);
+    L.ef = dagger ? em : ep;
+    L.eb = dagger ? ep : em;
+    L.tbc = G->t_bc;
+    return L;
+}
 
 // switch a launch to per-column operators: clover per column (parity `par`, inverse or not), f by mode
 static void apply_cols(const OpCall& c, HopLaunch& L, int par, bool inverse, int fk)
@@ -709,7 +710,7 @@ static void apply_cols(const OpCall& c, HopLaunch& L, int par, bool inverse, int
 static int k1(const OpCall& c, int dag, FieldArg in_o, FieldArg out_e, FieldArg v_e = FieldArg(), double a = 0,
               double f = 1, int fk = FK_CONST)
 {
-    HopLaunch L = hop_base(c.op, c.prec, c.t, dag, 0, c.ncol, c.nact);
+    HopLaunch L = hop_base(c, dag, 0);
     L.epi = EPI_TINV;
     L.in = in_o;
     L.out = out_e;
@@ -727,7 +728,7 @@ static int k1(const OpCall& c, int dag, FieldArg in_o, FieldArg out_e, FieldArg 
 static int tv(const OpCall& c, int dag, int parity, FieldArg in, FieldArg v, FieldArg out, double f, double* partial,
               int nwaves, int pstride, int fk = FK_CONST)
 {
-    HopLaunch L = hop_base(c.op, c.prec, c.t, dag, parity, c.ncol, c.nact);
+    HopLaunch L = hop_base(c, dag, parity);
     L.epi = EPI_TV;
     L.in = in;
     L.v = v;
@@ -747,7 +748,7 @@ static int tv(const OpCall& c, int dag, int parity, FieldArg in, FieldArg v, Fie
 static int tvr(const OpCall& c, int dag, int parity, FieldArg in, FieldArg v, FieldArg rin, FieldArg rout, double f,
                const double* alpha, double* partial, int nwaves, int pstride, int fk = FK_CONST)
 {
-    HopLaunch L = hop_base(c.op, c.prec, c.t, dag, parity, c.ncol, c.nact);
+    HopLaunch L = hop_base(c, dag, parity);
     L.epi = EPI_TVR;
     L.in = in;
     L.v = v;
@@ -775,7 +776,7 @@ static int tvr(const OpCall& c, int dag, int parity, FieldArg in, FieldArg v, Fi
 static int hopv(const OpCall& c, int dag, int parity, FieldArg in, FieldArg out, FieldArg v, double a, double f,
                 int fk = FK_CONST)
 {
-    HopLaunch L = hop_base(c.op, c.prec, c.t, dag, parity, c.ncol, c.nact);
+    HopLaunch L = hop_base(c, dag, parity);
     L.epi = EPI_HOP;
     L.in = in;
     L.out = out;
@@ -793,7 +794,7 @@ static int hopv(const OpCall& c, int dag, int parity, FieldArg in, FieldArg out,
 static int hop_coef(const OpCall& c, int parity, FieldArg in, FieldArg out, FieldArg v, double a, double f, double ef,
                     double eb)
 {
-    HopLaunch L = hop_base(c.op, c.prec, c.t, 0, parity, c.ncol, c.nact);
+    HopLaunch L = hop_base(c, 0, parity);
     L.epi = EPI_HOP;
     L.in = in;
     L.out = out;
@@ -861,7 +862,7 @@ struct Workspace {
     int graph_chunk = 0;
     double graph_delta2 = -1;
     const ColTable* ct = nullptr;  // per-column operators (server sessions)
-    int nact = 0;                  // columns in use (server sessions; 0: all)
+    int used = 0;                  // the columns in use are among the first `used` (server sessions; 0: all)
     ~Workspace()
     {
         if (graph) (void)hipGraphExecDestroy(graph);
@@ -1001,7 +1002,7 @@ static int cg_iteration(bq_op op, Workspace* w, int prec, hipStream_t st)
     const int n = w->xs.sites();
     OpCall c{op, prec, get_tune(ctx, prec, w->ncol), w->ncol, w->cs.status, kIterMask, st};
     c.ct = w->ct;
-    c.nact = w->nact;
+    c.used = w->used;
     CHK(op_fwd(c, w->full, w->ps, w->qs, w->ts, w->partial, w->hw));
     HIPCHK(launch_fin_alpha(w->cs, w->partial, w->pstride, w->ncol, st));
     CHK(op_dag_r(c, w->full, w->qs, w->ts, w->rs, w->rs, w->cs.alpha, w->partial, w->hw));
@@ -1020,7 +1021,7 @@ static int cg_iteration_fused(bq_op op, Workspace* w, int prec, const CgScalars&
     bq_context ctx = op->gauge->ctx;
     OpCall c{op, prec, get_tune(ctx, prec, w->ncol), w->ncol, cur.status, kIterMask, st};
     c.ct = w->ct;
-    c.nact = w->nact;
+    c.used = w->used;
     CHK(op_fwd(c, 0, w->ps, w->qs, w->ts, w->partial, w->hw));
     c.pap = w->partial;
     c.cg = &cur;
@@ -1057,7 +1058,7 @@ static int true_residual(bq_op op, Workspace* w, const int* status, int statmask
     bq_context ctx = op->gauge->ctx;
     OpCall c{op, PREC_F64, get_tune(ctx, PREC_F64, w->ncol), w->ncol, status, statmask, st};
     c.ct = w->ct;
-    c.nact = w->nact;
+    c.used = w->used;
     CHK(op_fwd(c, w->full, w->x, w->q64, w->t64, nullptr, w->hw));
     return op_dag_r(c, w->full, w->q64, w->t64, w->bp, w->r, nullptr, w->partial, w->hw);
 }
@@ -3044,7 +3045,7 @@ int bq_autotune(bq_op op, int prec, int nrhs)
         L.prec = prec;
         L.ncol = nrhs;
         int order = 0;
-        pick_kernel(L, op->gauge->g, nrhs, order);
+        pick_kernel(L, op->gauge->g, order);
         const Tune t = L.split ? Tune{recon} : Tune{recon, L.R, L.bs, 0, L.lds, order};
         const double ms = time_of(t, 5);
         if (ms < 1e300) cand.push_back({ms, t});
@@ -3280,6 +3281,15 @@ static int session_for(bq_server S, const Request* q, Session** out, Session** f
 static int* dsel(Session* s) { return s->dflags.as<int>(); }
 static double* dtol2(Session* s) { return (double*)(s->dflags.as<int>() + s->cap); }
 
+// The slots that stencils have to cover: up to the highest in use (requests take the lowest free ones)
+static int slots_in_use(const Session* s)
+{
+    int n = 0;
+    for (int c = 0; c < s->cap; c++)
+        if (s->slot[c]) n = c + 1;
+    return n;
+}
+
 static int admit(bq_server S, Request* q, Session* s)
 {
     bq_context ctx = S->ctx;
@@ -3320,7 +3330,6 @@ static int admit(bq_server S, Request* q, Session* s)
             k++;
         }
     s->used += q->nrhs;
-    s->w.nact = s->used;
     q->sess = s;
     q->state = REQ_RUNNING;
     return BQ_OK;
@@ -3332,13 +3341,13 @@ static int prepare_new(Session* s)
     const int cap = s->cap;
     Workspace* w = &s->w;
     hipStream_t st = s->st;
-    w->nact = s->used;
+    w->used = slots_in_use(s);
     HIPCHK(hipMemcpyAsync(s->dflags.p, s->hflags, sizeof(int) * cap + sizeof(double) * cap, hipMemcpyHostToDevice, st));
     HIPCHK(launch_set_status(w->cs.status, dsel(s), cap, COL_NEW, st));
     const int m = 1 << COL_NEW;
     OpCall c64{&s->stub, PREC_F64, get_tune(s->g->ctx, PREC_F64, cap), cap, w->cs.status, m, st};
     c64.ct = &s->ct;
-    c64.nact = w->nact;
+    c64.used = w->used;
     const void* tinv[kMaxCols];
     for (int c = 0; c < cap; c++) tinv[c] = s->ct.Tinv[PREC_F64][0][c];
     HIPCHK(launch_clover_apply(PREC_F64, s->g->g, nullptr, s->bfull.half(0), w->t64.all(), cap, st, tinv, w->cs.status, m));
@@ -3372,6 +3381,7 @@ static int retire(bq_server S, Session* s, std::vector<Request*>& done)
     for (Request* q : done)
         for (int c : q->slots) s->hflags[c] = 1;
     HIPCHK(hipMemcpyAsync(s->dflags.p, s->hflags, sizeof(int) * cap, hipMemcpyHostToDevice, st));
+    w->used = slots_in_use(s);  // those of `done` among them
     const int n = w->x.sites();
     // columns that stopped on maxiter still hold an inner iterate: fold it in (it is 0 for
     // columns that converged, whose last reliable update folded it)
@@ -3386,7 +3396,7 @@ static int retire(bq_server S, Session* s, std::vector<Request*>& done)
     HIPCHK(launch_convert(PREC_F64, w->x.all(), PREC_F64, s->xfull.half(1), n, cap, w->cs.status, m, st));
     OpCall c64{&s->stub, PREC_F64, get_tune(s->g->ctx, PREC_F64, cap), cap, w->cs.status, m, st};
     c64.ct = &s->ct;
-    c64.nact = w->nact;
+    c64.used = w->used;
     CHK(k1(c64, 0, s->xfull.half(1), s->xfull.half(0), s->bfull.half(0), 1.0, 0.0, FK_KAPPA));
     // |b - M x|^2 on the full lattice (t64 and q64 as even / odd scratch) and |b|^2
     const int hw = w->hw;
@@ -3650,7 +3660,7 @@ static int launch_idle(bq_server S)
         Session* s = sp.get();
         if (s->busy || s->used == 0) continue;
         Workspace* w = &s->w;
-        w->nact = s->used;
+        w->used = slots_in_use(s);
         w->cs.delta2 = s->prec == PREC_F64 ? 0.0 : 0.01;  // reliable-update threshold delta = 0.1
         CHK(chunk(&s->stub, w, s->prec, S->chunk, s->st));
         HIPCHK(hipMemcpyAsync(w->h_status, w->cs.status, sizeof(int) * 4 * s->cap, hipMemcpyDeviceToHost, s->st));
