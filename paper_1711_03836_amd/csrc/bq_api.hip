@@ -574,8 +574,10 @@ static Tune get_tune(bq_context ctx, int prec, int ncol)
 // registers hold one FP64 or two FP32/FP16 of them at a time.
 static bool split_fits(const Geom& g, int prec, int n) { return (long)g.ntiles * n <= (prec == PREC_F64 ? 512 : 1024); }
 
-// The kernel of a launch whose configuration nobody chose, by tiles and columns.  Times are of Mhat (K1 + K2, 18-real links; FP16 12) in us on one MI355X.
-static void pick_kernel(HopLaunch& L, const Geom& g, int& order)
+// The kernel of a launch whose configuration nobody chose, by tiles and columns (percol: each
+// with a clover of its own).  Times are of Mhat (K1 + K2, 18-real links; FP16 12) in us on one MI355X,
+// with percol of a request in a 16-slot session solved to 1e-10, in ms.
+static void pick_kernel(HopLaunch& L, const Geom& g, bool percol, int& order)
 {
     const int n = L.ncol;
     const long items = (long)g.ntiles * n;
@@ -598,7 +600,11 @@ static void pick_kernel(HopLaunch& L, const Geom& g, int& order)
     // From these column counts on, links and clover read once per tile into LDS beat reading them
     // per wave (32^3x64: FP64 x 3 1442 against 1572, x 2 1307 against 1176; FP32 x 6 1176 against
     // 1211, x 5 1100 against 1077; FP16 x 8 967 against 1015, x 6 852 against 770)
-    if (n >= (f64 ? 3 : f16 ? 8 : 6)) {
+    // With percol the clover, most of what a column reads, is not shared, and links that caches hold are as
+    // soon read again: FP32 x 8 on 16^3x32 34.6 against 30.9, x 16 65.0 and 59.7, on 24^3x48 167 and 173, 324 and
+    // 354; FP64 x 16 on 12^3x24 29.2 and 28.5, on 16^3x32 89.1 and 95.2; FP16 x 16 16.9 and 17.9, 46.3 and 47.5
+    const int least = !percol || f16 ? 0 : f64 ? 1024 : 4096;  // tiles
+    if (n >= (f64 ? 3 : f16 ? 8 : 6) && g.ntiles >= least) {
         L.lds = 1;
         L.R = 1;
         L.bs = 768;
@@ -608,9 +614,11 @@ static void pick_kernel(HopLaunch& L, const Geom& g, int& order)
     // Two columns per wave halve the link reads but also the waves: worth it beyond 4096 one-column
     // waves, four per SIMD (FP32 x 2: 16^3x32 43 against 33.3, 32^3x64 535 against 661), not for
     // FP64, which then runs two waves per SIMD (32^3x64 x 2: 1335 against 1176), nor for FP16, whose
-    // links are half as large, below five columns (24^3x48 x 4: 169 against 165; x 6: 254 against 269)
+    // links are half as large, below five columns (24^3x48 x 4: 169 against 165; x 6: 254 against 269), and
+    // with percol, where there is less to share, for FP32 and FP16 not at all (FP32 on 24^3x48, x 2 54.6
+    // against 52.8, x 4 93.1 against 90.1; FP16 x 4 67.0 against 63.7)
     const bool many = items > 4096;
-    L.R = std::min(n, f64 ? (many ? 1 : 2) : f16 ? (n > 4 ? 2 : 1) : (many ? 2 : 1));
+    L.R = std::min(n, f64 ? (many ? 1 : 2) : percol ? 1 : f16 ? (n > 4 ? 2 : 1) : (many ? 2 : 1));
     L.bs = f64 && n > 1 ? 128 : 64;
 }
 
@@ -674,7 +682,7 @@ static HopLaunch hop_base(const OpCall& c, int dagger, int out_parity)
     L.march = (t.march > 0 && G->g.blocked && G->g.L[3] % t.march == 0) ? t.march : 0;
     L.lds = t.lds;
     int order = t.order;
-    if (!t.chosen()) pick_kernel(L, G->g, order);
+    if (!t.chosen()) pick_kernel(L, G->g, c.ct != nullptr, order);
     L.dagger = dagger;
     L.g = with_order(G->g, order);
     L.last_t = order >= 1;
@@ -3045,7 +3053,7 @@ int bq_autotune(bq_op op, int prec, int nrhs)
         L.prec = prec;
         L.ncol = nrhs;
         int order = 0;
-        pick_kernel(L, op->gauge->g, order);
+        pick_kernel(L, op->gauge->g, false, order);
         const Tune t = L.split ? Tune{recon} : Tune{recon, L.R, L.bs, 0, L.lds, order};
         const double ms = time_of(t, 5);
         if (ms < 1e300) cand.push_back({ms, t});
