@@ -391,6 +391,7 @@ struct Args {
     double* partial;
     int nwaves, pstride;
     int tpb, gw, nch;  // tiles per workgroup, column groups per workgroup, group chunks
+    int stage_nt;      // tile-shared: staged links and clover stream past the L2
     int nblk;          // tile blocks
     const int* status;
     int statmask;
@@ -1112,9 +1113,9 @@ __global__ __launch_bounds__(lds_max_threads<P>()) __attribute__((amdgpu_waves_p
     const int tile = tile_at(A.g, lt);                // lt < ntiles: one tile per workgroup
     const int base = tile * kTile;
     // 1. stage the tile's links (8 half hops x 64 sites) and clover.  One workgroup (one per chunk of
-    // columns) reads them, so they stream past the neighbour spinors in the L2: the launch is bound by
-    // what the L2s miss (32^3x64 x 12, FP32: 6.5 GB in 0.9 ms).  Mhat at 24^3x48, cached -> streamed: FP32 x
-    // 12 755 -> 731 us, FP64 x 4 667 -> 640, x 16 2362 -> 2304, FP16 x 8 368 -> 361
+    // columns) reads them, so on large lattices they stream past the neighbour spinors in the L2
+    // (stage_nt, see launch_t): the launch is bound by what the L2s miss (32^3x64 x 12, FP32: 6.5 GB in 0.9 ms)
+    const bool nt = A.stage_nt;
     for (int t = threadIdx.x; t < 8 * kTile; t += blockDim.x) {
         const int site = t & (kTile - 1), H = t >> kTileLog;
         const int mu = H >> 1;
@@ -1125,8 +1126,9 @@ __global__ __launch_bounds__(lds_max_threads<P>()) __attribute__((amdgpu_waves_p
             const Site st = site_of(A.g, A.parity, j);
             const int jn = nbr(A.g, st, mu, bw ? -1 : +1);
             Raw<P, link_cx<RECON>()> raw;
-            load_units<P, link_cx<RECON>(), kBufNT>(buf_rsrc(A.U[(bw ? 1 - A.parity : A.parity) * 4 + mu]), bw ? jn : j,
-                                                    raw);
+            const __amdgpu_buffer_rsrc_t rs = buf_rsrc(A.U[(bw ? 1 - A.parity : A.parity) * 4 + mu]);
+            if (nt) load_units<P, link_cx<RECON>(), kBufNT>(rs, bw ? jn : j, raw);
+            else load_units<P, link_cx<RECON>(), LA>(rs, bw ? jn : j, raw);
             link_from_raw<P, RECON>(raw, u);
         } else {
 #pragma unroll
@@ -1141,7 +1143,8 @@ __global__ __launch_bounds__(lds_max_threads<P>()) __attribute__((amdgpu_waves_p
         const __amdgpu_buffer_rsrc_t rs = buf_rsrc(C);
         for (int t = threadIdx.x; t < (NU / 2) * kTile; t += blockDim.x) {
             const int site = t & (kTile - 1), q = t >> kTileLog;
-            const bq_u4v v = buf_load16<kBufNT>(rs, (uint32_t)toff<U>(site, 2 * q, NU) * 8u);
+            const uint32_t at = (uint32_t)toff<U>(site, 2 * q, NU) * 8u;
+            const bq_u4v v = nt ? buf_load16<kBufNT>(rs, at) : buf_load16<LA>(rs, at);
             sc[(2 * q) * kTile + site] = __builtin_bit_cast(U, bq_u2v_b{v.x, v.y});
             sc[(2 * q + 1) * kTile + site] = __builtin_bit_cast(U, bq_u2v_b{v.z, v.w});
         }
@@ -1565,6 +1568,11 @@ hipError_t launch_t(const HopLaunch& L, hipStream_t st)
         A.nch = (G + A.gw - 1) / A.gw;
         A.gw = (G + A.nch - 1) / A.nch;  // balance the chunks
         A.nblk = L.g.ntiles;
+        // Links and clover of up to 64 MiB are still in the caches at the next launch when they are read
+        // through them.  Mhat in us, cached and streamed: 16^3x32 FP32 18-real (57 MB) x 4 57.9 and
+        // 63.8, x 8 83.3 and 87.4; 12^3x24 FP64 (36 MB) x 8 71.0 and 74.7; 16^3x64 FP16 (44 MB) x 8 111 and 118;
+        // 16^3x32 FP64 12-real (88 MB) x 8 182 and 177; 24^3x48 FP32 (287 MB) x 12 623 and 609
+        A.stage_nt = (long)L.g.ntiles * kTile * (8 * RECON + 72) * (P::id == PREC_F16 ? 2 : (int)sizeof(T)) > 64L << 20;
         // G > 1 here: the other column groups' waves of a tile read the same clover (FP64 keeps it
         // in global memory), so loads go through the caches
         auto launch = [&](auto kern, bool& attr) -> hipError_t {
