@@ -380,8 +380,9 @@ int bq_time_copy(bq_context ctx, uint64_t bytes, int reps, void* stream, double*
  * lie in its own tile from the other lanes' registers instead of from memory.
  * order: the traversal of the 64-site tiles by the plain and tile-shared stencils: 0 visits them in
  * blocks of 4x4 (z,t) planes where (x,y) planes hold whole tiles, else in memory order; 1 cuts each
- * time slice into up to 8 slabs, one per XCD, and walks each slab slice by slice (where time slices
- * hold whole tiles; elsewhere memory order; ignored by the t-marching stencil); 2 is order 1
+ * time slice into up to 8 slabs, one per XCD, and walks each slab slice by slice (where (x,y) planes
+ * hold whole tiles, or time slices do and the launch works on 4096 tiles or 256 MiB of spinors;
+ * elsewhere memory order; ignored by the t-marching stencil); 2 is order 1
  * and, on a lattice with a multiple of 8 tile blocks, has each XCD walk its tile blocks once per column-group chunk
  * (fewer columns in flight per XCD; links and clover are read once per chunk).  Errors: BQ_ERR_INVALID for a configuration
  * that is not compiled or out of range.  Results do not depend on the configuration.

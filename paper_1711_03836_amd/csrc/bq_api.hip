@@ -151,11 +151,13 @@ static int gcd_of(int a, int b)
 // thick, then trades y extent for thickness while it is more than twice as wide: fewer of its sites
 // have neighbours in another slab (32^3x64 x 12, K1: 32 x 4 rows FP64 2154 us, FP32 850, FP16 653;
 // 16 x 8 2064, 848, 664).  Where only whole slices do (24^3x48) it is any gcd(tiles, 8)th of the slice
-// (K1 x 12 against walking slice after slice: FP64 744 -> 667 us, FP32 302 -> 292, FP16 219 -> 214).
-static Geom with_order(Geom g, int order)
+// (K1 x 12 against walking slice after slice: FP64 744 -> 667 us, FP32 302 -> 292, FP16 219 -> 214), and
+// only for launches whose spinors the last-level cache does not hold (slabs; Mhat x 12 on 12^3x24: FP64 116 us
+// in memory order, 121 in slabs, FP32 53 and 61; on 8^3x16 FP64 44 and 54).
+static Geom with_order(Geom g, int order, bool slabs)
 {
     g.cmajor = order == 2;
-    if (order < 1) return g;
+    if (!slabs) return g;
     if (g.blocked) {
         int ub = g.nu, zb = g.L[2] / gcd_of(g.L[2], 8);
         const double rows = (double)g.L[1] / g.nu;  // per tile
@@ -570,6 +572,12 @@ static Tune get_tune(bq_context ctx, int prec, int ncol)
     return it != ctx->tune.end() ? it->second : Tune{prec == PREC_F16 ? 12 : 18};
 }
 
+// Whether a launch on n columns works on more spinors than the last-level cache holds
+static bool beyond_llc(const Geom& g, int prec, int n)
+{
+    return g.ntiles >= 4096 || (long)g.ntiles * kTile * spinor_nu(prec) * (long)unit_bytes(prec) * n > 256L << 20;
+}
+
 // Two rounds of the hop-split kernel's workgroups (one per tile and column) on 256 CUs, which by their
 // registers hold one FP64 or two FP32/FP16 of them at a time.
 static bool split_fits(const Geom& g, int prec, int n) { return (long)g.ntiles * n <= (prec == PREC_F64 ? 512 : 1024); }
@@ -608,7 +616,7 @@ static void pick_kernel(HopLaunch& L, const Geom& g, bool percol, int& order)
         L.lds = 1;
         L.R = 1;
         L.bs = 768;
-        if (items * kTile * 12 * (f64 ? 16 : f16 ? 4 : 8) > 256L << 20) order = 1;
+        if (beyond_llc(g, L.prec, n)) order = 1;
         return;
     }
     // Two columns per wave halve the link reads but also the waves: worth it beyond 4096 one-column
@@ -684,8 +692,9 @@ static HopLaunch hop_base(const OpCall& c, int dagger, int out_parity)
     int order = t.order;
     if (!t.chosen()) pick_kernel(L, G->g, c.ct != nullptr, order);
     L.dagger = dagger;
-    L.g = with_order(G->g, order);
-    L.last_t = order >= 1;
+    const bool slabs = order >= 1 && (G->g.blocked || beyond_llc(G->g, prec, L.ncol));
+    L.g = with_order(G->g, order, slabs);
+    L.last_t = slabs;
     L.parity = out_parity;
     const LinkSet* ls = G->get(prec, L.recon);
     for (int k = 0; k < 8; k++) L.U[k] = ls ? ls->U[k] : nullptr;
