@@ -578,10 +578,6 @@ static bool beyond_llc(const Geom& g, int prec, int n)
     return g.ntiles >= 4096 || (long)g.ntiles * kTile * spinor_nu(prec) * (long)unit_bytes(prec) * n > 256L << 20;
 }
 
-// Two rounds of the hop-split kernel's workgroups (one per tile and column) on 256 CUs, which by their
-// registers hold one FP64 or two FP32/FP16 of them at a time.
-static bool split_fits(const Geom& g, int prec, int n) { return (long)g.ntiles * n <= (prec == PREC_F64 ? 512 : 1024); }
-
 // The kernel of a launch whose configuration nobody chose, by tiles and columns (percol: each
 // with a clover of its own).  Times are of Mhat (K1 + K2, 18-real links; FP16 12) in us on one MI355X,
 // with percol of a request in a 16-slot session solved to 1e-10, in ms.
@@ -591,11 +587,13 @@ static void pick_kernel(HopLaunch& L, const Geom& g, bool percol, int& order)
     const long items = (long)g.ntiles * n;
     const bool f64 = L.prec == PREC_F64, f16 = L.prec == PREC_F16;
     L.march = L.lds = 0;
-    // Within two rounds of its workgroups a launch is one or two chains of memory latencies and the hop split
+    // Within two rounds of the hop split's workgroups (one per tile and column; by their registers 256 CUs hold
+    // one FP64 or two FP32/FP16 each) a launch is one or two chains of memory latencies and the split
     // shortens it (8^4: FP64 20.7 -> 10.6, FP32 x 8 43 -> 10.3; 12^3x24 FP32 x 3 20.7 -> 19.2);
-    // beyond it the kernels that use fewer waves per site win (12^3x24 FP64 x 2 31.1 against 28.7,
-    // FP32 x 4 25.3 against 24.8)
-    if (split_fits(g, L.prec, n)) {
+    // beyond them the kernels that use fewer waves per site win (12^3x24 FP64 x 2 31.1 against 28.7,
+    // FP32 x 4 25.3 against 24.8), and in FP32 with two full rounds (16^3x32 x 1: 28.5 against 28.4, M 29.4 and
+    // 27.4; 16^4 x 2: 22.0 and 20.9; FP16 20.5 against 21.9, M 20.8 and 21.9; with percol 8.5 against 9.3)
+    if (items <= (f64 ? 512 : f16 || percol ? 1024 : 1023)) {
         L.split = 1;
         L.R = 1;
         return;
@@ -612,7 +610,10 @@ static void pick_kernel(HopLaunch& L, const Geom& g, bool percol, int& order)
     // soon read again: FP32 x 8 on 16^3x32 34.6 against 30.9, x 16 65.0 and 59.7, on 24^3x48 167 and 173, 324 and
     // 354; FP64 x 16 on 12^3x24 29.2 and 28.5, on 16^3x32 89.1 and 95.2; FP16 x 16 16.9 and 17.9, 46.3 and 47.5
     const int least = !percol || f16 ? 0 : f64 ? 1024 : 4096;  // tiles
-    if (n >= (f64 ? 3 : f16 ? 8 : 6) && g.ntiles >= least) {
+    // FP64 workgroups run one per CU: not where few columns share a second round that is less than half
+    // full (12^3x24, 324 tiles, K1 + M + Mhat: x 4 106 against 101, x 6 154 against 139; x 3 93 against 101)
+    const bool thin = f64 && n > 3 && n < 7 && g.ntiles > 256 && g.ntiles <= 384;
+    if (n >= (f64 ? 3 : f16 ? 8 : 6) && g.ntiles >= least && !thin) {
         L.lds = 1;
         L.R = 1;
         L.bs = 768;
@@ -620,13 +621,14 @@ static void pick_kernel(HopLaunch& L, const Geom& g, bool percol, int& order)
         return;
     }
     // Two columns per wave halve the link reads but also the waves: worth it beyond 4096 one-column
-    // waves, four per SIMD (FP32 x 2: 16^3x32 43 against 33.3, 32^3x64 535 against 661), not for
-    // FP64, which then runs two waves per SIMD (32^3x64 x 2: 1335 against 1176), nor for FP16, whose
-    // links are half as large, below five columns (24^3x48 x 4: 169 against 165; x 6: 254 against 269), and
+    // waves, four per SIMD, or 2048 tiles (FP32 x 2: 16^3x32 43 against 33.3, 16^3x64 68.8 against 72.3, 32^3x64 535
+    // against 661), not for FP64, which then runs two waves per SIMD (32^3x64 x 2: 1335 against 1176), nor
+    // for FP16, whose links are half as large, below five columns (24^3x48 x 4: 169 against 165; x 6: 254 against
+    // 269) or where the last wave is half empty (K1 + M + Mhat on 12^3x24: x 5 90 against 71, x 7 94 and 87), and
     // with percol, where there is less to share, for FP32 and FP16 not at all (FP32 on 24^3x48, x 2 54.6
     // against 52.8, x 4 93.1 against 90.1; FP16 x 4 67.0 against 63.7)
     const bool many = items > 4096;
-    L.R = std::min(n, f64 ? (many ? 1 : 2) : percol ? 1 : f16 ? (n > 4 ? 2 : 1) : (many ? 2 : 1));
+    L.R = std::min(n, f64 ? (many ? 1 : 2) : percol ? 1 : f16 ? (n == 6 ? 2 : 1) : (many || g.ntiles >= 2048 ? 2 : 1));
     L.bs = f64 && n > 1 ? 128 : 64;
 }
 
