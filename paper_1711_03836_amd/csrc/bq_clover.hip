@@ -459,14 +459,52 @@ __device__ __forceinline__ void block_mul(const cx<T> (&cb)[18], const cx<T>* v,
         }
 }
 
-// out = C in for the columns c0 .. c0 + cols - 1 of one tile per wavefront.  A shared clover is read once
-// for all of them and kept in registers: one of its two blocks per wavefront (blockIdx.z) in FP64 and
-// FP32, both in FP16, whose spinors have one scale for the site.  Bound by HBM; read once per column it
-// was most of the traffic: 24^3x48 x 12, both parities: FP64 1174 -> 678 us, FP32 555 -> 345, FP16 285 -> 197.
+// the packed values of block blk of site j
+template <class P>
+__device__ __forceinline__ void load_block(const typename P::unit* C, int j, int blk, cx<typename P::real> (&cb)[18])
+{
+    if constexpr (P::id == PREC_F16) {
+#pragma unroll
+        for (int u = 0; u < 9; u++) CxIO<P16, 2>::unpack(at(C, j, blk * 9 + u, 18), cb[2 * u], cb[2 * u + 1]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 18; k++) {
+            const auto t = at(C, j, blk * 18 + k, 36);
+            cb[k] = {t.x, t.y};
+        }
+    }
+}
+
+// out = C in, one column of one tile per wavefront
 template <class P>
 __global__ __launch_bounds__(128) void k_clover_apply(const Geom g, const typename P::unit* C0, SpinorPtr<P> in,
-                                                      SpinorPtr<P> out, int ncol, int cols, int percol, const CloverCols cc,
-                                                      const int* status, int statmask)
+                                                      SpinorPtr<P> out, int percol, const CloverCols cc, const int* status,
+                                                      int statmask)
+{
+    using T = typename P::real;
+    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    const int c = blockIdx.y;
+    if (j >= g.Vh || (status && !col_selected(status, statmask, c))) return;
+    const typename P::unit* C = percol ? (const typename P::unit*)cc.p[c] : C0;
+    cx<T> v[12], y[12];
+    load_spinor(in, c, j, v);
+#pragma unroll
+    for (int b = 0; b < 2; b++) {
+        cx<T> cb[18];
+        load_block<P>(C, j, b, cb);
+        block_mul(cb, v + 6 * b, y + 6 * b);
+    }
+    store_spinor(out, c, j, y);
+}
+
+// The same for the columns c0 .. c0 + cols - 1.  A shared clover is read once for all of them and kept in
+// registers: one of its two blocks per wavefront (blockIdx.z) in FP64 and FP32, both in FP16, whose
+// spinors have one scale for the site.  Bound by HBM; read once per column the clover was most of the
+// traffic: 24^3x48 x 12, both parities: FP64 1174 -> 678 us, FP32 555 -> 345, FP16 285 -> 197.
+template <class P>
+__global__ __launch_bounds__(128) void k_clover_apply_cols(const Geom g, const typename P::unit* C0, SpinorPtr<P> in,
+                                                           SpinorPtr<P> out, int ncol, int cols, int percol,
+                                                           const CloverCols cc, const int* status, int statmask)
 {
     using T = typename P::real;
     constexpr int NB = P::id == PREC_F16 ? 2 : 1;  // blocks per wavefront
@@ -475,20 +513,9 @@ __global__ __launch_bounds__(128) void k_clover_apply(const Geom g, const typena
     const int c0 = blockIdx.y * cols, c1 = min(ncol, c0 + cols);
     const int b0 = NB == 2 ? 0 : blockIdx.z;
     cx<T> cb[NB][18];
-    auto load_clover = [&](const typename P::unit* C) {
+    const auto load_clover = [&](const typename P::unit* C) {
 #pragma unroll
-        for (int b = 0; b < NB; b++) {
-            if constexpr (P::id == PREC_F16) {
-#pragma unroll
-                for (int u = 0; u < 9; u++) CxIO<P16, 2>::unpack(at(C, j, (b0 + b) * 9 + u, 18), cb[b][2 * u], cb[b][2 * u + 1]);
-            } else {
-#pragma unroll
-                for (int k = 0; k < 18; k++) {
-                    auto t = at(C, j, (b0 + b) * 18 + k, 36);
-                    cb[b][k] = {t.x, t.y};
-                }
-            }
-        }
+        for (int b = 0; b < NB; b++) load_block<P>(C, j, b0 + b, cb[b]);
     };
     if (!percol) load_clover(C0);
     for (int c = c0; c < c1; c++) {
@@ -600,18 +627,30 @@ hipError_t launch_clover_apply(int prec, const Geom& g, const void* clov, FieldA
     const int tiles = pad_sites(g.Vh) / kTile;
     const int groups = percol ? ncol : std::max(1, std::min(ncol, 4096 / (tiles * nz)));
     const int cols = (ncol + groups - 1) / groups;
-    const dim3 grid((g.Vh + bs - 1) / bs, (ncol + cols - 1) / cols, nz);
+    // One column and both blocks per wavefront instead: FP16 with nothing to share, or whose clover the L2s
+    // hold (16^3x32 x 6 20.2 us against 22.7, x 10 27.9 and 30; 20^3x40 x 4 47 and 34); FP32 on a few tiles
+    // (6x10x14x18 x 12 10.5 against 11.3; 16^4 x 6 17.9 and 16.6); one column in long streams (32^3x64 FP64
+    // 382 against 399; 20^3x40 58 and 49)
+    const bool single = prec == PREC_F16 ? percol || ncol == 1 || tiles < 2048
+                                         : (ncol == 1 && tiles >= 8192) || (prec == PREC_F32 && tiles < 256);
+    const int blocks = (g.Vh + bs - 1) / bs;
 #define CA(P, U)                                                                                                     \
-    hipLaunchKernelGGL(k_clover_apply<P>, grid, dim3(bs), 0, st, g, (const U*)clov,                                  \
-                       SpinorPtr<P>{(U*)in.d, in.s, in.cstride, in.sstride},                                         \
-                       SpinorPtr<P>{(U*)out.d, out.s, out.cstride, out.sstride}, ncol, cols, percol, cc, status, statmask)
+    {                                                                                                                \
+        const SpinorPtr<P> i{(U*)in.d, in.s, in.cstride, in.sstride}, o{(U*)out.d, out.s, out.cstride, out.sstride}; \
+        if (single)                                                                                                  \
+            hipLaunchKernelGGL(k_clover_apply<P>, dim3(blocks, ncol), dim3(bs), 0, st, g, (const U*)clov, i, o, percol, cc, \
+                               status, statmask);                                                                    \
+        else                                                                                                         \
+            hipLaunchKernelGGL(k_clover_apply_cols<P>, dim3(blocks, (ncol + cols - 1) / cols, nz), dim3(bs), 0, st, g, \
+                               (const U*)clov, i, o, ncol, cols, percol, cc, status, statmask);                      \
+    }
     switch (prec) {
-    case PREC_F64: CA(P64, double2); break;
-    case PREC_F32: CA(P32, float2); break;
-    case PREC_F16: CA(P16, uint2); break;
-#undef CA
+    case PREC_F64: CA(P64, double2) break;
+    case PREC_F32: CA(P32, float2) break;
+    case PREC_F16: CA(P16, uint2) break;
     default: return hipErrorInvalidValue;
     }
+#undef CA
     return hipGetLastError();
 }
 
