@@ -196,13 +196,17 @@ __global__ __launch_bounds__(kTile * 4) void k_spinor_turn(double2* __restrict__
     if constexpr (P::id == PREC_F16) f.s += (w % NP) * hss;
     cx<T> v[12];
     if constexpr (IMPORT) {
+        // all twelve loads are on their way before the first is used (a part-filled tile reads its last
+        // value again: a test around each load would have made them wait for one another)
+        bq_d2 x[12];
+        if (nu > 0)
+#pragma unroll
+            for (int i = 0; i < 12; i++)
+                x[i] = __builtin_nontemporal_load((const bq_d2*)can + canon_of(site0, min(i * kTile + lane, nu - 1), odd));
 #pragma unroll
         for (int i = 0; i < 12; i++) {
             const int u = i * kTile + lane;
-            if (u < nu) {
-                const bq_d2 x = __builtin_nontemporal_load((const bq_d2*)can + canon_of(site0, u, odd));
-                t[u + u / 12 * (kTurnRow - 12)] = C{(T)x.x, (T)x.y};
-            }
+            if (u < nu) t[u + u / 12 * (kTurnRow - 12)] = C{(T)x[i].x, (T)x[i].y};
         }
         __syncthreads();
 #pragma unroll
