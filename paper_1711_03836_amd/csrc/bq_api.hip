@@ -579,9 +579,9 @@ static bool beyond_llc(const Geom& g, int prec, int n)
 }
 
 // The kernel of a launch whose configuration nobody chose, by tiles and columns (percol: each
-// with a clover of its own).  Times are of Mhat (K1 + K2, 18-real links; FP16 12) in us on one MI355X,
+// with a clover of its own; solving: in a solver's iterations).  Times are of Mhat (K1 + K2, 18-real links; FP16 12) in us on one MI355X,
 // with percol of a request in a 16-slot session solved to 1e-10, in ms.
-static void pick_kernel(HopLaunch& L, const Geom& g, bool percol, int& order)
+static void pick_kernel(HopLaunch& L, const Geom& g, bool percol, bool solving, int& order)
 {
     const int n = L.ncol;
     const long items = (long)g.ntiles * n;
@@ -592,8 +592,9 @@ static void pick_kernel(HopLaunch& L, const Geom& g, bool percol, int& order)
     // shortens it (8^4: FP64 20.7 -> 10.6, FP32 x 8 43 -> 10.3; 12^3x24 FP32 x 3 20.7 -> 19.2);
     // beyond them the kernels that use fewer waves per site win (12^3x24 FP64 x 2 31.1 against 28.7,
     // FP32 x 4 25.3 against 24.8), and in FP32 with two full rounds (16^3x32 x 1: 28.5 against 28.4, M 29.4 and
-    // 27.4; 16^4 x 2: 22.0 and 20.9; FP16 20.5 against 21.9, M 20.8 and 21.9; with percol 8.5 against 9.3)
-    if (items <= (f64 ? 512 : f16 || percol ? 1024 : 1023)) {
+    // 27.4; 16^4 x 2: 22.0 and 20.9; FP16 20.5 against 21.9, M 20.8 and 21.9) unless in a CG solve, where waves
+    // without an epilogue sum the partials (16^3x32 x 1 8.9 ms against 9.5; with percol 8.5 and 9.3)
+    if (items <= (f64 ? 512 : f16 || percol || solving ? 1024 : 1023)) {
         L.split = 1;
         L.R = 1;
         return;
@@ -692,7 +693,7 @@ static HopLaunch hop_base(const OpCall& c, int dagger, int out_parity)
     L.march = (t.march > 0 && G->g.blocked && G->g.L[3] % t.march == 0) ? t.march : 0;
     L.lds = t.lds;
     int order = t.order;
-    if (!t.chosen()) pick_kernel(L, G->g, c.ct != nullptr, order);
+    if (!t.chosen()) pick_kernel(L, G->g, c.ct != nullptr, c.status != nullptr, order);
     L.dagger = dagger;
     const bool slabs = order >= 1 && (G->g.blocked || beyond_llc(G->g, prec, L.ncol));
     L.g = with_order(G->g, order, slabs);
@@ -3064,7 +3065,7 @@ int bq_autotune(bq_op op, int prec, int nrhs)
         L.prec = prec;
         L.ncol = nrhs;
         int order = 0;
-        pick_kernel(L, op->gauge->g, false, order);
+        pick_kernel(L, op->gauge->g, false, true, order);
         const Tune t = L.split ? Tune{recon} : Tune{recon, L.R, L.bs, 0, L.lds, order};
         const double ms = time_of(t, 5);
         if (ms < 1e300) cand.push_back({ms, t});
