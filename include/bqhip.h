@@ -169,8 +169,8 @@ typedef void (*bq_dealloc_fn)(void* ptr, void* alloc_ctx);
  *                     Without a caller's allocator, blocks that buffers give back are kept for
  *                     the next buffers of their size (at most 8 GiB and an eighth of the budget,
  *                     within the budget; the longest unused make room for others) until the
- *                     context is freed, bq_context_trim is called, an allocation of the
- *                     library needs room or a context is created with a budget of 0.
+ *                     context is freed, bq_context_trim is called or an allocation of the
+ *                     library needs room; such blocks count as free memory here.
  *   alloc, dealloc    route every device allocation of the context (fields, links, clover,
  *                     workspaces) through the caller's allocator; both NULL = hipMalloc/hipFree.
  *                     Before a block goes back to dealloc the library waits for the device

@@ -176,9 +176,8 @@ static Geom with_order(Geom g, int order, bool slabs)
 // FP64 Mhat^dag Mhat took 1.1 ms, 0.56 ms of it in its stencils, and a 32^3x64 12-column FP32 one
 // between 7.5 and 113 ms.  The pool holds at most kPoolMost bytes, an eighth of the budget and
 // what the budget leaves; a block that comes back to a full pool takes the place of the longest unused
-// ones.  All of it is given back by bq_context_trim, with the context, when an allocation fails in any
-// context, and before a new context asks for its budget how much memory is free; as much as is
-// needed where the budget needs it.
+// ones.  All of it is given back by bq_context_trim, with the context, and when an allocation fails in
+// any context (so a new context counts it as free memory); as much as is needed where the budget needs it.
 class BlockPool {
     static const size_t kPoolMost = (size_t)8 << 30;
     std::mutex mu;
@@ -237,6 +236,11 @@ public:
         dirty = dirty || !done;
         return true;
     }
+    size_t held()
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        return bytes;
+    }
     // give back what is beyond `most` bytes
     void shrink(size_t most)
     {
@@ -264,6 +268,13 @@ static void trim_pools()
 {
     std::lock_guard<std::mutex> lk(pools_mu);
     for (BlockPool* p : pools) p->shrink(0);
+}
+static size_t pooled_on(int device)
+{
+    std::lock_guard<std::mutex> lk(pools_mu);
+    size_t n = 0;
+    for (BlockPool* p : pools) n += p->device == device ? p->held() : 0;
+    return n;
 }
 
 struct bq_context_s {
@@ -1851,9 +1862,8 @@ int bq_context_create(int device, uint64_t hbm_budget_bytes, bq_alloc_fn alloc, 
     auto c = std::make_unique<bq_context_s>();
     c->device = c->pool.device = device;
     size_t fr = 0, tot = 0;
-    if (!hbm_budget_bytes) trim_pools();  // blocks that other contexts keep count as free
     HIPCHK(hipMemGetInfo(&fr, &tot));
-    c->budget = hbm_budget_bytes ? hbm_budget_bytes : (uint64_t)(0.9 * (double)fr);
+    c->budget = hbm_budget_bytes ? hbm_budget_bytes : (uint64_t)(0.9 * (double)(fr + pooled_on(device)));
     c->alloc = alloc;
     c->dealloc = dealloc;
     c->alloc_ctx = alloc_ctx;

@@ -1,5 +1,6 @@
 """Device blocks kept for the next buffers, where others want the memory too: other sizes, other allocators,
 other contexts, threads, and streams that still work on a field when it is freed."""
+import re
 import threading
 
 import numpy as np
@@ -52,11 +53,15 @@ def test_memory_goes_back(bq):
     ctx.trim()
     assert abs(before - _free()) / MIB < 64
     ctx.trim()
-    # a context without a budget of its own measures the free memory without the others' blocks
+    # a context without a budget of its own counts the blocks that others keep as free
     _pass_through(bq, ctx, 10)
     _pass_through(bq, other, 9)
-    bq.Context(0)
-    assert abs(before - _free()) / MIB < 64
+    assert (before - _free()) / MIB > 1800
+    with pytest.raises(bq.BqError) as e:
+        bq.Field(bq.Context(0), DIMS, bq.BQ_ODD, bq.BQ_F64, 5000)  # 480 GiB: beyond any budget
+    assert e.value.code == bq.BQ_ERR_OOM
+    budget = int(re.search(r"of (\d+) in use", str(e.value)).group(1))
+    assert abs(budget - 0.9 * before) / MIB < 64
     for f in warm:
         f.close()
 
