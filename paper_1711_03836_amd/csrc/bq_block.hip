@@ -738,8 +738,7 @@ inline dim3 unit_grid(size_t units, int y = 1) { return dim3((unsigned)((units +
 
 }  // namespace
 
-// workgroups of a Gram launch: two to four pieces of 16 units per wavefront on small lattices, at most
-// eight workgroups per CU
+// workgroups of a Gram launch: one per tile, 12 pieces of 16 units per wavefront, and at most eight per CU
 int block_gram_parts(int tiles) { return std::min(2048, tiles); }
 
 hipError_t launch_block_gram(FieldArg X, FieldArg Y, double s, const BlockState& S, int vh, int tiles, double2* partial,
