@@ -613,8 +613,8 @@ static void pick_kernel(HopLaunch& L, const Geom& g, bool percol, bool solving, 
     // The slab walk keeps the +-t slices in the last-level cache; columns that fit there whole lose a
     // little L2 locality to it (one column: 16^3x32 FP32 28.1 in order 0, 29.0 in order 1; 32^3x64 415 and
     // 386.  K1 of several: FP64 x 12 on 16^3x64, 302 MB, 284 and 272, on 16^3x32, 151 MB, 138 and 140; FP32 x 16 on
-    // 16^3x32, 101 MB, 71 and 78, on 20^3x40, 246 MB, 186 and 194, on 48^3x96 6636 and 5469, with chunks of columns
-    // one after another, order 2, 5746; FP16 x 16 on 20^3x40 124 and 124, on 48^3x96 3771 and 3627, order 2 3629)
+    // 16^3x32, 101 MB, 71 and 78, on 20^3x40, 246 MB, 186 and 194, on 48^3x96 7166 and 5953, with chunks of columns
+    // one after another, order 2, 6235; FP16 x 16 on 20^3x40 124 and 124, on 48^3x96 4406 and 4240, order 2 4262)
     order = g.ntiles >= 4096 ? 1 : 0;
     // From these column counts on, links and clover read once per tile into LDS beat reading them
     // per wave (32^3x64: FP64 x 3 1442 against 1572, x 2 1307 against 1176; FP32 x 6 1176 against

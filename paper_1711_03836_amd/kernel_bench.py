@@ -29,6 +29,8 @@ def main():
     ap.add_argument("--kind", default="K1", help="an operator kind (K1, MHAT, ...) or SOLVE")
     ap.add_argument("--reps", type=int, default=20)
     ap.add_argument("--tune", default="auto", help="'auto' (timed) or recon,R,bs[,march[,lds[,order]]]; recon,0,0: by size")
+    ap.add_argument("--repeat-t", type=int, default=1, help="make links and sources for 1/N of the time slices and "
+                    "repeat them N times (host generation of a large lattice takes minutes)")
     ap.add_argument("--eps", type=float, default=0.2)
     ap.add_argument("--kappa", type=float, default=0.124)
     ap.add_argument("--csw", type=float, default=1.5)
@@ -81,7 +83,8 @@ def main():
 
     dims = tuple(int(v) for v in args.dims.split(","))
     prec = PREC[args.prec]
-    U = inputs.gauge_field(dims, args.eps, seed=20171110)
+    short = (*dims[:3], dims[3] // args.repeat_t)  # t is the slowest site index
+    U = np.tile(inputs.gauge_field(short, args.eps, seed=20171110), (1, args.repeat_t, 1, 1))
     ctx = bq.Context(0)
     G = bq.Gauge(ctx, dims, U, t_bc=-1)
     op = bq.Op(G, args.kappa, args.csw, args.mu)
@@ -114,7 +117,7 @@ def main():
     si, so = bq.OP_SUBSETS[kind]
     fi = bq.Field(ctx, dims, si, prec, args.nrhs)
     fo = bq.Field(ctx, dims, so, prec, args.nrhs)
-    fi.put(inputs.gaussian_spinor(dims, args.nrhs, seed=5))
+    fi.put(np.tile(inputs.gaussian_spinor(short, args.nrhs, seed=5), (1, args.repeat_t, 1, 1)))
     stream = torch.cuda.Stream()
     ms, by = op.time_apply(kind, fi, fo, reps=args.reps, stream=stream)
     print(json.dumps({"kind": args.kind, "dims": dims, "prec": args.prec, "nrhs": args.nrhs,
