@@ -93,7 +93,7 @@ def main():
     log(f"[bench] plaquette {plaq:.6f}; autotuning stencil for {args.inner} x {nrhs} and f64 x {nrhs}")
     for prec in {inner, 0}:
         op.autotune(prec, nrhs)
-        log(f"[bench]   tune prec={prec}: recon/R/bs = {ctx.tune_get(prec, nrhs)}")
+        log(f"[bench]   tune prec={prec}: recon/R/bs/march/lds/order = {ctx.tune_get(prec, nrhs)}")
     prefer_profiled_tune(bq, ctx, op, dims, args.inner, inner, nrhs)
 
     def solve(prec):
@@ -205,7 +205,7 @@ def main():
     copy_gbs = device_copy_gbs(ctx, stream)
     roof = {"bound": "hbm", "achieved": k["k1_gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": k["k1_gbs"] / HBM_PEAK_GBS, "traffic": traffic,
-            "kernel": f"K1 = T_ee^-1 D_eo, {args.inner}, {nrhs} columns, recon/R/bs/march/lds={k['tune']}",
+            "kernel": f"K1 = T_ee^-1 D_eo, {args.inner}, {nrhs} columns, recon/R/bs/march/lds/order={k['tune']}",
             "bytes_per_launch": k["k1_bytes"], "traffic_source": traffic_note,
             "copy_gbs": copy_gbs, "frac_of_copy": k["k1_gbs"] / copy_gbs}
     log(f"[bench] device copy {copy_gbs:.0f} GB/s; K1 at {roof['frac_of_copy']:.1%} of it")
@@ -288,7 +288,7 @@ def measured_traffic(dims, inner, nrhs, tune):
     if rec.get("source_digest") != source_digest():
         return None, f"profiles/{name} was taken on other kernel sources"
     if rec.get("tune") and list(rec["tune"]) != list(tune):
-        return None, f"profiles/{name} was taken with recon/R/bs={rec['tune']}, this run uses {list(tune)}"
+        return None, f"profiles/{name} was taken with recon/R/bs/march/lds/order={rec['tune']}, this run uses {list(tune)}"
     return rec["traffic_bytes"], f"profiles/{name} (FETCH_SIZE x{rec['fetch']['factor']:.3f} + WRITE_SIZE " \
                                  f"x{rec['write']['factor']:.3f}, copy-calibrated)"
 
